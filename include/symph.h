@@ -177,10 +177,10 @@ int32_t symph_kv_append(const symph_kv_cache* cache, int32_t layer, const void* 
  *   d_cu_new_lens [n_sessions+1] int32, d_prefix_lens [n_sessions] int32, d_block_table as above.
  *   total_new_tokens = T, max_new_len >= max N_s, max_prefix_len >= max P_s (host copies).  total_new_tokens and
  *   n_sessions size the grids and the work list; max_prefix_len is only checked against the table width; max_new_len
- *   only chooses kernels: a batch with max_new_len * (n_q_heads / n_kv_heads) <= 32 is a decode step and its short
- *   turns run in a kernel that streams K,V with one wave per kv-head.  Neither of the two is relied on for memory safety: a
- *   session longer than stated is still computed, and computed correctly (a turn with more new tokens than stated is
- *   not a short turn for the device-side scheduler and goes through the general kernel), only not at the best speed.
+ *   only chooses kernels: a batch with max_new_len * (n_q_heads / n_kv_heads) <= 32 and total_new_tokens <= n_sessions *
+ *   max_new_len is a decode step and runs in a kernel that streams K,V with one wave per kv-head.  Neither of the two is
+ *   relied on for memory safety: a session longer than stated is still computed, and computed correctly (a decode step
+ *   takes it max_new_len tokens at a time and reads its prefix once for each), only not at the best speed.
  *   scale > 0 and finite (fp32).  d_workspace: device scratch of at least
  *   symph_prefix_prefill_attn_workspace_bytes(...) bytes, 256-byte aligned (may be NULL when that is 0).
  * Arithmetic: bf16 inputs, fp32 accumulation on MFMA, fp32 online softmax, probabilities rounded to bf16 before

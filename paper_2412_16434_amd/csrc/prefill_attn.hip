@@ -154,14 +154,15 @@ struct WorkItem {   // 96 bytes
                                   // workgroup's first K,V loads wait for this item only, not for a table read as well
   int32_t pad[5];
 };
-struct MergeItem {  // 16 bytes: a short turn that the decode kernel cut at the boundary of two shares
-  int32_t s, t0, pslot0, n_chunks;  // pslot0: the decode kernel's slot (2 * workgroup + 0 / 1) of the first piece
+struct MergeItem {  // 16 bytes, one per key range of the decode kernel: the unit that starts in it and leaves it
+  int32_t row0, n_unit, pslot0, n_chunks;  // its first row of q / out and its tokens; slot (2 * range + 0 / 1) of its
+                                           // first piece; n_chunks 0: no such unit
 };
-// Header of the workspace (ints): counts written by the scheduler, a counter of the decode kernel, flags, and a 256-byte
-// page of zeros (source of absent key rows).
+// Header of the workspace (ints): counts and flags written by the scheduler (by the decode kernel in a decode step), and a
+// 256-byte page of zeros (source of absent key rows).
 constexpr int kHdrInts = 128;
-constexpr int kHdrItems = 0, kHdrChunk = 1, kHdrSplitUnits = 2, kHdrPslots = 3, kHdrDecSessions = 4, kHdrDecTiles = 5,
-              kHdrDecMerges = 6, kHdrFlags = kAttnHdrFlags;
+constexpr int kHdrItems = 0, kHdrChunk = 1, kHdrSplitUnits = 2, kHdrPslots = 3, kHdrDecTiles = 5,
+              kHdrFlags = kAttnHdrFlags;
 static_assert(kHdrFlags < kAttnHdrInts && kAttnHdrInts <= 64, "the counts and flags lie in front of the zero page");
 constexpr int kZeroPageInt = 64;
 constexpr int kPartialFloats = 256 * 66;  // per workgroup: 64 accumulators + running max + running sum per thread
@@ -176,9 +177,6 @@ struct SchedParams {
   const int32_t* prefix_lens;
   int32_t n_sessions, bmt, n_kv_heads, target, target_slots, c_min, coarse_ok;
   int32_t items_bound, merges_bound, pslots_bound;
-  int32_t bmt_dec;      // sessions with at most this many new tokens go to the decode kernel (0: none do)
-  int32_t* dec_s;       // their indices, in session order
-  int32_t* dec_off;     // exclusive prefix sum of their key counts in 32-key tiles (one more entry: the total)
   int32_t* hdr;
   WorkItem* items;
   int32_t* merge_cnt;   // [merges_bound][n_kv_heads]: chunks of a split unit that have written their partial result
@@ -273,8 +271,8 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(const Sche
     flags_s = 0;
   }
   if (tid < kSchedBuckets) hist[tid] = 0;
-  // unit offsets: exclusive prefix sum of ceil(N_s / bmt); short turns: their count and their keys in 32-key tiles
-  int U = 0, n_dec = 0, dec_total = 0;
+  // unit offsets: exclusive prefix sum of ceil(N_s / bmt)
+  int U = 0;
   for (int base = 0; base < S; base += kSchedThreads) {
     const int s = base + tid;
     // the lengths are read from memory once and kept in LDS for the passes below
@@ -290,31 +288,16 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(const Sche
     block_inclusive_scan2(nq, zero, wave_sums, tot_q, tot_z);
     if (s < S) unit_off[s] = U + nq - (N > 0 ? (N + p.bmt - 1) / p.bmt : 0);
     U += tot_q;
-    if (p.bmt_dec > 0) {
-      // Short turns (1 <= N_s <= bmt_dec) are not cut into work items: the decode kernel splits the concatenation of
-      // their key ranges evenly among its workgroups, and needs their indices and the prefix sum of their lengths.
-      const int is_dec = N >= 1 && N <= p.bmt_dec;
-      const int nt = is_dec ? (P + N + 31) / 32 : 0;
-      int ic = is_dec, itl = nt, tot_c, tot_t;
-      block_inclusive_scan2(ic, itl, wave_sums, tot_c, tot_t);
-      if (is_dec) {
-        p.dec_s[n_dec + ic - 1] = s;
-        p.dec_off[n_dec + ic - 1] = dec_total + itl - nt;
-      }
-      n_dec += tot_c;
-      dec_total += tot_t;
-    }
   }
   if (tid == 0) {
     unit_off[S] = U;
-    if (p.bmt_dec > 0) p.dec_off[n_dec] = dec_total;
   }
-  if (U == n_dec) {  // every unit is a short turn (each has exactly one), or there is none: nothing for the work list
-    if (tid < 8) p.hdr[tid] = tid == kHdrDecSessions ? n_dec : (tid == kHdrDecTiles ? dec_total : 0);
+  if (U == 0) {  // no session has new tokens
+    if (tid < kAttnHdrInts) p.hdr[tid] = 0;
     return;
   }
   __syncthreads();
-  // unit u -> tiles it has to visit (0: none, it is past the list or a short turn), with its session and lengths
+  // unit u -> tiles it has to visit (0: it is past the list), with its session and lengths
   struct Unit {
     int s, t0, P, N, nt;
   };
@@ -333,7 +316,7 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(const Sche
     r.t0 = (u - unit_off[lo]) * p.bmt;
     r.P = len_prefix[lo];
     r.N = len_new[lo];
-    r.nt = r.N <= p.bmt_dec ? 0 : unit_tiles(r.P, r.N, r.t0, p.bmt);
+    r.nt = unit_tiles(r.P, r.N, r.t0, p.bmt);
     return r;
   };
   // A thread's units (u = tid, tid + 256, ...) and the way they are cut are worked out once and kept in registers
@@ -393,7 +376,7 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(const Sche
   if (tid == 0) {
     // With at least two workgroup-sized units per slot, longest-first dispatch balances well without splitting
     // anything but the longest units; with fewer, every unit is cut so that there are about two pieces per slot.
-    const long long wg_units = (long long)(U - n_dec) * p.n_kv_heads;
+    const long long wg_units = (long long)U * p.n_kv_heads;
     const int target = (p.coarse_ok && wg_units >= 2ll * p.target_slots) ? p.target_slots : p.target;
     // C = ceil(total tiles * kv-heads / target): a single-precision estimate, then exact steps in integers
     const unsigned long long tot = total_tiles_s * (unsigned long long)p.n_kv_heads;
@@ -560,9 +543,7 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(const Sche
     p.hdr[kHdrChunk] = C;
     p.hdr[kHdrSplitUnits] = n_split_s;
     p.hdr[kHdrPslots] = n_pslot_s;
-    p.hdr[kHdrDecSessions] = n_dec;
-    p.hdr[kHdrDecTiles] = dec_total;
-    p.hdr[kHdrDecMerges] = 0;
+    p.hdr[kHdrDecTiles] = 0;
     p.hdr[kHdrFlags] = flags_s;
   }
 }
@@ -587,14 +568,12 @@ struct MfmaParams {
   const WorkItem* items;
   int32_t* merge_cnt;   // [split unit][kv-head]: chunks that have written their partial result
   float* partials;
-  // attn_decode_kernel: the short turns' session indices and tile prefix sums (written by the scheduler), the first of
-  // its partial-result slots, its list of sessions cut at the boundary of two shares and the room in that list
-  const int32_t* dec_s;
-  const int32_t* dec_off;
-  MergeItem* dec_merges;
-  int32_t dec_merges_bound;
-  float* dec_partials;  // [2 * key ranges][n_kv_heads][dec_slot_floats], behind the work items' slots
-  int32_t dec_slot_floats;  // room for the packed piece of the longest short turn the call admits (whole lines)
+  // attn_decode_kernel: new tokens per unit (the call's max_new_len), the rows of q / out, its ranges, one record per
+  // range, and the pieces of units that several ranges share
+  int32_t dec_m, total_new_tokens, dec_ranges;
+  MergeItem* dec_merges;    // [key ranges]
+  float* dec_partials;      // [2 * key ranges][n_kv_heads][dec_slot_floats]
+  int32_t dec_slot_floats;  // room for the packed piece of a unit (whole lines)
 };
 
 
@@ -1177,7 +1156,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
 
 // ------------------------------------------------------------------------------------------------------------
 // Short turns (decode-like rows): a session whose new rows fit one wave (n_new * G <= 32) reads its whole K,V for
-// 32 query rows or fewer, so the work is moving K,V, not arithmetic.  The short turns' key ranges, laid end to end,
+// 32 query rows or fewer, so the work is moving K,V, not arithmetic.  A unit is (session, max_new_len of its new tokens):
+// one per session, more only where the caller understated max_new_len.  The units' key ranges, laid end to end,
 // are cut into equal ranges; a workgroup takes one range for a group of kv-heads, ONE WAVE PER KV-HEAD (eight waves
 // for the usual eight heads, else single-wave workgroups).  A wave loads each 32-key tile of its head into an LDS
 // buffer of its own (direct global->LDS loads) and uses it; the waves of a workgroup therefore read the eight 256-byte
@@ -1193,6 +1173,11 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
 constexpr int kSub = 32;                    // keys per tile of this kernel
 constexpr int kSubBytes = 8 * kGroupBytes;  // 8320
 constexpr int kDecWaveBytes = 2 * kSubBytes;  // K and V of one tile, per wave
+// Shortest range, in tiles.  What a step with little to read takes is the launch, a few trips to memory and the merge of
+// its pieces: 1 / 2 / 4 tiles measured 16.6 / 15.4 / 16.7 us for one session of 1777 tokens.
+constexpr int kDecMinTiles = 2;
+// Source of absent key rows (one head's 256 bytes)
+static __device__ __attribute__((aligned(256))) const unsigned kZeroRow[64] = {};
 
 template <int G, int LB, int HW>
 __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(const MfmaParams p) {
@@ -1200,44 +1185,102 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
   static_assert(kDecPartialFloats * 4 <= kDecWaveBytes, "a wave stages its piece in its own tile buffers");
   __shared__ __attribute__((aligned(16))) char lds[HW * kDecWaveBytes];
 
-  // Even split: the short turns' key ranges, laid end to end, are cut into equal ranges of 32-key tiles, whatever the
-  // sessions' lengths.  A range covers the end of one session, whole sessions and the start of another: one segment
-  // each, processed one after the other.  A session that lies in one range is finished here; the pieces of one that
-  // spans several ranges go to the merge kernel.
+  // Even split: the units' key ranges, laid end to end, are cut into equal ranges of 32-key tiles, whatever the sessions'
+  // lengths.  A range covers the end of one unit, whole units and the start of another: one segment each, processed one
+  // after the other.  A unit that lies in one range is finished here; the pieces of one that spans several ranges go to
+  // the merge kernel.
   const int Hkv = p.n_kv_heads;
   const int n_groups = Hkv / HW;                 // groups of HW kv-heads: one wave per head of the group
   const int wg = blockIdx.x / n_groups;          // the range
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kvh = (blockIdx.x - wg * n_groups) * HW + wave;
-  const int n_dec = p.hdr[kHdrDecSessions];
-  const int total = p.hdr[kHdrDecTiles];
-  const int n_ranges = (int)gridDim.x / n_groups;
-  const int per_wg = (total + n_ranges - 1) / n_ranges;
-  const int range_begin = wg * per_wg;
-  const int range_end = min(total, range_begin + per_wg);
-  if (range_begin >= range_end) return;
   const int lb = LB ? LB : p.log_bs;
   const int bs_mask = (1 << lb) - 1;
-  int unit;  // last one that starts at or before range_begin
-  {
-    int lo = 0, hi = n_dec;
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (p.dec_off[mid] <= range_begin)
-        lo = mid;
-      else
-        hi = mid;
-    }
-    unit = lo;
+
+  // Every workgroup works its range out from the sessions' lengths by itself: one trip to memory and a scan over the
+  // workgroup.  (A scheduling kernel in front, whose result every workgroup then read, was two more trips, a launch and
+  // the gap behind it: 6 us of a decode step.)  Thread t adds up sessions t * c .. t * c + c - 1.
+  const int m = p.dec_m;
+  auto span_of = [&](int s, int& cu_s, int& N, int& P) {  // rows past total_new_tokens do not exist (flagged below)
+    cu_s = p.cu_new_lens[s];
+    N = max(min(p.cu_new_lens[s + 1], p.total_new_tokens) - cu_s, 0);
+    P = max(p.prefix_lens[s], 0);
+  };
+  auto tiles_to = [](int P, int end) { return (P + end + kSub - 1) / kSub; };  // of a unit whose last token is end - 1
+  auto session_tiles = [&](int N, int P) {
+    int n = 0;
+    for (int t0 = 0; t0 < N; t0 += m) n += tiles_to(P, min(N, t0 + m));
+    return n;
+  };
+  __shared__ int scan_sums[HW];
+  __shared__ int start_of[6];  // where the range begins: session, token, the unit's first tile, its session's N, P, cu
+  const int c = (p.n_sessions + 64 * HW - 1) / (64 * HW);
+  int mine = 0;
+  for (int i = 0; i < c; ++i) {
+    const int s = tid * c + i;
+    if (s >= p.n_sessions) break;
+    int cu_s, N, P;
+    span_of(s, cu_s, N, P);
+    mine += session_tiles(N, P);
   }
-  for (int pos = range_begin; pos < range_end; ++unit) {
-  const int unit_begin = p.dec_off[unit], unit_end = p.dec_off[unit + 1];
-  const int s = p.dec_s[unit];
-  const int cu_s = p.cu_new_lens[s];
-  const int N = p.cu_new_lens[s + 1] - cu_s;
-  const int P = p.prefix_lens[s];
-  const int u_begin = pos - unit_begin;                        // this segment: tiles [u_begin, u_end) of the session
+  int incl = wave_inclusive_scan(mine);
+  if ((tid & 63) == 63) scan_sums[wave] = incl;
+  __syncthreads();
+  int total = 0;
+#pragma unroll
+  for (int w = 0; w < HW; ++w) {
+    const int x = scan_sums[w];
+    if (w < wave) incl += x;
+    total += x;
+  }
+  const int per_wg = max((total + p.dec_ranges - 1) / p.dec_ranges, kDecMinTiles);
+  const int range_begin = wg * per_wg;
+  const int range_end = min(total, range_begin + per_wg);
+  MergeItem rec{0, 0, 0, 0};
+  if (blockIdx.x == 0 && tid < kAttnHdrInts) {
+    const bool dropped = p.cu_new_lens[p.n_sessions] > p.total_new_tokens;
+    p.hdr[tid] = tid == kHdrDecTiles ? total : (tid == kHdrFlags && dropped ? 2 : 0);
+  }
+  if (range_begin >= range_end) {
+    if (kvh == 0 && (tid & 63) == 0) p.dec_merges[wg] = rec;
+    return;
+  }
+  if (incl - mine <= range_begin && range_begin < incl) {  // this thread's sessions hold the range's first tile
+    int at = incl - mine;
+    for (int s = tid * c; s < p.n_sessions; ++s) {  // (ends in this thread's sessions: their tiles reach past range_begin)
+      int cu_s, N, P;
+      span_of(s, cu_s, N, P);
+      int t0 = 0;
+      for (; t0 < N; t0 += m) {
+        const int nt = tiles_to(P, min(N, t0 + m));
+        if (at + nt > range_begin) break;
+        at += nt;
+      }
+      if (t0 < N) {
+        start_of[0] = s;
+        start_of[1] = t0;
+        start_of[2] = at;
+        start_of[3] = N;
+        start_of[4] = P;
+        start_of[5] = cu_s;
+        break;
+      }
+    }
+  }
+  __syncthreads();
+  int s = __builtin_amdgcn_readfirstlane(start_of[0]);
+  int t0 = __builtin_amdgcn_readfirstlane(start_of[1]);
+  int unit_begin = __builtin_amdgcn_readfirstlane(start_of[2]);
+  int N = __builtin_amdgcn_readfirstlane(start_of[3]);
+  int P = __builtin_amdgcn_readfirstlane(start_of[4]);
+  int cu = __builtin_amdgcn_readfirstlane(start_of[5]);
+  for (int pos = range_begin; pos < range_end;) {
+  const int cu_s = cu + t0;                                    // the unit's first row
+  const int n_end = min(N, t0 + m);                            // its tokens: t0 .. n_end - 1
+  const int n_unit = n_end - t0;
+  const int unit_end = unit_begin + tiles_to(P, n_end);
+  const int u_begin = pos - unit_begin;                        // this segment: tiles [u_begin, u_end) of the unit
   const int u_end = min(range_end, unit_end) - unit_begin;
   const bool whole = u_begin == 0 && u_end == unit_end - unit_begin;
   const bool at_range_start = pos == range_begin;
@@ -1249,7 +1292,7 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
   // a wave holds the 32 query rows of its kv-head: row n = head n / BMTD, token n % BMTD
   const int hh = n / BMTD;
   const int tt = n - hh * BMTD;
-  const bool q_valid = tt < N;
+  const bool q_valid = tt < n_unit;
   const int head = kvh * G + hh;
 
   bf16x8 qreg[8];
@@ -1265,7 +1308,7 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
     }
   }
 
-  const int total_keys = P + N;
+  const int total_keys = P + n_end;  // keys past the unit's last token are masked for all its rows
   const int fast_end = min(u_end, P / kSub);  // tiles below lie entirely inside the paged prefix
 
   const bool has_table = p.table != nullptr && p.table_stride > 0;
@@ -1312,7 +1355,7 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
       asm volatile("; end of the scalar-base loads");
     } else {
       const unsigned in_row = (unsigned)kvh * 256u + (unsigned)((lane & 15) ^ (((lane >> 4) & 3) << 2)) * 16u;
-      const char* const zeros = reinterpret_cast<const char*>(p.hdr + kZeroPageInt) + (lane & 15) * 16;
+      const char* const zeros = reinterpret_cast<const char*>(kZeroRow) + (lane & 15) * 16;
       const char* const fresh = reinterpret_cast<const char*>(which ? p.v_new : p.k_new);
 #pragma unroll
       for (int g = 0; g < 8; ++g) {
@@ -1324,7 +1367,7 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
         if (in_pool)
           src = pool + (uint64_t)bid * p.block_bytes + (uint64_t)(key & bs_mask) * row_bytes + in_row;
         else if (in_new)
-          src = fresh + (uint64_t)(cu_s + key - P) * row_bytes + in_row;
+          src = fresh + (uint64_t)(cu_s - t0 + key - P) * row_bytes + in_row;
         SYMPH_GLDS16(src, buf + g * kGroupBytes);
       }
     }
@@ -1352,7 +1395,7 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
   float mb = 0.f;           // the same, finite
   float l_run = 0.f;
   const float cs = p.scale_log2e;
-  const int q_limit = P + tt;
+  const int q_limit = P + t0 + tt;
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 
   auto exps = [&](const f32x16& sc, bf16x8 (&pb)[2]) {
@@ -1399,7 +1442,7 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
       sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag, qreg[g], sc, 0, 0, 0);
     }
     // causal mask: only tiles that reach past the first query's limit
-    if (u * kSub + kSub - 1 > P) {
+    if (u * kSub + kSub - 1 > P + t0) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int key = u * kSub + 16 * (e >> 3) + 8 * g2 + (e & 7);
@@ -1470,24 +1513,20 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
     if (q_valid)
       store_out_row(p.out + ((int64_t)(cu_s + tt) * p.n_q_heads + head) * kD, o_acc, 1.0f / l_row, g2);
   } else {
-    // Two slots per range: 2 * wg for a segment that starts where the range starts (a session continued from the
-    // range before), 2 * wg + 1 for one that starts inside it.  The pieces of a session are then its first one and,
-    // for every further range it reaches into, that range's even slot; the wave of kv-head 0 that has the first piece
-    // puts the session on the merge list.
+    // Two slots per range: 2 * wg for a segment that starts where the range starts (a unit continued from the range
+    // before), 2 * wg + 1 for one that starts inside it.  The pieces of a unit are then its first one and, for every
+    // further range it reaches into, that range's even slot; the range that has the first piece (at most one unit starts
+    // in a range and leaves it) names it in its record.
     const int pslot = 2 * wg + (at_range_start ? 0 : 1);
-    if (u_begin == 0 && kvh == 0 && lane == 0) {
-      const int last_wg = (unit_end - 1) / per_wg;
-      const int mi = atomicAdd(p.hdr + kHdrDecMerges, 1);  // at most one per range: the list has room for all
-      if (mi < p.dec_merges_bound) p.dec_merges[mi] = MergeItem{s, 0, pslot, last_wg - wg + 1};
-    }
+    if (u_begin == 0) rec = MergeItem{cu_s, n_unit, pslot, (unit_end - 1) / per_wg - wg + 1};
     // The piece goes through the wave's LDS buffers into the packed layout, so that every store instruction writes
     // whole lines (the wave's own reads of the buffers are done: it has used the last tile).
-    const int rows = G * N;
+    const int rows = G * n_unit;
     const int n_floats = rows * 130;
     const int n_padded = (n_floats + 31) & ~31;
     float* const stage = reinterpret_cast<float*>(my_lds);
     if (q_valid) {
-      const int r = hh * N + tt;
+      const int r = hh * n_unit + tt;
       float* so = stage + r * 128 + 4 * g2;
 #pragma unroll
       for (int dt = 0; dt < 4; ++dt)
@@ -1507,63 +1546,121 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
     for (int idx = lane; idx < n_padded; idx += 64) part[idx] = stage[idx];
     __builtin_amdgcn_wave_barrier();
   }
+  unit_begin = unit_end;
+  t0 += m;
+  if (t0 >= N && pos < range_end) {  // the next session with new tokens (there is one: tiles are left)
+    t0 = 0;
+    do {
+      ++s;
+      span_of(s, cu, N, P);
+    } while (N == 0);
   }
+  }
+  if (kvh == 0 && (tid & 63) == 0) p.dec_merges[wg] = rec;
 }
 
-// Combine the pieces of a short turn that the decode kernel cut at the boundaries of its workgroups' shares:
+// Combine the pieces of a unit that the decode kernel cut at the boundaries of its ranges:
 // out = sum_c w_c O_c / sum_c w_c l_c with w_c = 2^(m_c - max_c m_c), m_c being the piece's softmax reference in log2
 // units (-inf: the piece saw no key of the row).  The first piece is in slot pslot0, piece c >= 1 in the even slot of
-// the c-th workgroup after the one that wrote pslot0; pieces are added in that order.
-// One workgroup per (session, kv-head); a thread per (row, d) element of the packed pieces.
+// the c-th range after the one that wrote pslot0.
+// One workgroup per (range, kv-head), eight rows at a time.  Wave w takes pieces w, w + 4, ..: a step that decodes a few
+// long sessions cuts them into tens of pieces each, and a thread that reads them one after the other waits for memory
+// every time (one session of 1777 tokens in 56 pieces: 50 us; this way 8 us, and 5 us for its 28 pieces of two tiles).
+constexpr int kMergeRows = 8;
 template <int G>
 __global__ __launch_bounds__(256) void attn_decode_merge_kernel(const MfmaParams p) {
+  __shared__ float part_o[4][kMergeRows * 128];
+  __shared__ float part_m[4][kMergeRows], part_l[4][kMergeRows];
   const int Hkv = p.n_kv_heads;
-  const int mi = blockIdx.x / Hkv;
-  if (mi >= min(p.hdr[kHdrDecMerges], p.dec_merges_bound)) return;
-  const int kvh = blockIdx.x - mi * Hkv;
-  const MergeItem m = p.dec_merges[mi];
-  const int cu_s = p.cu_new_lens[m.s];
-  const int N = p.cu_new_lens[m.s + 1] - cu_s;
-  const int rows = G * N;
-  const int first_wg = m.pslot0 >> 1;
+  const int range = blockIdx.x / Hkv;
+  const MergeItem mg = p.dec_merges[range];
+  if (mg.n_chunks == 0) return;
+  const int kvh = blockIdx.x - range * Hkv;
+  const int n_unit = mg.n_unit;
+  const int rows = G * n_unit;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   auto piece = [&](int c) {
-    const int slot = c == 0 ? m.pslot0 : 2 * (first_wg + c);
+    const int slot = c == 0 ? mg.pslot0 : 2 * (range + c);
     return p.dec_partials + ((int64_t)slot * Hkv + kvh) * p.dec_slot_floats;
   };
-  for (int idx = threadIdx.x; idx < rows * 128; idx += 256) {
-    const int r = idx >> 7, d = idx & 127;
-    float M = -INFINITY, L = 0.f, o = 0.f;
-    if (m.n_chunks <= 8) {
-      // the usual case: everything is asked for at once (one trip to memory, not one for the references and another
-      // for the rest), and added in piece order
-      float mc[8], lc[8], oc[8];
+  for (int r0 = 0; r0 < rows; r0 += kMergeRows) {
+    // lane l holds elements 4 * (l % 32) .. + 3 of rows r0 + 2 * i + l / 32
+    f32x4 o[4];
+    float m_run[4], l_run[4];
+    int row[4];
 #pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const float* part = piece(c < m.n_chunks ? c : 0);
-        mc[c] = c < m.n_chunks ? part[rows * 128 + r] : -INFINITY;
-        lc[c] = part[rows * 129 + r];
-        oc[c] = part[idx];
+    for (int i = 0; i < 4; ++i) {
+      o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      m_run[i] = -INFINITY;
+      l_run[i] = 0.f;
+      row[i] = r0 + 2 * i + (lane >> 5);
+    }
+    for (int c0 = wave; c0 < mg.n_chunks; c0 += 16) {  // pieces c0, c0 + 4, c0 + 8, c0 + 12: all asked for at once
+      f32x4 oc[4][4];
+      float mc[4][4], lc[4][4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const bool there = c0 + 4 * k < mg.n_chunks;
+        const float* src = piece(there ? c0 + 4 * k : c0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          mc[k][i] = -INFINITY;
+          if (there && row[i] < rows) {
+            oc[k][i] = *reinterpret_cast<const f32x4*>(src + row[i] * 128 + 4 * (lane & 31));
+            mc[k][i] = src[rows * 128 + row[i]];
+            lc[k][i] = src[rows * 129 + row[i]];
+          }
+        }
       }
 #pragma unroll
-      for (int c = 0; c < 8; ++c) M = fmaxf(M, mc[c]);
+      for (int k = 0; k < 4; ++k)
 #pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const float w = (mc[c] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mc[c] - M);  // references are in log2 units
-        L += w * lc[c];
-        o = fmaf(w, oc[c], o);
-      }
-    } else {
-      for (int c = 0; c < m.n_chunks; ++c) M = fmaxf(M, piece(c)[rows * 128 + r]);
-      for (int c = 0; c < m.n_chunks; ++c) {
-        const float* part = piece(c);
-        const float mc = part[rows * 128 + r];
-        const float w = (mc == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mc - M);
-        L += w * part[rows * 129 + r];
-        o = fmaf(w, part[idx], o);
+        for (int i = 0; i < 4; ++i) {
+          if (mc[k][i] == -INFINITY) continue;  // absent, or it saw no key of the row
+          const float m_new = fmaxf(m_run[i], mc[k][i]);
+          const float a = __builtin_amdgcn_exp2f(m_run[i] - m_new);  // (0 for the first piece)
+          const float w = __builtin_amdgcn_exp2f(mc[k][i] - m_new);
+          m_run[i] = m_new;
+          l_run[i] = fmaf(w, lc[k][i], l_run[i] * a);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[i][e] = fmaf(w, oc[k][i][e], o[i][e] * a);
+        }
+    }
+    if (r0 > 0) __syncthreads();  // the rows before have been read
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int rr = 2 * i + (lane >> 5);
+      *reinterpret_cast<f32x4*>(&part_o[wave][rr * 128 + 4 * (lane & 31)]) = o[i];
+      if ((lane & 31) == 0) {
+        part_m[wave][rr] = m_run[i];
+        part_l[wave][rr] = l_run[i];
       }
     }
-    const int hh = r / N, tt = r - hh * N;
-    p.out[((int64_t)(cu_s + tt) * p.n_q_heads + (kvh * G + hh)) * kD + d] = (__bf16)(o * (1.0f / L));
+    __syncthreads();
+    // the four waves' sums, in wave order: thread t has elements 4 * (t % 32) .. of row t / 32
+    const int rr = threadIdx.x >> 5, r = r0 + rr;
+    if (r < rows) {
+      float M = -INFINITY, L = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) M = fmaxf(M, part_m[w][rr]);
+      f32x4 sum{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const float mw = part_m[w][rr];
+        const float f = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - M);
+        L = fmaf(f, part_l[w][rr], L);
+        const f32x4 ow = *reinterpret_cast<const f32x4*>(&part_o[w][rr * 128 + 4 * (threadIdx.x & 31)]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[e] = fmaf(f, ow[e], sum[e]);
+      }
+      const float inv = 1.0f / L;
+      const int hh = r / n_unit, tt = r - hh * n_unit;
+      bf16x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = (__bf16)(sum[e] * inv);
+      *reinterpret_cast<bf16x4*>(p.out + ((int64_t)(mg.row0 + tt) * p.n_q_heads + (kvh * G + hh)) * kD +
+                                 4 * (threadIdx.x & 31)) = v;
+    }
   }
 }
 
@@ -1588,24 +1685,19 @@ static AttnTuning resolve_tuning(const symph_attn_tuning* t) {
 
 struct MfmaPlan {
   int32_t bmt, target, target_slots, c_min, coarse, units_bound, items_bound, merges_bound, pslots_bound;
-  // decode kernel: whether this call runs it, its key ranges (two slots each per kv-head), room in its
-  // list of sessions cut between shares
-  int32_t dec_mode, dec_wgs, dec_merges_bound, dec_slot_floats;
-  int64_t off_items, off_dec_s, off_dec_off, off_dec_merges, off_merge_cnt, off_partials, off_dec_partials, total_bytes;
+  // decode kernel: whether this call runs it (alone), its key ranges (a record and, per kv-head, two slots each)
+  int32_t dec_mode, dec_wgs, dec_slot_floats;
+  int64_t off_items, off_dec_merges, off_merge_cnt, off_partials, off_dec_partials, total_bytes;
 };
 
 static inline int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
-static void lay_out(MfmaPlan& pl, int32_t n_sessions, int32_t n_kv_heads) {
+static void lay_out(MfmaPlan& pl, int32_t n_kv_heads) {
   pl.items_bound = pl.units_bound + pl.pslots_bound;  // every unit once, plus one more item per chunk of a split unit
   pl.merges_bound = pl.pslots_bound / 2;              // a split unit has at least two chunks
-  pl.dec_merges_bound = pl.dec_wgs;                   // at most one session starts inside a share and leaves it
-  const int32_t ns = n_sessions < kSchedMaxSessions ? n_sessions : kSchedMaxSessions;  // per scheduler slice
   pl.off_items = align256(kHdrInts * 4);
-  pl.off_dec_s = align256(pl.off_items + (int64_t)pl.items_bound * sizeof(WorkItem));
-  pl.off_dec_off = align256(pl.off_dec_s + (int64_t)ns * 4);
-  pl.off_dec_merges = align256(pl.off_dec_off + (int64_t)(ns + 1) * 4);
-  pl.off_merge_cnt = align256(pl.off_dec_merges + (int64_t)pl.dec_merges_bound * sizeof(MergeItem));
+  pl.off_dec_merges = align256(pl.off_items + (int64_t)pl.items_bound * sizeof(WorkItem));
+  pl.off_merge_cnt = align256(pl.off_dec_merges + (int64_t)pl.dec_wgs * sizeof(MergeItem));
   pl.off_partials = align256(pl.off_merge_cnt + (int64_t)pl.merges_bound * n_kv_heads * 4);
   pl.off_dec_partials = pl.off_partials + (int64_t)pl.pslots_bound * n_kv_heads * kPartialFloats * 4;
   pl.total_bytes = pl.off_dec_partials + (int64_t)2 * pl.dec_wgs * n_kv_heads * pl.dec_slot_floats * 4;
@@ -1626,29 +1718,33 @@ static bool make_plan(MfmaPlan& pl, int32_t n_sessions, int32_t n_q_heads, int32
   // A batch in which no session has more new rows than one wave holds (decode steps) takes the decode kernel: one
   // equal share of the keys per workgroup, two partial-result slots per workgroup.  Mixed batches do not: their short
   // turns are memory-bound pieces that share the CUs with the compute-bound ones inside the main kernel, which
-  // measured faster than two kernels one after the other.
-  pl.dec_mode = tu.decode && max_new_len >= 1 && max_new_len * G <= 32;
-  // The decode kernel takes the sessions with at most max_new_len new tokens (longer ones, if the bound was understated,
-  // are work items), so a piece has at most G * max_new_len rows of 130 values: slots of that size, in whole lines.
+  // measured faster than two kernels one after the other.  A session longer than max_new_len is taken max_new_len tokens
+  // at a time and its prefix is streamed once for each of them; more tokens than n_sessions * max_new_len show that the
+  // bound is wrong by more than a few such passes, and the batch is then no decode step.
+  pl.dec_mode = tu.decode && max_new_len >= 1 && max_new_len <= 32 / G &&
+                total_new_tokens <= (int64_t)n_sessions * max_new_len;
+  // A piece has at most G * max_new_len rows of 130 values: slots of that size, in whole lines.
   pl.dec_slot_floats = pl.dec_mode ? ((G * max_new_len * 130 + 31) & ~31) : 0;
   // ranges of the decode kernel: one wave per (range, kv-head), as many waves as decode_wgs workgroups of four would have
   pl.dec_wgs = pl.dec_mode ? (4 * tu.decode_wgs / n_kv_heads < 1 ? 1 : 4 * tu.decode_wgs / n_kv_heads) : 0;
   // Chunks of split units: a unit is split when it has more than C tiles, C >= total tiles * kv-heads / target, so
   // there are at most target / kv-heads split units and their chunks number at most twice that.
   pl.pslots_bound = 2 * (pl.target / n_kv_heads + 1);
-  lay_out(pl, n_sessions, n_kv_heads);
+  if (pl.dec_mode) pl.units_bound = pl.pslots_bound = 0;  // no work list
+  lay_out(pl, n_kv_heads);
   if (budget_bytes <= 0 || pl.total_bytes <= budget_bytes) return true;
-  // First the work list gives up its partial-result slots (in a decode step it only serves sessions longer than the
-  // stated bound), then the decode kernel's ranges are halved until its pieces fit, and the work list gets back as
-  // many slots as the room that is left holds.
+  if (pl.dec_mode) {  // the ranges are halved until their pieces fit
+    while (pl.dec_wgs > 1 && pl.total_bytes > budget_bytes) {
+      pl.dec_wgs /= 2;
+      lay_out(pl, n_kv_heads);
+    }
+    return pl.total_bytes <= budget_bytes;
+  }
+  // the work list gets as many partial-result slots as the room beside the uncut list holds
   const int64_t slot_bytes = (int64_t)n_kv_heads * kPartialFloats * 4;
   const int32_t wanted = pl.pslots_bound;
   pl.pslots_bound = 0;
-  lay_out(pl, n_sessions, n_kv_heads);
-  while (pl.dec_wgs > 1 && pl.total_bytes > budget_bytes) {
-    pl.dec_wgs /= 2;
-    lay_out(pl, n_sessions, n_kv_heads);
-  }
+  lay_out(pl, n_kv_heads);
   const int64_t per_slot = slot_bytes + (int64_t)sizeof(WorkItem) + 4 * n_kv_heads;
   const int64_t room = budget_bytes - pl.total_bytes - 4 * 256;  // (the arrays are aligned to 256 bytes)
   if (room < 0) return false;
@@ -1657,7 +1753,7 @@ static bool make_plan(MfmaPlan& pl, int32_t n_sessions, int32_t n_q_heads, int32
   const int64_t pieces = (int64_t)(pl.pslots_bound / 2) * n_kv_heads;  // (the bound above, solved for the target)
   if (pieces < pl.target) pl.target = pieces < n_kv_heads ? n_kv_heads : (int32_t)pieces;
   if (pl.target_slots > pl.target) pl.target_slots = pl.target;
-  lay_out(pl, n_sessions, n_kv_heads);
+  lay_out(pl, n_kv_heads);
   return pl.total_bytes <= budget_bytes;
 }
 
@@ -1731,9 +1827,6 @@ static int32_t launch_mfma(const AttnArgs& a, hipStream_t stream) {
   sp.merges_bound = pl.merges_bound;
   sp.pslots_bound = pl.pslots_bound;
   sp.hdr = (int32_t*)ws;
-  sp.bmt_dec = pl.dec_mode ? a.max_new_len : 0;   // (<= 32 / G in this mode)
-  sp.dec_s = (int32_t*)(ws + pl.off_dec_s);
-  sp.dec_off = (int32_t*)(ws + pl.off_dec_off);
   sp.items = (WorkItem*)(ws + pl.off_items);
   sp.merge_cnt = (int32_t*)(ws + pl.off_merge_cnt);
   sp.table = a.table;
@@ -1763,21 +1856,22 @@ static int32_t launch_mfma(const AttnArgs& a, hipStream_t stream) {
   p.hdr = sp.hdr;
   p.items = sp.items;
   p.merge_cnt = sp.merge_cnt;
-  p.dec_s = sp.dec_s;
-  p.dec_off = sp.dec_off;
+  p.dec_m = a.max_new_len;
+  p.total_new_tokens = a.total_new_tokens;
+  p.dec_ranges = pl.dec_wgs;
   p.dec_merges = (MergeItem*)(ws + pl.off_dec_merges);
   p.dec_partials = (float*)(ws + pl.off_dec_partials);
   p.dec_slot_floats = pl.dec_slot_floats;
-  p.dec_merges_bound = pl.dec_merges_bound;
   p.partials = (float*)(ws + pl.off_partials);
 
   const int64_t g_main = (int64_t)pl.items_bound * a.n_kv_heads;
   const int dec_hw = a.n_kv_heads % 8 == 0 ? 8 : 1;   // kv-heads (= waves) per workgroup of the decode kernel
   const int64_t g_dec = (int64_t)pl.dec_wgs * (a.n_kv_heads / dec_hw);
-  const int64_t g_merge = (int64_t)pl.dec_merges_bound * a.n_kv_heads;
+  const int64_t g_merge = (int64_t)pl.dec_wgs * a.n_kv_heads;
   if (g_main > 0x7FFFFFFFLL || g_merge > 0x7FFFFFFFLL) return SYMPH_EUNSUPPORTED;
-  // The scheduler keeps one table entry per session in LDS: larger batches run as consecutive slices of sessions
-  // (same stream, same workspace; the bounds of the whole batch cover every slice).
+  // The scheduler keeps one table entry per session in LDS (and the decode kernel adds the sessions up in every
+  // workgroup): larger batches run as consecutive slices of sessions (same stream, same workspace; the bounds of the
+  // whole batch cover every slice).
   for (int32_t s0 = 0; s0 < a.n_sessions; s0 += kSchedMaxSessions) {
     const int32_t ns = a.n_sessions - s0 < kSchedMaxSessions ? a.n_sessions - s0 : kSchedMaxSessions;
     sp.cu_new_lens = a.cu_new_lens + s0;
@@ -1788,13 +1882,6 @@ static int32_t launch_mfma(const AttnArgs& a, hipStream_t stream) {
     p.table = a.table ? a.table + (int64_t)s0 * a.table_stride : nullptr;
     sp.table = p.table;
     p.n_sessions = ns;
-    hipLaunchKernelGGL(attn_schedule_kernel, dim3(1), dim3(kSchedThreads), 0, stream, sp);
-    // The work-item kernel runs for decode steps too.  Its list is then empty if max_new_len was a true bound; a
-    // session with more new tokens than the caller stated is not a short turn for the scheduler and is computed here.
-    if (a.block_size == 16)
-      hipLaunchKernelGGL((attn_mfma_kernel<G, 4>), dim3((unsigned)g_main), dim3(256), 0, stream, p);
-    else
-      hipLaunchKernelGGL((attn_mfma_kernel<G, 0>), dim3((unsigned)g_main), dim3(256), 0, stream, p);
     if (pl.dec_mode) {
       if (dec_hw == 8) {
         if (a.block_size == 16)
@@ -1808,6 +1895,12 @@ static int32_t launch_mfma(const AttnArgs& a, hipStream_t stream) {
           hipLaunchKernelGGL((attn_decode_kernel<G, 0, 1>), dim3((unsigned)g_dec), dim3(64), 0, stream, p);
       }
       hipLaunchKernelGGL((attn_decode_merge_kernel<G>), dim3((unsigned)g_merge), dim3(256), 0, stream, p);
+    } else {
+      hipLaunchKernelGGL(attn_schedule_kernel, dim3(1), dim3(kSchedThreads), 0, stream, sp);
+      if (a.block_size == 16)
+        hipLaunchKernelGGL((attn_mfma_kernel<G, 4>), dim3((unsigned)g_main), dim3(256), 0, stream, p);
+      else
+        hipLaunchKernelGGL((attn_mfma_kernel<G, 0>), dim3((unsigned)g_main), dim3(256), 0, stream, p);
     }
   }
   return hipGetLastError() == hipSuccess ? SYMPH_OK : SYMPH_ELAUNCH;

@@ -139,8 +139,8 @@ def test_more_sessions_than_one_scheduler_slice(oracle_mod, decode):
 @pytest.mark.parametrize("stated", [1, 2, 8])
 def test_understated_max_new_len_on_a_decode_shaped_batch(oracle_mod, stated):
     """The caller says "no session has more than `stated` new tokens" (a decode step for the launcher), but some have up
-    to 40.  max_new_len only chooses kernels: the scheduler on the device sorts every session by its real length, the
-    long ones go through the work-item kernel that is launched beside the decode kernel, and every row is computed."""
+    to 40.  max_new_len only chooses kernels: more tokens in all than sessions x stated are no decode step, else the
+    decode kernel takes the long ones `stated` tokens at a time, and every row is computed."""
     cfg = _cfg(n_sessions=24, n_blocks=1024, prefix_dist=("uniform", 1, 700), new_dist=("uniform", 1, 3))
     sess = W.make_sessions(cfg, 59)
     new_lens = sess.new_lens.copy()
@@ -149,6 +149,29 @@ def test_understated_max_new_len_on_a_decode_shaped_batch(oracle_mod, stated):
     assert sess.max_new_len == 40 and stated * cfg.group <= 32
     check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 59), label=f"max_new_len stated as {stated}",
           max_new_len=stated)
+
+
+@pytest.mark.parametrize("hkv,group,prefix,new,stated", [
+    (8, 4, [1777], [1], 1),                              # one session in tens of pieces (more than one round of the merge)
+    (8, 4, [5003], [8], 8),                              # 32 rows per piece: four groups of rows in the merge
+    (3, 8, [4100, 0, 31], [1, 4, 3], 4),                 # single-wave workgroups; a session without a prefix
+    (8, 4, [700, 0, 64, 33, 900, 5], [0, 7, 1, 0, 2, 2], 2),   # understated within total <= sessions * stated: units
+    (8, 16, [300, 2, 1200], [0, 0, 3], 1),               # the only turn is three units of one token
+    (16, 2, [1, 63, 64, 65], [1, 16, 1, 2], 5),          # two groups of heads; a turn of four units
+])
+def test_decode_units_and_merges(oracle_mod, hkv, group, prefix, new, stated):
+    cfg = _cfg(n_sessions=len(new), n_kv_heads=hkv, n_q_heads=hkv * group, n_blocks=1024,
+               prefix_dist=("const", max(prefix)))
+    sess = W.make_sessions(cfg, 61, new_lens=np.array(new))
+    sess.prefix_lens[:] = prefix                         # (the tables cover the longest prefix)
+    sess.buf_token_offsets[1:] = np.cumsum(prefix)
+    assert stated * group <= 32 and sum(new) <= len(new) * stated
+    inputs = W.make_attn_inputs(cfg, sess, 61)
+    got, _ = check(oracle_mod, cfg, sess, inputs, label=f"decode units, stated {stated}", max_new_len=stated)
+    main = gpu_attention(cfg, sess, inputs, scale=cfg.scale, tuning=S.AttnTuning(decode=-1))
+    f = lambda x: W.bf16_bits_to_f32(x).astype(np.float64)
+    # two correct results of the same arithmetic: each within the bounds of `check` of the oracle
+    assert np.sqrt(np.sum((f(got) - f(main)) ** 2) / np.sum(f(main) ** 2)) <= 1e-2
 
 
 @pytest.mark.parametrize("seed", range(6))
