@@ -373,7 +373,7 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(const Sche
     }
   }
   __syncthreads();
-  if (tid == 0) {
+  if (tid < 64) {
     // With at least two workgroup-sized units per slot, longest-first dispatch balances well without splitting
     // anything but the longest units; with fewer, every unit is cut so that there are about two pieces per slot.
     const long long wg_units = (long long)U * p.n_kv_heads;
@@ -387,25 +387,32 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(const Sche
     // Units of (nearly) one length, and too few of them for the coarse rule: a single long session, or a batch of
     // equal ones.  Equal pieces are dispatched in whole rounds, so what counts is rounds x (piece + fixed cost), and
     // one round of longer pieces can beat two rounds of shorter ones.  Only cuts that are not finer than the one
-    // above are tried (the workspace bounds are derived from it).
+    // above are tried (the workspace bounds are derived from it): lane k - 1 tries k pieces.  (One lane that tried them
+    // all took 17 us for its 128 divisions.)
     const long long max_nt = max_nt_s, min_nt = 0x7FFFFFFF - inv_min_nt_s;
     if (target == p.target && max_nt > 0 && min_nt * 51 >= max_nt * 50 && c > 0) {
-      constexpr long long kFixedTiles = 6;  // a work item's fixed cost (~11 us) in key tiles (~1.9 us)
-      long long best_c = c, best_cost = 0x7FFFFFFFFFFFFFFFll;
-      for (long long k = 1; k <= 64; ++k) {
-        const long long ck = (max_nt + k - 1) / k;
-        if (ck < c) break;
-        const long long rounds = (wg_units * k + p.target_slots - 1) / p.target_slots;
-        const long long cost = rounds * (ck + kFixedTiles);
-        if (cost <= best_cost) {  // (of equal costs the finer cut: more pieces in flight)
-          best_cost = cost;
-          best_c = ck;
+      constexpr unsigned kFixedTiles = 6;  // a work item's fixed cost (~11 us) in key tiles (~1.9 us)
+      const unsigned k = tid + 1;
+      const unsigned ck = ((unsigned)max_nt + k - 1) / k;
+      // (units past 2^25 in number make every cost so large that their order no longer matters)
+      const unsigned pieces = (unsigned)(wg_units < (1 << 25) ? wg_units : (1 << 25)) * k;
+      const unsigned rounds = (pieces + p.target_slots - 1) / (unsigned)p.target_slots;
+      unsigned long long best = (long long)ck < c && k > 1 ? ~0ull : (unsigned long long)rounds * (ck + kFixedTiles);
+      unsigned best_k = k;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {  // smallest cost; of equal costs the finer cut: more pieces in flight
+        const unsigned long long other = __shfl_xor(best, o);
+        const unsigned other_k = __shfl_xor(best_k, o);
+        if (other < best || (other == best && other_k > best_k)) {
+          best = other;
+          best_k = other_k;
         }
       }
-      c = best_c;
+      const long long best_c = ((unsigned)max_nt + best_k - 1) / best_k;
+      if (best_c >= c) c = best_c;
     }
     if (c < p.c_min) c = p.c_min;
-    chunk_s = (int)c;
+    if (tid == 0) chunk_s = (int)c;
   }
   __syncthreads();
   const int C = chunk_s;
