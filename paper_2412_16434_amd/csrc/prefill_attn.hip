@@ -588,6 +588,7 @@ constexpr int kD = 128;  // head_dim
 // A row sum above this (one probability of 2^40 or more, or an overflow) makes the softmax reference stale.
 constexpr float kRefreshSum = 1.0995116e12f;  // 2^40
 
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
@@ -617,6 +618,27 @@ __device__ __forceinline__ void store_out_row(__bf16* op, const f32x16 (&acc)[4]
       *reinterpret_cast<bf16x4*>(op + 32 * dt + 4 * g2 + 8 * i) = v;
     }
 }
+
+// A slot of partial results, written and read at device scope (sc1: the access goes to the point where the XCDs' L2
+// caches agree), 8 or 16 bytes per lane.  Offsets in bytes from the slot's start.
+struct PartialSlot {
+  static constexpr int kDeviceScope = 16;  // the sc1 bit of the cache-policy operand
+  __amdgpu_buffer_rsrc_t rsrc;
+  __device__ __forceinline__ explicit PartialSlot(float* slot)
+      : rsrc(__builtin_amdgcn_make_buffer_rsrc(slot, 0, kPartialFloats * 4, 0x00027000)) {}
+  __device__ __forceinline__ void store4(int off, f32x4 v) const {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rsrc, off, 0, kDeviceScope);
+  }
+  __device__ __forceinline__ void store2(int off, f32x2 v) const {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rsrc, off, 0, kDeviceScope);
+  }
+  __device__ __forceinline__ f32x4 load4(int off) const {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, kDeviceScope));
+  }
+  __device__ __forceinline__ f32x2 load2(int off) const {
+    return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, off, 0, kDeviceScope));
+  }
+};
 
 // The 32 output rows of a wave through a buffer of its own in LDS: every store instruction then writes whole 128-byte
 // lines (the G heads of a token are neighbours in memory: a wave's rows, in (token, head) order, are 32 / G runs of
@@ -1106,19 +1128,23 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
       store_out_rows_staged(out_stage, out_first, (int64_t)p.n_q_heads * kD, G, row_m, valid_bits, o_acc, 1.0f / l_tot, g2,
                             lane);
   } else {
-    // Register dump, one float per thread per store: fully coalesced.  The chunks of a unit may run on different XCDs,
+    // Register dump, 16 bytes per lane per store: fully coalesced.  The chunks of a unit may run on different XCDs,
     // whose L2 caches do not see each other's lines, so everything that passes between them is written and read at
     // device scope (each access goes to the point where the XCDs agree) instead of flushing and invalidating whole
     // caches around the hand-over: a release / acquire fence pair at device scope per chunk cost a quarter of the
-    // kernel's time on a batch that is all split units.
-    float* part = p.partials + ((int64_t)it.pslot * Hkv + kvh) * kPartialFloats + tid;
+    // kernel's time on a batch that is all split units.  A wave without rows has nothing to hand over.
+    const int64_t chunk_floats = (int64_t)Hkv * kPartialFloats;
+    float* const unit_parts = p.partials + ((int64_t)it.pslot0 * Hkv + kvh) * kPartialFloats;
+    if (wave_works) {
+      const PartialSlot part(unit_parts + (it.pslot - it.pslot0) * chunk_floats);
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+      for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-      for (int e = 0; e < 16; ++e)
-        __hip_atomic_store(part + (dt * 16 + e) * 256, o_acc[dt][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(part + 64 * 256, m_run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(part + 65 * 256, l_run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int i = 0; i < 4; ++i)
+          part.store4(((dt * 4 + i) * 256 + tid) * 16,
+                      f32x4{o_acc[dt][4 * i], o_acc[dt][4 * i + 1], o_acc[dt][4 * i + 2], o_acc[dt][4 * i + 3]});
+      part.store2(64 * 256 * 4 + tid * 8, f32x2{m_run, l_run});
+    }
     // The chunk that arrives last combines all of them (no further kernel).  Every wave waits until its stores have
     // been performed, then one thread counts the chunk in.
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -1128,36 +1154,55 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
       merges_here = __hip_atomic_fetch_add(p.merge_cnt + (int64_t)it.merge * Hkv + kvh, 1, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT) == it.n_chunks - 1;
     __syncthreads();
-    if (!merges_here) return;
+    if (!merges_here || !wave_works) return;
     // out = sum_c w_c O_c / sum_c w_c l_c with w_c = 2^(m_c - max_c m_c), m_c being chunk c's softmax reference in log2
     // units (-inf: the chunk saw no key of the row).  All chunks are read back in chunk order, this one's too, so the
-    // result does not depend on which chunk came last.  Same thread -> (row, d) mapping as the dump above.
-    const float* first = p.partials + ((int64_t)it.pslot0 * Hkv + kvh) * kPartialFloats + tid;
-    const int64_t chunk_stride = (int64_t)Hkv * kPartialFloats;
-    float M = -INFINITY;
-    auto peer = [](const float* q) {  // a value another workgroup wrote during this launch
-      return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    for (int ch = 0; ch < it.n_chunks; ++ch) M = fmaxf(M, peer(first + ch * chunk_stride + 64 * 256));
+    // result does not depend on which chunk came last.  Same thread -> (row, d) mapping as the dump above.  kAtOnce chunks
+    // of one half of the accumulators are asked for at a time (more would not fit the registers beside the other half)
+    // and the weights follow a running maximum: 2 * n / kAtOnce waits for memory for n chunks, not n + 1.
+    constexpr int kAtOnce = 3;
+    float l_all = 0.f;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int half = 0; half < 2; ++half) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) o_acc[dt][e] = 0.f;
-    float L = 0.f;
-    for (int ch = 0; ch < it.n_chunks; ++ch) {
-      const float* src = first + ch * chunk_stride;
-      const float mc = peer(src + 64 * 256);
-      const float w = (mc == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mc - M);
-      L += w * peer(src + 65 * 256);
+      for (int e = 0; e < 32; ++e) o_acc[2 * half + (e >> 4)][e & 15] = 0.f;
+      float M = -INFINITY, L = 0.f;
+      for (int ch = 0; ch < it.n_chunks; ch += kAtOnce) {
+        f32x4 oc[kAtOnce][8];
+        f32x2 ml[kAtOnce];
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
+        for (int k = 0; k < kAtOnce; ++k) {  // (past the last chunk: it again, without weight)
+          const PartialSlot src(unit_parts + min(ch + k, it.n_chunks - 1) * chunk_floats);
+          ml[k] = src.load2(64 * 256 * 4 + tid * 8);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) o_acc[dt][e] = fmaf(w, peer(src + (dt * 16 + e) * 256), o_acc[dt][e]);
+          for (int i = 0; i < 8; ++i) oc[k][i] = src.load4(((8 * half + i) * 256 + tid) * 16);
+        }
+        float m_new = M;
+#pragma unroll
+        for (int k = 0; k < kAtOnce; ++k) {
+          if (ch + k >= it.n_chunks) ml[k][0] = -INFINITY;
+          m_new = fmaxf(m_new, ml[k][0]);
+        }
+        const float a = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - m_new);
+        M = m_new;
+        L *= a;
+#pragma unroll
+        for (int e = 0; e < 32; ++e) o_acc[2 * half + (e >> 4)][e & 15] *= a;
+#pragma unroll
+        for (int k = 0; k < kAtOnce; ++k) {
+          const float w = ml[k][0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml[k][0] - M);
+          L = fmaf(w, ml[k][1], L);
+#pragma unroll
+          for (int e = 0; e < 32; ++e)
+            o_acc[2 * half + (e >> 4)][e & 15] = fmaf(w, oc[k][e >> 2][e & 3], o_acc[2 * half + (e >> 4)][e & 15]);
+        }
+      }
+      l_all = L;
     }
+    const float L = l_all;
     const float l_tot = sum_across_halves(L);
-    if (wave_works)
-      store_out_rows_staged(out_stage, out_first, (int64_t)p.n_q_heads * kD, G, row_m, valid_bits, o_acc, 1.0f / l_tot, g2,
-                            lane);
+    store_out_rows_staged(out_stage, out_first, (int64_t)p.n_q_heads * kD, G, row_m, valid_bits, o_acc, 1.0f / l_tot, g2,
+                          lane);
   }
 }
 
