@@ -176,8 +176,9 @@ int32_t symph_kv_append(const symph_kv_cache* cache, int32_t layer, const void* 
  *   layer: which layer of `cache` holds the prefix.  q/k_new/v_new/out have the cache dtype.
  *   d_cu_new_lens [n_sessions+1] int32, d_prefix_lens [n_sessions] int32, d_block_table as above.
  *   total_new_tokens = T, max_new_len >= max N_s, max_prefix_len >= max P_s (host copies).  total_new_tokens and
- *   n_sessions size the grids and the work list; max_prefix_len is only checked against the table width; max_new_len
- *   only chooses kernels: a batch with max_new_len * (n_q_heads / n_kv_heads) <= 32 and total_new_tokens <= n_sessions *
+ *   n_sessions size the grids and the work list; max_prefix_len is checked against the table width; beside that the two
+ *   bounds only choose kernels: a batch of few query tiles takes a launch that needs no scheduling kernel, unless its turns
+ *   are longer than its prefixes; a batch with max_new_len * (n_q_heads / n_kv_heads) <= 32 and total_new_tokens <= n_sessions *
  *   max_new_len is a decode step and runs in a kernel that streams K,V with one wave per kv-head.  Neither of the two is
  *   relied on for memory safety: a session longer than stated is still computed, and computed correctly (a decode step
  *   takes it max_new_len tokens at a time and reads its prefix once for each), only not at the best speed.

@@ -144,7 +144,8 @@ __global__ __launch_bounds__(64) void attn_generic_kernel(const GenericParams p)
 // every kv-head by one workgroup: global index g -> (item g / H_kv, kv-head g % H_kv), which with 8 kv-heads also
 // pins each kv-head to one XCD (workgroups are dealt round-robin to the 8 XCDs), so the query tiles of a session
 // that re-read the same K,V share that XCD's L2.  Chunks of a split unit write unnormalised partial results
-// (running max, running sum, accumulators) to the workspace and a merge kernel combines them.
+// (running max, running sum, accumulators) to the workspace and the last of them to arrive combines them.  Batches of few
+// units are cut without that kernel (direct mode, below).
 struct WorkItem {   // 96 bytes
   int32_t s, t0, tile_begin, tile_end;
   int32_t pslot;                  // < 0: whole unit, the workgroup writes the output rows itself
@@ -154,17 +155,16 @@ struct WorkItem {   // 96 bytes
                                   // workgroup's first K,V loads wait for this item only, not for a table read as well
   int32_t pad[5];
 };
-struct MergeItem {  // 16 bytes, one per key range of the decode kernel: the unit that starts in it and leaves it
+struct MergeItem {  // 16 bytes: one per unit of a direct call; one per key range of the decode kernel, for the unit that
+                    // starts in it and leaves it
   int32_t row0, n_unit, pslot0, n_chunks;  // its first row of q / out and its tokens; slot (2 * range + 0 / 1) of its
                                            // first piece; n_chunks 0: no such unit
 };
-// Header of the workspace (ints): counts and flags written by the scheduler (by the decode kernel in a decode step), and a
-// 256-byte page of zeros (source of absent key rows).
-constexpr int kHdrInts = 128;
+// Header of the workspace (ints): counts and flags written by the scheduler (by the attention kernel itself where none
+// runs).
 constexpr int kHdrItems = 0, kHdrChunk = 1, kHdrSplitUnits = 2, kHdrPslots = 3, kHdrDecTiles = 5,
               kHdrFlags = kAttnHdrFlags;
-static_assert(kHdrFlags < kAttnHdrInts && kAttnHdrInts <= 64, "the counts and flags lie in front of the zero page");
-constexpr int kZeroPageInt = 64;
+static_assert(kHdrFlags < kAttnHdrInts, "the header holds the counts and flags");
 constexpr int kPartialFloats = 256 * 66;  // per workgroup: 64 accumulators + running max + running sum per thread
 // A piece of a short turn (decode kernel): only the session's own rows, r = head * N + token (at most 32), packed:
 // rows x 128 accumulators, then the rows' softmax references, then their sums.  Whole 128-byte lines are written and
@@ -259,7 +259,6 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(const Sche
   __shared__ int n_items_s, n_split_s, n_pslot_s, chunk_s, flags_s;
   const int tid = threadIdx.x;
   const int S = p.n_sessions;
-  if (tid >= kZeroPageInt && tid < kHdrInts) p.hdr[tid] = 0;
   for (int i = tid; i < p.merges_bound * p.n_kv_heads; i += kSchedThreads) p.merge_cnt[i] = 0;
   if (tid == 0) {
     total_tiles_s = 0ull;
@@ -575,6 +574,9 @@ struct MfmaParams {
   const WorkItem* items;
   int32_t* merge_cnt;   // [split unit][kv-head]: chunks that have written their partial result
   float* partials;
+  // direct mode of attn_mfma_kernel: shortest piece (tiles), workgroups the pieces are cut for, one record per unit
+  int32_t direct_c_min, direct_slots, units_bound;
+  MergeItem* unit_recs;
   // attn_decode_kernel: new tokens per unit (the call's max_new_len), the rows of q / out, its ranges, one record per
   // range, and the pieces of units that several ranges share
   int32_t dec_m, total_new_tokens, dec_ranges;
@@ -585,6 +587,8 @@ struct MfmaParams {
 
 
 constexpr int kD = 128;  // head_dim
+// Source of absent key rows (one head's 256 bytes)
+static __device__ __attribute__((aligned(256))) const unsigned kZeroRow[64] = {};
 // A row sum above this (one probability of 2^40 or more, or an overflow) makes the softmax reference stale.
 constexpr float kRefreshSum = 1.0995116e12f;  // 2^40
 
@@ -712,6 +716,107 @@ constexpr int kTileBytes = 16 * kGroupBytes;  // 16640
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),             \
                                    (__attribute__((address_space(3))) void*)(dst), 16, 0, 2)
 
+// ---- direct mode: a batch of at most 64 units, where a scheduling kernel in front and a last piece that combines all
+// others behind would take longer than the attention.  Every wave reads the sessions' lengths (lane s those of session s),
+// lists the units (lane u has unit u, in session order), chooses the cut (64 lanes price 64 cuts of the longest unit, from
+// whole to 63 pieces) and picks its workgroup's piece: no LDS, no barrier, one trip to memory for the lengths and one for
+// the first block ids.
+// What a cut into W workgroups of at most C tiles costs, in microseconds, fitted to 280 timings of 27 batches (1 to 48
+// sessions of 500 to 32 768 tokens, 8 to 1000 new ones, 2 to 8 kv-heads; the cut it chooses is on average 0.5 % slower
+// than the best one tried): a tile takes 1.1 while every workgroup has its CU to itself and up to 1.65 when two share it,
+// a further round of workgroups 14 beside its tiles and a piece that has to be combined 0.018 (its 66 KB written and
+// read back).  Against the scheduling kernel and the combining last piece: 45 new tokens over 3001, 30.0 -> 20.2 us (47
+// before either was reworked); 17 over 16 000, 53 -> 28; 8 x 64 .. 128 over 1500 .. 3000, 69 -> 55; 512 over 32 768 in
+// groups of eight heads, 496 -> 490.
+constexpr int kDirectUnits = 64;
+constexpr float kTileAlone = 1.1f, kTilePaired = 1.65f, kRoundFixed = 14.f, kPieceMerge = 0.018f;
+
+__device__ __forceinline__ bool direct_item(const MfmaParams& p, int bmt, int piece, WorkItem& it) {
+  const int lane = threadIdx.x & 63;
+  int cu = 0, N = 0, P = 0;
+  if (lane < p.n_sessions) {
+    cu = p.cu_new_lens[lane];  // (rows past total_new_tokens do not exist; such lengths are flagged below)
+    N = max(min(p.cu_new_lens[lane + 1], p.total_new_tokens) - cu, 0);
+    P = max(p.prefix_lens[lane], 0);
+  }
+  const int nq = (N + bmt - 1) / bmt;
+  const int q_end = wave_inclusive_scan(nq);
+  const int n_units = min(__builtin_amdgcn_readlane(q_end, 63), kDirectUnits);
+  // lane u: the session of unit u is the first one whose units end past u
+  int lo = 0;
+#pragma unroll
+  for (int step = 32; step > 0; step >>= 1)
+    if (__shfl(q_end, lo + step - 1) <= lane) lo += step;
+  const int s = min(lo, 63);
+  const int t0 = (lane - (__shfl(q_end, s) - __shfl(nq, s))) * bmt;
+  const int uN = __shfl(N, s), uP = __shfl(P, s), ucu = __shfl(cu, s);
+  const int nt = lane < n_units ? unit_tiles(uP, uN, t0, bmt) : 0;
+  const int total = __builtin_amdgcn_readlane(wave_inclusive_scan(nt), 63);
+  const int max_nt = __builtin_amdgcn_readlane(wave_inclusive_max(nt), 63);
+  // (no cut finer than c_lo: the slots for partial results are sized by it)
+  const int c_lo = max((int)(((int64_t)total * p.n_kv_heads + p.direct_slots - 1) / p.direct_slots), p.direct_c_min);
+  // lanes 0 .. 31: 1, 1.25, .. 8.75 pieces of the longest unit; lanes 32 .. 63: 9, 10.75, .. 63.25
+  const float cuts = lane < 32 ? 1.f + 0.25f * (float)lane : 9.f + 1.75f * (float)(lane - 32);
+  int C = max((int)ceilf((float)max_nt / cuts), c_lo);
+  {
+    const float inv_c = 1.0f / (float)C;
+    const float below = (float)(nt - 1);
+    float pieces = 0.f, split = 0.f;
+#pragma unroll 4
+    for (int u = 0; u < n_units; ++u) {
+      const float n = floorf(__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, below), u)) * inv_c);
+      pieces += n;
+      split += n > 0.f ? n + 1.f : 0.f;
+    }
+    const float heads = (float)p.n_kv_heads, slots = (float)p.direct_slots;
+    const float w = (pieces + (float)n_units) * heads;
+    const float shared = fminf(fmaxf(2.f * w / slots - 1.f, 0.f), 1.f);
+    const float tile = kTileAlone + (kTilePaired - kTileAlone) * __builtin_amdgcn_sqrtf(shared);
+    float cost = ceilf(w / slots) * fmaf((float)C, tile, kRoundFixed) + split * heads * kPieceMerge;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const float other = __shfl_xor(cost, o);
+      const int other_c = __shfl_xor(C, o);
+      if (other < cost || (other == cost && other_c < C)) {
+        cost = other;
+        C = other_c;
+      }
+    }
+    C = __builtin_amdgcn_readfirstlane(C);
+  }
+  const int nc = (nt + C - 1) / C;
+  const int end = wave_inclusive_scan(nc);
+  const int n_pieces = __builtin_amdgcn_readlane(end, 63);
+  if (blockIdx.x == 0 && threadIdx.x < 64) {
+    const bool dropped = p.cu_new_lens[p.n_sessions] > p.total_new_tokens;
+    if (lane < kAttnHdrInts)
+      p.hdr[lane] = lane == kHdrItems ? n_pieces : (lane == kHdrChunk ? C : (lane == kHdrFlags && dropped ? 2 : 0));
+    if (lane < p.units_bound)
+      p.unit_recs[lane] = MergeItem{ucu + t0, min(bmt, uN - t0), end - nc, lane < n_units && nc > 1 ? nc : 0};
+  }
+  if (piece >= n_pieces) return false;
+  const int u = __builtin_ctzll(__ballot(piece < end));
+  auto of_unit = [&](int x) { return __builtin_amdgcn_readlane(x, u); };
+  const int n = of_unit(nc), tiles = of_unit(nt), ch = piece - (of_unit(end) - n);
+  it.s = of_unit(s);
+  it.t0 = of_unit(t0);
+  it.tile_begin = (int)((int64_t)ch * tiles / n);  // near-equal pieces
+  it.tile_end = (int)((int64_t)(ch + 1) * tiles / n);
+  it.pslot = n > 1 ? piece : -1;
+  it.n_chunks = n;
+  it.cu_s = of_unit(ucu);
+  it.n_new = of_unit(uN);
+  it.n_prefix = of_unit(uP);
+  // block ids of the first two tiles: lane i < 8 reads that of group i
+  int raw = -1;
+  if (p.table && p.table_stride > 0)
+    raw = p.table[(int64_t)it.s * p.table_stride +
+                  min((it.tile_begin * kBN + 16 * (lane & 7)) >> p.log_bs, p.table_stride - 1)];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) it.first_ids[i] = __builtin_amdgcn_readlane(raw, i);
+  return true;
+}
+
 // One workgroup = one work item x one kv-head: 128 query rows (G heads x 128/G tokens) against the item's key tiles.
 // Requires block_size >= 16 (a power of two): the 16 consecutive key rows of a staging group then lie in ONE block, so
 // block ids are workgroup-uniform and a row address is scalar base + per-lane constant.
@@ -724,7 +829,9 @@ constexpr int kTileBytes = 16 * kGroupBytes;  // 16640
 //   then  : O += V(j)^T P(j);   end: wait for the loads, one barrier.
 // The first product of the NEXT tile is independent of the softmax of the current one, so one wave keeps the matrix
 // pipe and the vector ALU busy at the same time instead of alternating between them.
-template <int G, int LB>
+// DIRECT: without a scheduling kernel.  Workgroup g works out piece g / H_kv by itself (direct_item) and the pieces of split
+// units are combined by attn_merge_kernel.
+template <int G, int LB, bool DIRECT>
 __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
   constexpr int BMT = 128 / G;  // query tokens per tile
   __shared__ __attribute__((aligned(16))) char K0[kTileBytes];
@@ -735,13 +842,18 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
   const int Hkv = p.n_kv_heads;
   const int item_idx = blockIdx.x / Hkv;
   __shared__ int merges_here;  // set for the chunk of a split unit that arrives last
-  // The array covers the whole grid, so the item is read beside the count, not after it: one trip to memory less in
-  // front of the first K,V loads.  (The empty statement makes the compiler issue both loads before the branch.)
-  const WorkItem it = p.items[item_idx];
-  const int n_items = p.hdr[kHdrItems];
-  asm volatile("" ::"s"(it.s), "s"(it.pslot), "s"(it.n_chunks), "s"(it.first_ids[0]), "s"(it.first_ids[7]), "s"(n_items));
-  if (item_idx >= n_items) return;
   const int kvh = blockIdx.x - item_idx * Hkv;
+  WorkItem it;
+  if constexpr (DIRECT) {
+    if (!direct_item(p, BMT, item_idx, it)) return;
+  } else {
+    // The array covers the whole grid, so the item is read beside the count, not after it: one trip to memory less in
+    // front of the first K,V loads.  (The empty statement makes the compiler issue both loads before the branch.)
+    it = p.items[item_idx];
+    const int n_items = p.hdr[kHdrItems];
+    asm volatile("" ::"s"(it.s), "s"(it.pslot), "s"(it.n_chunks), "s"(it.first_ids[0]), "s"(it.first_ids[7]), "s"(n_items));
+    if (item_idx >= n_items) return;
+  }
   const int s = it.s;
   const int t0 = it.t0;
   const int cu_s = it.cu_s;
@@ -812,7 +924,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
     for (int i = 0; i < 4; ++i) ids[i] = __builtin_amdgcn_readlane(ids_raw, i);
   };
   // Issue the loads of one tile of K or of V into an LDS buffer.  Rows that do not exist (past the session's keys, or
-  // named by a block id outside the cache) are read from the page of zeros, so they are finite and add nothing.
+  // named by a block id outside the cache) are read from a row of zeros, so they are finite and add nothing.
   auto issue_tile = [&](const char* pool_bytes, const __bf16* new_rows, char* lds_buf, int tile) {
     // one comparison of the largest id (as unsigned: a negative id is huge)
     const unsigned id_max = max(max((unsigned)ids[0], (unsigned)ids[1]), max((unsigned)ids[2], (unsigned)ids[3]));
@@ -838,7 +950,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
       asm volatile("" : "+v"(l));
       const int row = 4 * wave + (l >> 4);
       const unsigned in_row = (unsigned)kvh * 256u + (unsigned)((l & 15) ^ (((l >> 4) & 3) << 2)) * 16u;
-      const char* const zeros = reinterpret_cast<const char*>(p.hdr + kZeroPageInt) + (l & 15) * 16;
+      const char* const zeros = reinterpret_cast<const char*>(kZeroRow) + (l & 15) * 16;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int key = tile * kBN + 16 * i + row;
@@ -1127,6 +1239,18 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
     if (wave_works)   // (every wave is past the last barrier of the loop: the tile buffers are free)
       store_out_rows_staged(out_stage, out_first, (int64_t)p.n_q_heads * kD, G, row_m, valid_bits, o_acc, 1.0f / l_tot, g2,
                             lane);
+  } else if constexpr (DIRECT) {
+    // The piece's accumulators, 16 bytes per lane per store, for the merge kernel.  A wave without rows has none.
+    float* const part = p.partials + ((int64_t)it.pslot * Hkv + kvh) * kPartialFloats;
+    if (wave_works) {
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          *reinterpret_cast<f32x4*>(part + ((dt * 4 + i) * 256 + tid) * 4) =
+              f32x4{o_acc[dt][4 * i], o_acc[dt][4 * i + 1], o_acc[dt][4 * i + 2], o_acc[dt][4 * i + 3]};
+      *reinterpret_cast<f32x2*>(part + 64 * 256 + tid * 2) = f32x2{m_run, l_run};
+    }
   } else {
     // Register dump, 16 bytes per lane per store: fully coalesced.  The chunks of a unit may run on different XCDs,
     // whose L2 caches do not see each other's lines, so everything that passes between them is written and read at
@@ -1206,6 +1330,68 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
   }
 }
 
+// Combines the pieces of split units in direct mode: four workgroups per (unit, kv-head), one for each quarter of the
+// head dimension; eight pieces are asked for at a time.
+template <int G>
+__global__ __launch_bounds__(256) void attn_merge_kernel(const MfmaParams p) {
+  constexpr int TW = 128 / G / 4;  // tokens per wave, as in attn_mfma_kernel
+  const int Hkv = p.n_kv_heads;
+  const int u = blockIdx.x / (4 * Hkv);
+  const MergeItem mg = p.unit_recs[u];
+  if (mg.n_chunks == 0) return;
+  const int dt = blockIdx.x & 3, kvh = (blockIdx.x >> 2) - u * Hkv;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 31, g2 = lane >> 5;
+  const int hh = n / TW, tt = wave * TW + (n - hh * TW);
+  if (wave * TW >= mg.n_unit) return;
+  f32x4 o[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float M = -INFINITY, L = 0.f;
+  constexpr int kAtOnce = 8;
+  for (int ch = 0; ch < mg.n_chunks; ch += kAtOnce) {
+    f32x4 oc[kAtOnce][4];
+    f32x2 ml[kAtOnce];
+#pragma unroll
+    for (int k = 0; k < kAtOnce; ++k) {
+      ml[k] = f32x2{-INFINITY, 0.f};
+      if (ch + k < mg.n_chunks) {
+        const float* part = p.partials + ((int64_t)(mg.pslot0 + ch + k) * Hkv + kvh) * kPartialFloats;
+        ml[k] = *reinterpret_cast<const f32x2*>(part + 64 * 256 + tid * 2);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) oc[k][i] = *reinterpret_cast<const f32x4*>(part + ((dt * 4 + i) * 256 + tid) * 4);
+      }
+    }
+    float m_new = M;
+#pragma unroll
+    for (int k = 0; k < kAtOnce; ++k) m_new = fmaxf(m_new, ml[k][0]);
+    const float a = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - m_new);
+    M = m_new;
+    L *= a;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] *= a;
+#pragma unroll
+    for (int k = 0; k < kAtOnce; ++k) {
+      if (ml[k][0] == -INFINITY) continue;  // absent, or it saw no key of the row
+      const float w = __builtin_amdgcn_exp2f(ml[k][0] - M);
+      L = fmaf(w, ml[k][1], L);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[i][e] = fmaf(w, oc[k][i][e], o[i][e]);
+    }
+  }
+  const float inv = 1.0f / sum_across_halves(L);
+  if (tt >= mg.n_unit) return;
+  __bf16* const op = p.out + ((int64_t)(mg.row0 + tt) * p.n_q_heads + kvh * G + hh) * kD + 32 * dt + 4 * g2;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    bf16x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (__bf16)(o[i][e] * inv);
+    *reinterpret_cast<bf16x4*>(op + 8 * i) = v;
+  }
+}
+
 // ------------------------------------------------------------------------------------------------------------
 // Short turns (decode-like rows): a session whose new rows fit one wave (n_new * G <= 32) reads its whole K,V for
 // 32 query rows or fewer, so the work is moving K,V, not arithmetic.  A unit is (session, max_new_len of its new tokens):
@@ -1228,8 +1414,6 @@ constexpr int kDecWaveBytes = 2 * kSubBytes;  // K and V of one tile, per wave
 // Shortest range, in tiles.  What a step with little to read takes is the launch, a few trips to memory and the merge of
 // its pieces: 1 / 2 / 4 tiles measured 16.6 / 15.4 / 16.7 us for one session of 1777 tokens.
 constexpr int kDecMinTiles = 2;
-// Source of absent key rows (one head's 256 bytes)
-static __device__ __attribute__((aligned(256))) const unsigned kZeroRow[64] = {};
 
 template <int G, int LB, int HW>
 __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(const MfmaParams p) {
@@ -1739,17 +1923,20 @@ struct MfmaPlan {
   int32_t bmt, target, target_slots, c_min, coarse, units_bound, items_bound, merges_bound, pslots_bound;
   // decode kernel: whether this call runs it (alone), its key ranges (a record and, per kv-head, two slots each)
   int32_t dec_mode, dec_wgs, dec_slot_floats;
+  int32_t direct;  // no scheduling kernel: pslots_bound pieces at most, one record per unit
   int64_t off_items, off_dec_merges, off_merge_cnt, off_partials, off_dec_partials, total_bytes;
 };
+
+constexpr int kDirectCMin = 2;  // shortest piece of a direct call, in tiles
 
 static inline int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
 static void lay_out(MfmaPlan& pl, int32_t n_kv_heads) {
   pl.items_bound = pl.units_bound + pl.pslots_bound;  // every unit once, plus one more item per chunk of a split unit
   pl.merges_bound = pl.pslots_bound / 2;              // a split unit has at least two chunks
-  pl.off_items = align256(kHdrInts * 4);
-  pl.off_dec_merges = align256(pl.off_items + (int64_t)pl.items_bound * sizeof(WorkItem));
-  pl.off_merge_cnt = align256(pl.off_dec_merges + (int64_t)pl.dec_wgs * sizeof(MergeItem));
+  pl.off_items = align256(kAttnHdrInts * 4);
+  pl.off_dec_merges = align256(pl.off_items + (pl.direct ? 0 : (int64_t)pl.items_bound * sizeof(WorkItem)));
+  pl.off_merge_cnt = align256(pl.off_dec_merges + (int64_t)(pl.direct ? pl.units_bound : pl.dec_wgs) * sizeof(MergeItem));
   pl.off_partials = align256(pl.off_merge_cnt + (int64_t)pl.merges_bound * n_kv_heads * 4);
   pl.off_dec_partials = pl.off_partials + (int64_t)pl.pslots_bound * n_kv_heads * kPartialFloats * 4;
   pl.total_bytes = pl.off_dec_partials + (int64_t)2 * pl.dec_wgs * n_kv_heads * pl.dec_slot_floats * 4;
@@ -1759,7 +1946,8 @@ static void lay_out(MfmaPlan& pl, int32_t n_kv_heads) {
 // agree.  budget_bytes > 0: the plan has to fit that many bytes; the decode kernel then gets fewer workgroups and the
 // work list is cut into fewer pieces (fewer partial-result slots).  Returns false if not even the uncut list fits.
 static bool make_plan(MfmaPlan& pl, int32_t n_sessions, int32_t n_q_heads, int32_t n_kv_heads,
-                      int32_t total_new_tokens, int32_t max_new_len, const AttnTuning& tu, int64_t budget_bytes) {
+                      int32_t total_new_tokens, int32_t max_new_len, int32_t max_prefix_len, const AttnTuning& tu,
+                      int64_t budget_bytes) {
   const int G = n_q_heads / n_kv_heads;
   pl.bmt = 128 / G;
   pl.target_slots = tu.slots < n_kv_heads ? n_kv_heads : tu.slots;  // workgroups resident at once
@@ -1783,6 +1971,20 @@ static bool make_plan(MfmaPlan& pl, int32_t n_sessions, int32_t n_q_heads, int32
   // there are at most target / kv-heads split units and their chunks number at most twice that.
   pl.pslots_bound = 2 * (pl.target / n_kv_heads + 1);
   if (pl.dec_mode) pl.units_bound = pl.pslots_bound = 0;  // no work list
+  // Direct calls: few units, and not one long turn over a shorter prefix that would fill the chip.  (There a unit's keys
+  // grow with its place in the turn, and the work list's longest-first order is worth more than the scheduling kernel:
+  // 2 x 2000 new tokens over 30, 4 kv-heads: 35 us by the list, 41 without; 2 x 900 over 500, 8 heads: 44 and 47.)
+  const int64_t wg_units = pl.units_bound * (int64_t)n_kv_heads;
+  pl.direct = !pl.dec_mode && tu.coarse && pl.units_bound <= kDirectUnits && wg_units <= tu.slots &&
+              (max_new_len <= max_prefix_len || 4 * wg_units <= tu.slots);
+  if (pl.direct) {
+    const int32_t listed = pl.pslots_bound;
+    pl.pslots_bound = pl.target_slots / n_kv_heads + 1 + pl.units_bound;
+    lay_out(pl, n_kv_heads);
+    if (budget_bytes <= 0 || pl.total_bytes <= budget_bytes) return true;
+    pl.direct = 0;
+    pl.pslots_bound = listed;
+  }
   lay_out(pl, n_kv_heads);
   if (budget_bytes <= 0 || pl.total_bytes <= budget_bytes) return true;
   if (pl.dec_mode) {  // the ranges are halved until their pieces fit
@@ -1817,12 +2019,13 @@ static bool mfma_path_ok(int32_t dtype, int32_t head_dim, int32_t n_q_heads, int
 }
 
 int64_t prefill_attn_workspace_bytes(const symph_kv_cache* c, int32_t n_sessions, int32_t n_q_heads,
-                                     int32_t total_new_tokens, int32_t max_new_len, int32_t,
+                                     int32_t total_new_tokens, int32_t max_new_len, int32_t max_prefix_len,
                                      const symph_attn_tuning* tuning) {
   if (n_q_heads % c->n_kv_heads != 0) return -1;
   if (!mfma_path_ok(c->dtype, c->head_dim, n_q_heads, c->n_kv_heads, c->block_size)) return 0;
   MfmaPlan pl;
-  make_plan(pl, n_sessions, n_q_heads, c->n_kv_heads, total_new_tokens, max_new_len, resolve_tuning(tuning), 0);
+  make_plan(pl, n_sessions, n_q_heads, c->n_kv_heads, total_new_tokens, max_new_len, max_prefix_len,
+            resolve_tuning(tuning), 0);
   return pl.total_bytes;
 }
 
@@ -1859,7 +2062,7 @@ static int32_t launch_mfma(const AttnArgs& a, hipStream_t stream) {
   const AttnTuning tu = resolve_tuning(a.tuning);
   char* ws = (char*)a.workspace;
   // fit_workspace: the caller's buffer has a fixed size and the plan is made to fit it (a coarser cut of the work list)
-  if (!make_plan(pl, a.n_sessions, a.n_q_heads, a.n_kv_heads, a.total_new_tokens, a.max_new_len, tu,
+  if (!make_plan(pl, a.n_sessions, a.n_q_heads, a.n_kv_heads, a.total_new_tokens, a.max_new_len, a.max_prefix_len, tu,
                  a.fit_workspace ? a.workspace_bytes : 0) ||
       !ws || a.workspace_bytes < pl.total_bytes)
     return SYMPH_EWORKSPACE;
@@ -1911,7 +2114,10 @@ static int32_t launch_mfma(const AttnArgs& a, hipStream_t stream) {
   p.dec_m = a.max_new_len;
   p.total_new_tokens = a.total_new_tokens;
   p.dec_ranges = pl.dec_wgs;
-  p.dec_merges = (MergeItem*)(ws + pl.off_dec_merges);
+  p.direct_c_min = a.tuning && a.tuning->c_min > 0 ? a.tuning->c_min : kDirectCMin;
+  p.direct_slots = pl.target_slots;
+  p.units_bound = pl.units_bound;
+  p.dec_merges = p.unit_recs = (MergeItem*)(ws + pl.off_dec_merges);
   p.dec_partials = (float*)(ws + pl.off_dec_partials);
   p.dec_slot_floats = pl.dec_slot_floats;
   p.partials = (float*)(ws + pl.off_partials);
@@ -1947,12 +2153,19 @@ static int32_t launch_mfma(const AttnArgs& a, hipStream_t stream) {
           hipLaunchKernelGGL((attn_decode_kernel<G, 0, 1>), dim3((unsigned)g_dec), dim3(64), 0, stream, p);
       }
       hipLaunchKernelGGL((attn_decode_merge_kernel<G>), dim3((unsigned)g_merge), dim3(256), 0, stream, p);
+    } else if (pl.direct) {
+      const unsigned g_pieces = (unsigned)(pl.pslots_bound * a.n_kv_heads);
+      if (a.block_size == 16)
+        hipLaunchKernelGGL((attn_mfma_kernel<G, 4, true>), dim3(g_pieces), dim3(256), 0, stream, p);
+      else
+        hipLaunchKernelGGL((attn_mfma_kernel<G, 0, true>), dim3(g_pieces), dim3(256), 0, stream, p);
+      hipLaunchKernelGGL((attn_merge_kernel<G>), dim3((unsigned)(4 * pl.units_bound * a.n_kv_heads)), dim3(256), 0, stream, p);
     } else {
       hipLaunchKernelGGL(attn_schedule_kernel, dim3(1), dim3(kSchedThreads), 0, stream, sp);
       if (a.block_size == 16)
-        hipLaunchKernelGGL((attn_mfma_kernel<G, 4>), dim3((unsigned)g_main), dim3(256), 0, stream, p);
+        hipLaunchKernelGGL((attn_mfma_kernel<G, 4, false>), dim3((unsigned)g_main), dim3(256), 0, stream, p);
       else
-        hipLaunchKernelGGL((attn_mfma_kernel<G, 0>), dim3((unsigned)g_main), dim3(256), 0, stream, p);
+        hipLaunchKernelGGL((attn_mfma_kernel<G, 0, false>), dim3((unsigned)g_main), dim3(256), 0, stream, p);
     }
   }
   return hipGetLastError() == hipSuccess ? SYMPH_OK : SYMPH_ELAUNCH;

@@ -174,6 +174,29 @@ def test_decode_units_and_merges(oracle_mod, hkv, group, prefix, new, stated):
     assert np.sqrt(np.sum((f(got) - f(main)) ** 2) / np.sum(f(main) ** 2)) <= 1e-2
 
 
+@pytest.mark.parametrize("hkv,group,bs,prefix,new", [
+    (8, 4, 16, [3001], [45]),                            # one turn in many pieces, its last tile half empty
+    (8, 4, 16, [0, 1, 63, 64, 4000], [33, 1, 32, 0, 70]),    # no prefix, no new tokens, whole and split units together
+    (2, 16, 64, [1500, 300], [9, 8]),                    # larger blocks, tiles of eight tokens
+    (3, 1, 32, [200], [1900]),                           # a long turn over a short prefix, few heads
+    (8, 4, 16, [100] * 61, [1] * 60 + [40]),             # 64 (unit, session) slots: the most a direct call has
+    (8, 4, 16, [100] * 62, [1] * 61 + [40]),             # one more: the work list
+])
+def test_direct_calls(oracle_mod, hkv, group, bs, prefix, new):
+    """Small prefill batches: each workgroup finds its own piece (no scheduling kernel), a merge kernel combines them.  The
+    same batch through the work list (switched by cutting every unit) is another correct result."""
+    cfg = _cfg(n_sessions=len(new), n_kv_heads=hkv, n_q_heads=hkv * group, block_size=bs, n_blocks=1280,
+               prefix_dist=("const", max(prefix)))
+    sess = W.make_sessions(cfg, 67, new_lens=np.array(new))
+    sess.prefix_lens[:] = prefix
+    sess.buf_token_offsets[1:] = np.cumsum(prefix)
+    inputs = W.make_attn_inputs(cfg, sess, 67)
+    got, _ = check(oracle_mod, cfg, sess, inputs, label="direct", max_new_len=max(new))
+    listed = gpu_attention(cfg, sess, inputs, scale=cfg.scale, tuning=S.AttnTuning(coarse=-1, decode=-1))
+    f = lambda x: W.bf16_bits_to_f32(x).astype(np.float64)
+    assert np.sqrt(np.sum((f(got) - f(listed)) ** 2) / np.sum(f(listed) ** 2)) <= 1e-2
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_seeded_random_batches(oracle_mod, seed):
     """Five drawn batches per seed: kv-heads, group size, block size, session count, length ranges, and whether the
