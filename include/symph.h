@@ -189,7 +189,7 @@ int32_t symph_kv_append(const symph_kv_cache* cache, int32_t layer, const void* 
  * Supported: head_dim 64 or 128; n_q_heads a multiple of n_kv_heads.  Sessions with N_s == 0 produce no rows;
  * P_s == 0 is a plain causal prefill.  The matrix-core kernels cover bf16, head_dim 128, group sizes 1, 2, 4, 8, 16 and
  * block sizes that are powers of two >= 16; every other supported shape (fp32, head_dim 64, other group sizes, smaller
- * blocks) runs a plain kernel with one wave per query row: correct, not tuned, and its workspace query returns 0.
+ * blocks) runs a kernel without a work list, which keeps probabilities in 32 bits; its workspace query returns 0.
  */
 int32_t symph_prefix_prefill_attn(const symph_kv_cache* cache, int32_t layer, const void* d_q, const void* d_k_new,
                                   const void* d_v_new, void* d_out, const int32_t* d_cu_new_lens,

@@ -56,6 +56,7 @@ struct AttnArgs {
   bool fit_workspace;               // the workspace has a fixed size: cut the work list so that it is enough
 };
 int32_t launch_prefill_attn(const AttnArgs& a, hipStream_t stream);
+int32_t launch_rows_attn(const AttnArgs& a, hipStream_t stream);  // the shapes without a work list
 int64_t prefill_attn_workspace_bytes(const symph_kv_cache* cache, int32_t n_sessions, int32_t n_q_heads,
                                      int32_t total_new_tokens, int32_t max_new_len, int32_t max_prefix_len,
                                      const symph_attn_tuning* tuning);

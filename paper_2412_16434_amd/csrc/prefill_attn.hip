@@ -14,124 +14,12 @@
 //     contiguous new-turn K,V straight into LDS (global_load_lds_dwordx4), double-buffered, one tile ahead;
 //   * the softmax reference is stale on purpose (refreshed only when a row sum shows that it has to be), so no
 //     per-tile maximum and no per-tile rescaling of the accumulators.
-// generic path (fp32, or head_dim 64): one wave per query row, lanes over keys, fp32 online softmax.
-#include "common.h"
+// Every other shape (fp32, head_dim 64, other group sizes, smaller blocks): rows_attn.hip.
+#include "attn_lanes.h"
 
 #include <type_traits>
 
 namespace symph {
-
-// ------------------------------------------------------------------------------------------------------------
-// generic path: one wave per (token, query head)
-// ------------------------------------------------------------------------------------------------------------
-struct GenericParams {
-  const void* k_layer;
-  const void* v_layer;
-  int64_t block_stride;
-  int32_t n_blocks, block_size, n_kv_heads, n_q_heads;
-  const void* q;
-  const void* k_new;
-  const void* v_new;
-  void* out;
-  const int32_t* cu_new_lens;
-  const int32_t* prefix_lens;
-  const int32_t* table;
-  int32_t table_stride, n_sessions, total_new_tokens;
-  float scale;
-};
-
-__device__ __forceinline__ float to_f32(float x) { return x; }
-__device__ __forceinline__ float to_f32(__bf16 x) { return (float)x; }
-__device__ __forceinline__ void from_f32(float* p, float x) { *p = x; }
-__device__ __forceinline__ void from_f32(__bf16* p, float x) { *p = (__bf16)x; }
-
-template <typename T, int D>
-__global__ __launch_bounds__(64) void attn_generic_kernel(const GenericParams p) {
-  __shared__ float q_s[D];
-  const int64_t row = blockIdx.x;  // (token, head)
-  const int32_t tok = (int32_t)(row / p.n_q_heads);
-  const int32_t h = (int32_t)(row % p.n_q_heads);
-  const int lane = threadIdx.x;
-
-  int32_t lo = 0, hi = p.n_sessions;  // session with cu[s] <= tok < cu[s+1]
-  while (hi - lo > 1) {
-    const int32_t mid = (lo + hi) >> 1;
-    if (p.cu_new_lens[mid] <= tok)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  const int32_t s = lo;
-  const int32_t cu_s = p.cu_new_lens[s];
-  const int32_t i = tok - cu_s;
-  const int32_t P = p.prefix_lens[s];
-  const int32_t G = p.n_q_heads / p.n_kv_heads;
-  const int32_t g = h / G;
-  const int32_t n_keys = P + i + 1;
-
-  const T* q = (const T*)p.q + ((int64_t)tok * p.n_q_heads + h) * D;
-  for (int c = lane; c < D; c += 64) q_s[c] = to_f32(q[c]);
-  __syncthreads();
-
-  float m = -INFINITY, l = 0.f;
-  float acc[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) acc[c] = 0.f;
-
-  for (int32_t j = lane; j < n_keys; j += 64) {
-    const T* kp = nullptr;  // a block id outside the cache names a row of zeros (score 0, value 0), as in the MFMA path
-    const T* vp = nullptr;
-    if (j < P) {
-      const int32_t jb = j / p.block_size;
-      const int32_t b = jb < p.table_stride ? p.table[(int64_t)s * p.table_stride + jb] : -1;
-      if (b >= 0 && b < p.n_blocks) {
-        const int64_t e = (int64_t)b * p.block_stride + ((int64_t)(j - jb * p.block_size) * p.n_kv_heads + g) * D;
-        kp = (const T*)p.k_layer + e;
-        vp = (const T*)p.v_layer + e;
-      }
-    } else {
-      const int64_t e = ((int64_t)(cu_s + j - P) * p.n_kv_heads + g) * D;
-      kp = (const T*)p.k_new + e;
-      vp = (const T*)p.v_new + e;
-    }
-    float dot = 0.f;
-    if (kp) {
-#pragma unroll 8
-      for (int c = 0; c < D; ++c) dot = fmaf(q_s[c], to_f32(kp[c]), dot);
-    }
-    const float x = p.scale * dot;
-    const float m_new = fmaxf(m, x);
-    const float alpha = expf(m - m_new);  // m = -inf on the first key: alpha = 0
-    const float w = expf(x - m_new);
-    l = l * alpha + w;
-    if (vp) {
-#pragma unroll
-      for (int c = 0; c < D; ++c) acc[c] = fmaf(w, to_f32(vp[c]), acc[c] * alpha);
-    } else {
-#pragma unroll
-      for (int c = 0; c < D; ++c) acc[c] *= alpha;
-    }
-    m = m_new;
-  }
-
-  // merge the 64 per-lane partial softmaxes
-  float M = m;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
-  const float f = (m == -INFINITY) ? 0.f : expf(m - M);
-  float lt = l * f;
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) lt += __shfl_xor(lt, o);
-  const float inv = lt > 0.f ? 1.0f / lt : 0.f;  // (every row sees at least itself, so the sum is positive)
-  T* out = (T*)p.out + ((int64_t)tok * p.n_q_heads + h) * D;
-#pragma unroll
-  for (int c = 0; c < D; ++c) {
-    float a = acc[c] * f;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) a += __shfl_xor(a, o);
-    if (lane == (c & 63)) from_f32(out + c, a * inv);
-  }
-}
 
 // ------------------------------------------------------------------------------------------------------------
 // bf16 MFMA path, head_dim 128
@@ -592,24 +480,6 @@ static __device__ __attribute__((aligned(256))) const unsigned kZeroRow[64] = {}
 // A row sum above this (one probability of 2^40 or more, or an overflow) makes the softmax reference stale.
 constexpr float kRefreshSum = 1.0995116e12f;  // 2^40
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-
-// Row r (0..31) of the A operand of S^T = K Q^T holds key key_of_row(r) of the 32-key block, chosen so that the
-// MFMA result registers 8*u .. 8*u+7 of a lane in half-wave g2 are keys 16*u + 8*g2 + 0..7.
-__device__ __forceinline__ int key_of_row(int r) {
-  const int j = r & 3, gg = (r >> 2) & 1, i = r >> 3;
-  return 16 * (i >> 1) + 8 * gg + 4 * (i & 1) + j;
-}
-
-// ds_read_b64_tr_b16: the 16 lanes of a group hand in the addresses of a 4 x 16 tile of 16-bit values (lanes
-// 4e .. 4e+3 cover row e, 4 values each) and lane i gets column i, i.e. 4 consecutive rows of one column.
-__device__ __forceinline__ s16x4 lds_read_tr16(const __bf16* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (s16x4 __attribute__((address_space(3)))*)(const_cast<__bf16*>(p)));
-}
-
 // Write one query row's 128 outputs: this lane holds d = 32*dt + 4*g2 + 8*i + j at acc[dt][4*i + j].
 __device__ __forceinline__ void store_out_row(__bf16* op, const f32x16 (&acc)[4], float inv, int g2) {
 #pragma unroll
@@ -676,28 +546,6 @@ __device__ __forceinline__ void store_out_rows_staged(char* stage, __bf16* first
   }
 }
 
-// Lanes l and l^32 hold the two halves of one query's keys.  v_permlane32_swap_b32 a, b exchanges lanes 32..63 of a
-// with lanes 0..31 of b, so starting from two copies of x it leaves a = low half twice, b = high half twice.
-// Written as inline assembly: with this compiler the builtin hands back the first register for both results.
-__device__ __forceinline__ void swap_halves(float x, float& lo_twice, float& hi_twice) {
-  float a = x, b = x;
-  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));  // a pure function of a, b: free to be scheduled
-  lo_twice = a;
-  hi_twice = b;
-}
-__device__ __forceinline__ float max_across_halves(float x) {
-  float lo, hi;
-  swap_halves(x, lo, hi);
-  return fmaxf(lo, hi);
-}
-__device__ __forceinline__ float sum_across_halves(float x) {
-  float lo, hi;
-  swap_halves(x, lo, hi);
-  return lo + hi;
-}
-
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // LDS tile layout shared by K and V (64 key rows x 256 bytes): rows are stored in groups of four; a group is the
 // 1 KiB that one wave writes with one direct global->LDS load (lane l lands at group base + 16*l), groups are
@@ -762,7 +610,6 @@ __device__ __forceinline__ bool direct_item(const MfmaParams& p, int bmt, int pi
     const float inv_c = 1.0f / (float)C;
     const float below = (float)(nt - 1);
     float pieces = 0.f, split = 0.f;
-#pragma unroll 4
     for (int u = 0; u < n_units; ++u) {
       const float n = floorf(__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, below), u)) * inv_c);
       pieces += n;
@@ -2029,33 +1876,6 @@ int64_t prefill_attn_workspace_bytes(const symph_kv_cache* c, int32_t n_sessions
   return pl.total_bytes;
 }
 
-template <typename T, int D>
-static int32_t launch_generic(const AttnArgs& a, hipStream_t stream) {
-  GenericParams p;
-  p.k_layer = a.k_layer;
-  p.v_layer = a.v_layer;
-  p.block_stride = a.block_stride;
-  p.n_blocks = a.n_blocks;
-  p.block_size = a.block_size;
-  p.n_kv_heads = a.n_kv_heads;
-  p.n_q_heads = a.n_q_heads;
-  p.q = a.q;
-  p.k_new = a.k_new;
-  p.v_new = a.v_new;
-  p.out = a.out;
-  p.cu_new_lens = a.cu_new_lens;
-  p.prefix_lens = a.prefix_lens;
-  p.table = a.table;
-  p.table_stride = a.table_stride;
-  p.n_sessions = a.n_sessions;
-  p.total_new_tokens = a.total_new_tokens;
-  p.scale = a.scale;
-  const int64_t rows = (int64_t)a.total_new_tokens * a.n_q_heads;
-  if (rows > 0x7FFFFFFFLL) return SYMPH_EUNSUPPORTED;
-  hipLaunchKernelGGL((attn_generic_kernel<T, D>), dim3((unsigned)rows), dim3(64), 0, stream, p);
-  return hipGetLastError() == hipSuccess ? SYMPH_OK : SYMPH_ELAUNCH;
-}
-
 template <int G>
 static int32_t launch_mfma(const AttnArgs& a, hipStream_t stream) {
   MfmaPlan pl;
@@ -2187,14 +2007,7 @@ int32_t launch_prefill_attn(const AttnArgs& a, hipStream_t stream) {
       default: break;
     }
   }
-  if (a.dtype == SYMPH_BF16) {
-    if (a.head_dim == 64) return launch_generic<__bf16, 64>(a, stream);
-    if (a.head_dim == 128) return launch_generic<__bf16, 128>(a, stream);
-  } else {
-    if (a.head_dim == 64) return launch_generic<float, 64>(a, stream);
-    if (a.head_dim == 128) return launch_generic<float, 128>(a, stream);
-  }
-  return SYMPH_EUNSUPPORTED;
+  return launch_rows_attn(a, stream);
 }
 
 // ------------------------------------------------------------------------------------------------------------

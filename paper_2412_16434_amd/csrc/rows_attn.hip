@@ -1,0 +1,575 @@
+// prefix_prefill_attn for the shapes the work-list kernels (prefill_attn.hip) do not cover: fp32, head_dim 64, group sizes
+// that are no power of two, blocks of fewer than 16 tokens.
+#include "attn_lanes.h"
+
+namespace symph {
+
+struct RowsParams {
+  const void* k_layer;
+  const void* v_layer;
+  int64_t block_stride;
+  int32_t n_blocks, block_size, bs_shift, n_kv_heads, n_q_heads;  // bs_shift: log2(block_size) or -1
+  const void* q;
+  const void* k_new;
+  const void* v_new;
+  void* out;
+  const int32_t* cu_new_lens;
+  const int32_t* prefix_lens;
+  const int32_t* table;
+  int32_t table_stride, n_sessions, total_new_tokens;
+  float scale;
+};
+
+__device__ __forceinline__ float to_f32(float x) { return x; }
+__device__ __forceinline__ float to_f32(__bf16 x) { return (float)x; }
+__device__ __forceinline__ void from_f32(float* p, float x) { *p = x; }
+__device__ __forceinline__ void from_f32(__bf16* p, float x) { *p = (__bf16)x; }
+
+// ---- one wave per (token, query head), lanes over keys, fp32 throughout.  q_s: D floats in LDS of the wave's own.  CH
+// output columns at a time (the scores are worked out again for each: where registers matter more than time).
+template <typename T, int D, int CH>
+__device__ __forceinline__ void row_by_lanes(const RowsParams& p, int32_t s, int32_t tok, int32_t h, float* q_s) {
+  const int lane = threadIdx.x & 63;
+  const int32_t cu_s = p.cu_new_lens[s];
+  const int32_t i = tok - cu_s;
+  const int32_t P = p.prefix_lens[s];
+  const int32_t G = p.n_q_heads / p.n_kv_heads;
+  const int32_t g = h / G;
+  const int32_t n_keys = P + i + 1;
+
+  const T* q = (const T*)p.q + ((int64_t)tok * p.n_q_heads + h) * D;
+  for (int c = lane; c < D; c += 64) q_s[c] = to_f32(q[c]);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  T* out = (T*)p.out + ((int64_t)tok * p.n_q_heads + h) * D;
+
+  for (int c0 = 0; c0 < D; c0 += CH) {
+    float m = -INFINITY, l = 0.f;
+    float acc[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) acc[c] = 0.f;
+
+    for (int32_t j = lane; j < n_keys; j += 64) {
+      const T* kp = nullptr;  // a block id outside the cache names a row of zeros (score 0, value 0), as in the other kernels
+      const T* vp = nullptr;
+      if (j < P) {
+        const int32_t jb = j / p.block_size;
+        const int32_t b = jb < p.table_stride ? p.table[(int64_t)s * p.table_stride + jb] : -1;
+        if (b >= 0 && b < p.n_blocks) {
+          const int64_t e = (int64_t)b * p.block_stride + ((int64_t)(j - jb * p.block_size) * p.n_kv_heads + g) * D;
+          kp = (const T*)p.k_layer + e;
+          vp = (const T*)p.v_layer + e;
+        }
+      } else {
+        const int64_t e = ((int64_t)(cu_s + j - P) * p.n_kv_heads + g) * D;
+        kp = (const T*)p.k_new + e;
+        vp = (const T*)p.v_new + e;
+      }
+      float dot = 0.f;
+      if (kp) {
+#pragma unroll 8
+        for (int c = 0; c < D; ++c) dot = fmaf(q_s[c], to_f32(kp[c]), dot);
+      }
+      const float x = p.scale * dot;
+      const float m_new = fmaxf(m, x);
+      const float alpha = expf(m - m_new);  // m = -inf on the first key: alpha = 0
+      const float w = expf(x - m_new);
+      l = l * alpha + w;
+      if (vp) {
+#pragma unroll
+        for (int c = 0; c < CH; ++c) acc[c] = fmaf(w, to_f32(vp[c0 + c]), acc[c] * alpha);
+      } else {
+#pragma unroll
+        for (int c = 0; c < CH; ++c) acc[c] *= alpha;
+      }
+      m = m_new;
+    }
+
+    // merge the 64 per-lane partial softmaxes
+    float M = m;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
+    const float f = (m == -INFINITY) ? 0.f : expf(m - M);
+    float lt = l * f;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) lt += __shfl_xor(lt, o);
+    const float inv = lt > 0.f ? 1.0f / lt : 0.f;  // (every row sees at least itself, so the sum is positive)
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      float a = acc[c] * f;
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) a += __shfl_xor(a, o);
+      if (lane == ((c0 + c) & 63)) from_f32(out + c0 + c, a * inv);
+    }
+  }
+}
+
+// Addresses that the tiled kernel below cannot load 16 bytes wide from.
+template <typename T, int D>
+__global__ __launch_bounds__(64) void attn_row_kernel(const RowsParams p) {
+  __shared__ float q_s[D];
+  const int64_t row = blockIdx.x;  // (token, head)
+  const int32_t tok = (int32_t)(row / p.n_q_heads);
+  int32_t lo = 0, hi = p.n_sessions;  // session with cu[s] <= tok < cu[s+1]
+  while (hi - lo > 1) {
+    const int32_t mid = (lo + hi) >> 1;
+    if (p.cu_new_lens[mid] <= tok)
+      lo = mid;
+    else
+      hi = mid;
+  }
+  row_by_lanes<T, D, D>(p, lo, tok, (int32_t)(row % p.n_q_heads), q_s);
+}
+
+// ---- the tiled kernel: one workgroup per (session, kv-head, tile of R query rows).  The rows of a kv-head, token by
+// token and the G heads of a token beside each other (any G), are cut into tiles of R = 32 (bf16) or 16 (fp32); the eight
+// waves of a workgroup take the tile's key blocks of R keys in turn, each with a softmax of its own, and are combined
+// through LDS at the end.  No scheduling kernel, no workspace, one launch: these shapes are small models and odd group
+// sizes, whose calls are short, so what counts is how few trips to memory stand one behind the other.
+//
+// What is held in 32 bits: probabilities too.  The bf16 kernel splits them into two bf16 values (p = hi + lo to 2^-17) and
+// multiplies V with both, which leaves the rounding of the output as the only one; the fp32 kernel uses the fp32 matrix
+// instruction throughout.
+//
+// Measured against one wave per row (attn_row_kernel below, 32-bit arithmetic on the vector unit, lanes over keys): six
+// sessions of 300 to 2000 tokens, 64-wide heads, 380 -> 22 us; one fp32 session of 256 tokens, 24.6 -> 11.6 us, which is the
+// call itself; three fp32 sessions of 8192, 775 -> 221.  Four waves per tile instead of eight: 24, 13 and 371; registers for
+// two workgroups per compute unit (64-wide heads; spills): 30 us.  The error against 64 bits is the same in bf16 and lower in
+// fp32 (2.9e-7 for 4.7e-7 at 128 x 8000 keys).
+//
+// K goes from memory straight into operand registers: a row's D values are the operand's contraction index, and any order
+// of it will do as long as Q has the same.  V is needed transposed: in bf16 through LDS (a tile of the wave's own, rows
+// 64 bytes apart in banks so that the transposing read has no conflicts), in fp32 not at all (its operand has one value
+// per lane).  The next block's rows are asked for before the present one is used, the block ids one block earlier.
+constexpr int kRowsWaves = 8;
+static __device__ __attribute__((aligned(256))) const unsigned kAbsentRow[128] = {};  // a head's row of zeros
+
+template <typename T>
+struct RowsTile;
+template <>
+struct RowsTile<__bf16> {
+  static constexpr int R = 32;
+};
+template <>
+struct RowsTile<float> {
+  static constexpr int R = 16;
+};
+
+// Last index i of [0, n) with holds(i), for a predicate that holds up to some index and not after it (holds(0) is taken for
+// granted): 64 lanes at once, one trip to memory for up to 64 sessions, two for 4096.
+template <typename F>
+__device__ __forceinline__ int wave_last(int n, F holds) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, hi = n;
+  while (hi - lo > 1) {
+    const int step = (hi - lo + 63) >> 6;
+    const int i = lo + lane * step;
+    const int k = __popcll(__ballot(lane == 0 || (i < hi && holds(i)))) - 1;
+    lo += k * step;
+    hi = min(hi, lo + step);
+  }
+  return lo;
+}
+
+// The eight waves' results of a tile of R rows, DC columns at a time through LDS: out = sum_w f_w O_w / sum_w f_w l_w with
+// f_w = e^(m_w - max_w m_w) (base 2 or e, as the caller's references are).  put(round, f, mine) writes the lane's part of the
+// wave's columns, scaled.  A result that is not finite (an infinity or a NaN among the inputs, which the matrix product
+// spreads over rows that must not see its key) is worked out again row by row.
+template <typename T, int D, int R, int DC, typename Put, typename Exp>
+__device__ __forceinline__ void combine_rows(const RowsParams& p, char* lds, const float (*wave_m)[R],
+                                             const float (*wave_l)[R], int& redo, Put put, Exp exp_of, int s, int cu_s,
+                                             int kvh, int G, int64_t row0, int n_rows) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int kStride = DC + 4;  // floats between rows (the padding spreads them over the banks)
+  float* const all = reinterpret_cast<float*>(lds);
+  const int n = lane & (R - 1);
+  float M = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < kRowsWaves; ++w) M = fmaxf(M, wave_m[w][n]);
+  const float mine_m = wave_m[wave][n];
+  const float f = mine_m == -INFINITY ? 0.f : exp_of(mine_m - M);
+  // thread t adds up V columns from c0 on of row t * V / DC
+  constexpr int V = R * DC / (64 * kRowsWaves);
+  const int r = tid * V / DC, c0 = tid * V % DC;
+  float Mr = -INFINITY, L = 0.f;
+#pragma unroll
+  for (int w = 0; w < kRowsWaves; ++w) Mr = fmaxf(Mr, wave_m[w][r]);
+#pragma unroll
+  for (int w = 0; w < kRowsWaves; ++w)
+    L += wave_m[w][r] == -INFINITY ? 0.f : wave_l[w][r] * exp_of(wave_m[w][r] - Mr);
+  const float inv = 1.0f / L;
+  const int64_t row = row0 + r;
+  const int tok = (int)(row / G);
+  T* const op = (T*)p.out + ((int64_t)(cu_s + tok) * p.n_q_heads + kvh * G + (int)(row - (int64_t)tok * G)) * D;
+  bool bad = false;
+#pragma unroll
+  for (int round = 0; round < D / DC; ++round) {
+    if (round > 0) __syncthreads();  // the columns before have been added up
+    put(round, f, all + wave * R * kStride);
+    __syncthreads();
+    float sum[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) sum[v] = 0.f;
+#pragma unroll
+    for (int w = 0; w < kRowsWaves; ++w)
+#pragma unroll
+      for (int v = 0; v < V; ++v) sum[v] += all[(w * R + r) * kStride + c0 + v];
+    if (r < n_rows) {
+      typedef T vec __attribute__((ext_vector_type(V)));
+      vec x;
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        bad = bad || !(fabsf(sum[v] * inv) < INFINITY);
+        x[v] = (T)(sum[v] * inv);
+      }
+      *reinterpret_cast<vec*>(op + round * DC + c0) = x;
+    }
+  }
+  if (__any(bad)) redo = 1;
+  __syncthreads();
+  if (!redo) return;
+  for (int i = wave; i < n_rows; i += kRowsWaves) {
+    const int64_t again = row0 + i;
+    const int t = (int)(again / G);
+    row_by_lanes<T, D, 32>(p, s, cu_s + t, kvh * G + (int)(again - (int64_t)t * G), all + wave * D);
+  }
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(64 * kRowsWaves, 2) void attn_rows_kernel(const RowsParams p) {
+  constexpr bool kBf16 = sizeof(T) == 2;
+  constexpr int R = RowsTile<T>::R;
+  constexpr int kVRow = D * 2 + 64;                                  // bytes between V rows in LDS (bf16)
+  constexpr int kVBytes = kBf16 ? kRowsWaves * 32 * kVRow : 0;
+  constexpr int DC = kBf16 ? 32 : D;                                 // columns combined at a time
+  constexpr int kCombBytes = kRowsWaves * R * (DC + 4) * 4;
+  __shared__ __attribute__((aligned(16))) char lds[kVBytes > kCombBytes ? kVBytes : kCombBytes];
+  __shared__ float wave_m[kRowsWaves][R], wave_l[kRowsWaves][R];
+  __shared__ int redo;
+
+  const int Hkv = p.n_kv_heads;
+  const int G = p.n_q_heads / Hkv;
+  const int kvh = blockIdx.x % Hkv;
+  const int slot = blockIdx.x / Hkv;
+  // Session s has the tile slots from floor(cu[s] * G / R) + s on: at least as many as it has tiles, without a list
+  auto first_slot = [&](int s) { return (int)((int64_t)p.cu_new_lens[s] * G / R) + s; };
+  const int s = wave_last(p.n_sessions, [&](int i) { return first_slot(i) <= slot; });
+  const int cu_s = p.cu_new_lens[s];
+  const int N = p.cu_new_lens[s + 1] - cu_s;
+  const int P = p.prefix_lens[s];
+  const int64_t row0 = (int64_t)(slot - first_slot(s)) * R;
+  const int64_t rows = (int64_t)N * G;
+  if (row0 >= rows) return;
+  const int n_rows = (int)min((int64_t)R, rows - row0);
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & (R - 1);   // query row of this lane; also its row of the K operand
+  const int kg = lane / R;        // its share of the contraction index: half (bf16) or quarter (fp32) of the wave
+  const int64_t my_row = row0 + min(n, n_rows - 1);
+  const int tok = (int)(my_row / G);
+  const int limit = P + tok;      // last key this row may see
+  const int total_keys = P + N;
+  const int n_blocks_k = (P + (int)((row0 + n_rows - 1) / G) + R) / R;  // key blocks up to the last row's limit
+  const T* const qp = (const T*)p.q + ((int64_t)(cu_s + tok) * p.n_q_heads + kvh * G + (int)(my_row - (int64_t)tok * G)) * D;
+  if (tid == 0) redo = 0;
+
+  // ---- rows of K and V: block ids are read one per lane (lane i: key i of the block) and passed between lanes
+  const int32_t* const table_row = p.table + (int64_t)s * p.table_stride;
+  auto block_of = [&](int key) { return p.bs_shift >= 0 ? key >> p.bs_shift : key / p.block_size; };
+  auto fetch_id = [&](int blk) {
+    const int key = blk * R + n;
+    const int j = block_of(key);
+    return blk < n_blocks_k && key < P && j < p.table_stride ? table_row[j] : -1;
+  };
+  auto row_of = [&](const void* pool, const void* fresh, int key, int id) {
+    if (key < P) {
+      if (id < 0 || id >= p.n_blocks) return (const T*)kAbsentRow;
+      return (const T*)pool + (int64_t)id * p.block_stride +
+             ((int64_t)(key - block_of(key) * p.block_size) * Hkv + kvh) * D;
+    }
+    return key < total_keys ? (const T*)fresh + ((int64_t)(cu_s + key - P) * Hkv + kvh) * D : (const T*)kAbsentRow;
+  };
+
+  if constexpr (kBf16) {
+    constexpr int NS = D / 16;            // contraction steps of the first product
+    constexpr int NT = D / 32;            // 32-column tiles of the output
+    constexpr int LPR = D / 8, RPI = 64 / LPR, NV = 32 / RPI;  // lanes per V row, rows per load, loads
+    char* const v_lds = lds + wave * 32 * kVRow;
+    bf16x8 q[NS];
+#pragma unroll
+    for (int st = 0; st < NS; ++st) q[st] = *reinterpret_cast<const bf16x8*>(qp + 16 * st + 8 * kg);
+    const int krow = key_of_row(n);
+    const int vlane_row = lane / LPR, vlane_col = (lane % LPR) * 16;
+    bf16x8 kr[NS];
+    u32x4 vr[NV];
+    auto load_block = [&](int blk, int id) {
+      const T* const k_row = row_of(p.k_layer, p.k_new, blk * 32 + krow, __shfl(id, krow)) + 8 * kg;
+#pragma unroll
+      for (int st = 0; st < NS; ++st) kr[st] = *reinterpret_cast<const bf16x8*>(k_row + 16 * st);
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int r = i * RPI + vlane_row;
+        const T* const v_row = row_of(p.v_layer, p.v_new, blk * 32 + r, __shfl(id, r));
+        vr[i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(v_row) + vlane_col);
+      }
+    };
+    const int i16 = lane & 15;
+    const int v_off = (8 * kg + (i16 >> 2)) * kVRow + 32 * ((lane >> 4) & 1) + 8 * (i16 & 3);
+    const float cs = p.scale * 1.4426950408889634f;
+    f32x16 o[NT];
+#pragma unroll
+    for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
+    float m = -INFINITY, l = 0.f;  // in log2 units
+    int id_next = fetch_id(wave);
+    if (wave < n_blocks_k) load_block(wave, id_next);
+    id_next = fetch_id(wave + kRowsWaves);
+    for (int blk = wave; blk < n_blocks_k; blk += kRowsWaves) {
+      f32x16 sc[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sc[h][e] = 0.f;
+#pragma unroll
+      for (int st = 0; st < NS; ++st)  // (two chains: a product does not wait for the one before it)
+        sc[st & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[st], q[st], sc[st & 1], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        *reinterpret_cast<u32x4*>(v_lds + (i * RPI + vlane_row) * kVRow + vlane_col) = vr[i];
+      if (blk + kRowsWaves < n_blocks_k) load_block(blk + kRowsWaves, id_next);
+      id_next = fetch_id(blk + 2 * kRowsWaves);
+      float x[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) x[e] = sc[0][e] + sc[1][e];
+      if (blk * 32 + 31 > P) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (blk * 32 + 16 * (e >> 3) + 8 * kg + (e & 7) > limit) x[e] = -INFINITY;
+      }
+      float mx = x[0];
+#pragma unroll
+      for (int e = 1; e < 16; ++e) mx = fmaxf(mx, x[e]);
+      const float m_new = fmaxf(m, max_across_halves(mx) * cs);
+      if (__any(m_new > m)) {
+        const float a = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+        m = m_new;
+        l *= a;
+#pragma unroll
+        for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) o[dt][e] *= a;
+      }
+      const float ref = m == -INFINITY ? 0.f : m;
+      bf16x8 hi[2], lo[2];
+      float sum = 0.f;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const float w = __builtin_amdgcn_exp2f(fmaf(x[e], cs, -ref));
+        sum += w;
+        hi[e >> 3][e & 7] = (__bf16)w;
+        lo[e >> 3][e & 7] = (__bf16)(w - (float)hi[e >> 3][e & 7]);
+      }
+      l += sum;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int dt = 0; dt < NT; ++dt) {
+          const char* vp = v_lds + v_off + 16 * u * kVRow + 64 * dt;
+          const s16x4 a0 = lds_read_tr16(reinterpret_cast<const __bf16*>(vp));
+          const s16x4 a1 = lds_read_tr16(reinterpret_cast<const __bf16*>(vp + 4 * kVRow));
+          const bf16x8 v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
+          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, hi[u], o[dt], 0, 0, 0);
+          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, lo[u], o[dt], 0, 0, 0);
+        }
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      __builtin_amdgcn_wave_barrier();  // the tile has been read before the next one is written
+    }
+    const float l_row = sum_across_halves(l);
+    if (kg == 0) {
+      wave_m[wave][n] = m;
+      wave_l[wave][n] = l_row;
+    }
+    __syncthreads();  // (also: no wave reads its V tile any more, the buffer is free)
+    combine_rows<T, D, R, DC>(p, lds, wave_m, wave_l, redo, [&](int round, float f, float* mine) {
+      // (o[round] by a chain of selects: a register array cannot be indexed)
+#pragma unroll
+      for (int dt = 0; dt < NT; ++dt)
+        if (dt == round) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            *reinterpret_cast<f32x4*>(mine + n * (DC + 4) + 4 * kg + 8 * i) =
+                f32x4{o[dt][4 * i] * f, o[dt][4 * i + 1] * f, o[dt][4 * i + 2] * f, o[dt][4 * i + 3] * f};
+        }
+    }, [](float x) { return __builtin_amdgcn_exp2f(x); }, s, cu_s, kvh, G, row0, n_rows);
+  } else {
+    constexpr int NS = D / 16;  // 16-byte loads of a row per lane
+    constexpr int NH = D / 64;  // groups of 64 output columns
+    f32x4 q[NS];
+#pragma unroll
+    for (int j = 0; j < NS; ++j) q[j] = *reinterpret_cast<const f32x4*>(qp + 16 * j + 4 * kg);
+    f32x4 kr[NS], vr[4][NH];
+    auto load_block = [&](int blk, int id) {
+      const T* const k_row = row_of(p.k_layer, p.k_new, blk * 16 + n, id) + 4 * kg;
+#pragma unroll
+      for (int j = 0; j < NS; ++j) kr[j] = *reinterpret_cast<const f32x4*>(k_row + 16 * j);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {  // key 4 * kg + e: values 64 * h + 4 * n .. + 3 of its row
+        const T* const v_row = row_of(p.v_layer, p.v_new, blk * 16 + 4 * kg + e, __shfl(id, 4 * kg + e)) + 4 * n;
+#pragma unroll
+        for (int h = 0; h < NH; ++h) vr[e][h] = *reinterpret_cast<const f32x4*>(v_row + 64 * h);
+      }
+    };
+    // o[h][c][e]: column 64 * h + 16 * kg + 4 * e + c of row n.  A sum over thousands of keys in one chain loses bits (6.0e-7
+    // from 64 bits at 8192 keys, a lane's shorter chain in the kernel above 4.6e-7): kRun blocks are added up by themselves
+    // (o_run, l_run) before they join the rest.
+    constexpr int kRun = 8;
+    f32x4 o[NH][4], o_run[NH][4];
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) o[h][c] = o_run[h][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, l = 0.f, l_run = 0.f;
+    auto join_run = [&]() {
+      l += l_run;
+      l_run = 0.f;
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          o[h][c] += o_run[h][c];
+          o_run[h][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    int run = 0;
+    int id_next = fetch_id(wave);
+    if (wave < n_blocks_k) load_block(wave, id_next);
+    id_next = fetch_id(wave + kRowsWaves);
+    for (int blk = wave; blk < n_blocks_k; blk += kRowsWaves) {
+      f32x4 sc[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < NS; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[j][e], q[j][e], sc[e], 0, 0, 0);
+      f32x4 v[4][NH];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int h = 0; h < NH; ++h) v[e][h] = vr[e][h];
+      if (blk + kRowsWaves < n_blocks_k) load_block(blk + kRowsWaves, id_next);
+      id_next = fetch_id(blk + 2 * kRowsWaves);
+      float x[4];  // key 4 * kg + e
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[e] = p.scale * ((sc[0][e] + sc[1][e]) + (sc[2][e] + sc[3][e]));
+        if (blk * 16 + 4 * kg + e > limit) x[e] = -INFINITY;
+      }
+      float mx = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      const float m_new = fmaxf(m, mx);
+      if (__any(m_new > m)) {
+        const float a = m == -INFINITY ? 0.f : expf(m - m_new);
+        m = m_new;
+        l *= a;
+        l_run *= a;
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            o[h][c] *= a;
+            o_run[h][c] *= a;
+          }
+      }
+      const float ref = m == -INFINITY ? 0.f : m;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float w = expf(x[e] - ref);
+        l_run += w;
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            o_run[h][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[e][h][c], w, o_run[h][c], 0, 0, 0);
+      }
+      if (++run == kRun) {
+        join_run();
+        run = 0;
+      }
+    }
+    join_run();
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (kg == 0) {
+      wave_m[wave][n] = m;
+      wave_l[wave][n] = l;
+    }
+    __syncthreads();
+    combine_rows<T, D, R, DC>(p, lds, wave_m, wave_l, redo, [&](int, float f, float* mine) {
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          *reinterpret_cast<f32x4*>(mine + n * (DC + 4) + 64 * h + 16 * kg + 4 * e) =
+              f32x4{o[h][0][e] * f, o[h][1][e] * f, o[h][2][e] * f, o[h][3][e] * f};
+    }, [](float x) { return expf(x); }, s, cu_s, kvh, G, row0, n_rows);
+  }
+}
+
+// ------------------------------------------------------------------------------------------------------------
+// host side
+// ------------------------------------------------------------------------------------------------------------
+template <typename T, int D>
+static int32_t launch_rows(const AttnArgs& a, hipStream_t stream) {
+  RowsParams p;
+  p.k_layer = a.k_layer;
+  p.v_layer = a.v_layer;
+  p.block_stride = a.block_stride;
+  p.n_blocks = a.n_blocks;
+  p.block_size = a.block_size;
+  p.bs_shift = (a.block_size & (a.block_size - 1)) == 0 ? __builtin_ctz((unsigned)a.block_size) : -1;
+  p.n_kv_heads = a.n_kv_heads;
+  p.n_q_heads = a.n_q_heads;
+  p.q = a.q;
+  p.k_new = a.k_new;
+  p.v_new = a.v_new;
+  p.out = a.out;
+  p.cu_new_lens = a.cu_new_lens;
+  p.prefix_lens = a.prefix_lens;
+  p.table = a.table;
+  p.table_stride = a.table_stride;
+  p.n_sessions = a.n_sessions;
+  p.total_new_tokens = a.total_new_tokens;
+  p.scale = a.scale;
+  const int64_t rows = (int64_t)a.total_new_tokens * a.n_q_heads;
+  if (rows > 0x7FFFFFFFLL) return SYMPH_EUNSUPPORTED;
+  const uintptr_t address_bits = (uintptr_t)a.k_layer | (uintptr_t)a.v_layer | (uintptr_t)a.q | (uintptr_t)a.k_new |
+                                 (uintptr_t)a.v_new | (uintptr_t)a.out | (uintptr_t)(a.block_stride * (int64_t)sizeof(T));
+  const int64_t slots = (rows / a.n_kv_heads) / RowsTile<T>::R + a.n_sessions;  // see first_slot in the kernel
+  const int64_t groups = slots * a.n_kv_heads;
+  // The tiled kernel loads 16 bytes at a time.  (A row of a head is a multiple of that, so the bases and the block stride
+  // decide.)
+  if ((address_bits & 15) == 0 && groups <= 0x7FFFFFFFLL)
+    hipLaunchKernelGGL((attn_rows_kernel<T, D>), dim3((unsigned)groups), dim3(64 * kRowsWaves), 0, stream, p);
+  else
+    hipLaunchKernelGGL((attn_row_kernel<T, D>), dim3((unsigned)rows), dim3(64), 0, stream, p);
+  return hipGetLastError() == hipSuccess ? SYMPH_OK : SYMPH_ELAUNCH;
+}
+
+int32_t launch_rows_attn(const AttnArgs& a, hipStream_t stream) {
+  if (a.dtype == SYMPH_BF16) {
+    if (a.head_dim == 64) return launch_rows<__bf16, 64>(a, stream);
+    if (a.head_dim == 128) return launch_rows<__bf16, 128>(a, stream);
+  } else {
+    if (a.head_dim == 64) return launch_rows<float, 64>(a, stream);
+    if (a.head_dim == 128) return launch_rows<float, 128>(a, stream);
+  }
+  return SYMPH_EUNSUPPORTED;
+}
+
+}  // namespace symph

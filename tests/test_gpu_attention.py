@@ -197,6 +197,71 @@ def test_direct_calls(oracle_mod, hkv, group, bs, prefix, new):
     assert np.sqrt(np.sum((f(got) - f(listed)) ** 2) / np.sum(f(listed) ** 2)) <= 1e-2
 
 
+@pytest.mark.parametrize("dtype,d,hkv,group,bs,prefix,new", [
+    ("bf16", 64, 8, 4, 16, [0, 1, 31, 32, 33, 700], [9, 1, 8, 7, 16, 0]),    # tiles of 32 rows and keys: edges, empty turns
+    ("bf16", 64, 1, 1, 8, [255, 256, 257], [31, 32, 33]),                    # eight waves x 32 keys; small blocks
+    ("bf16", 128, 2, 5, 24, [50, 513], [13, 3]),                             # tiles that end inside a token's heads; odd blocks
+    ("bf16", 128, 3, 7, 32, [300], [1]),                                     # a decode row
+    ("fp32", 64, 2, 3, 16, [0, 15, 16, 17, 128], [5, 6, 1, 0, 11]),
+    ("fp32", 128, 4, 1, 16, [127, 1100], [16, 17]),                          # more than eight blocks per wave: sums in runs
+    ("bf16", 64, 2, 2, 16, [20] * 70, [1, 0] * 35),                          # more sessions than lanes
+])
+def test_shapes_without_a_work_list(oracle_mod, dtype, d, hkv, group, bs, prefix, new):
+    cfg = _cfg(dtype=dtype, head_dim=d, n_sessions=len(new), n_kv_heads=hkv, n_q_heads=hkv * group, block_size=bs,
+               n_blocks=512, prefix_dist=("const", max(prefix)))
+    sess = W.make_sessions(cfg, 71, new_lens=np.array(new))
+    sess.prefix_lens[:] = prefix
+    sess.buf_token_offsets[1:] = np.cumsum(prefix)
+    check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 71), label="rows")
+
+
+@pytest.mark.parametrize("dtype,d,group", [("bf16", 64, 4), ("bf16", 128, 3), ("fp32", 64, 2), ("fp32", 128, 1)])
+def test_rows_do_not_see_what_they_must_not(oracle_mod, dtype, d, group):
+    """An infinity and a NaN among the values of a later token of the turn: earlier tokens are finite and right (a matrix
+    product multiplies them by zero, which is NaN), the token itself and the ones after it are not finite."""
+    cfg = _cfg(dtype=dtype, head_dim=d, n_sessions=2, n_kv_heads=2, n_q_heads=2 * group)
+    sess = W.make_sessions(cfg, 73, new_lens=np.array([40, 9]))
+    k_pool, v_pool, q, k_new, v_new = W.make_attn_inputs(cfg, sess, 73)
+    ref = oracle_mod.prefix_prefill_attn(k_pool, v_pool, q, k_new, v_new, sess.cu_new_lens, sess.prefix_lens,
+                                         sess.block_table, cfg.scale)
+    bits = (lambda x: W.f32_to_bf16_bits(np.float32([x]))[0]) if dtype == "bf16" else np.float32
+    v_new[17, 0, 5] = bits(np.inf)
+    v_new[44, 1, 3] = np.float32(np.nan) if dtype == "fp32" else W.SENTINEL16
+    got = widen(gpu_attention(cfg, sess, (k_pool, v_pool, q, k_new, v_new), scale=cfg.scale))
+    touched = np.zeros(got.shape, dtype=bool)
+    touched[17:40, :group, 5] = True
+    touched[44:49, group:, 3] = True
+    assert not np.isfinite(got[touched]).any() and np.isfinite(got[~touched]).all()
+    err = np.abs(got - ref)[~touched]
+    assert err.max() <= TOL[dtype][0]
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("fp32", 128)])
+def test_unaligned_pools_agree_with_aligned_ones(dtype, d):
+    """Pools that start one element past a 16-byte boundary take the kernel with narrow loads."""
+    import torch
+    from gpu_util import DeviceSessions, to_dev
+    cfg = _cfg(dtype=dtype, head_dim=d, n_sessions=5, n_blocks=512)
+    sess = W.make_sessions(cfg, 79)
+    k_pool, v_pool, q, k_new, v_new = W.make_attn_inputs(cfg, sess, 79)
+    ds = DeviceSessions(sess)
+    outs = []
+    for shift in (0, 1):
+        pools = []
+        for a in (k_pool, v_pool):
+            t = to_dev(a)[None]
+            flat = torch.empty(t.numel() + 8, dtype=t.dtype, device=t.device)
+            pools.append(flat[shift:shift + t.numel()].view(t.shape).copy_(t))
+        qd = to_dev(q)
+        out = torch.full_like(qd, float("nan"))
+        S.prefix_prefill_attn(S.KVCache(*pools), 0, qd, to_dev(k_new), to_dev(v_new), out, ds.cu_new_lens, ds.prefix_lens,
+                              ds.table, sess.max_new_len, sess.max_prefix_len, cfg.scale)
+        outs.append(out.double())
+    # both are within a rounding of the same 32-bit value: half a step of bf16 each, or sums in another order
+    rel = float((outs[0] - outs[1]).norm() / outs[0].norm())
+    assert rel <= (2.0 ** -8 if dtype == "bf16" else 2e-6), rel
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_seeded_random_batches(oracle_mod, seed):
     """Five drawn batches per seed: kv-heads, group size, block size, session count, length ranges, and whether the
