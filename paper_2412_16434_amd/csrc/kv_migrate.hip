@@ -82,16 +82,22 @@ __global__ __launch_bounds__(256) void kv_migrate_kernel(const MigrateParams p) 
   }
   if (tg >= p.total_tokens) return;
 
-  // session s with offsets[s] <= tg < offsets[s+1] (sessions of length 0 are skipped by taking the last match)
+  // session s with offsets[s] <= tg < offsets[s+1] (sessions of length 0 are skipped by taking the last match).  The search
+  // is for the wave's first token, on the scalar unit; where a wave holds several tokens (short rows) a lane whose token
+  // lies past that session's end walks on.  (A search per lane is a chain of log2(sessions) vector loads.)
+  const int64_t tg0 = ((int64_t)__builtin_amdgcn_readfirstlane((int32_t)(tg >> 32)) << 32) |
+                      (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)tg);
   int32_t lo = 0, hi = p.n_sessions;
   while (hi - lo > 1) {
     const int32_t mid = (lo + hi) >> 1;
-    if (p.offsets[mid] <= tg)
+    if (p.offsets[mid] <= tg0)
       lo = mid;
     else
       hi = mid;
   }
-  const int32_t s = lo;
+  int32_t s = lo;
+  if constexpr (!UNIFORM)
+    while (s + 1 < p.n_sessions && p.offsets[s + 1] <= tg) ++s;
   const int64_t off_s = p.offsets[s];
   const int32_t first = p.tail_begin ? p.tail_begin[s] : 0;
   const int32_t P = p.prefix_lens[s] - first;  // tokens of this session in the buffer
@@ -248,7 +254,7 @@ static int32_t launch_rows(const MigrateParams& p_in, hipStream_t stream) {
   const int64_t gy = ceil_div64(p_in.plane_end - p_in.plane_begin, PLANES);
   if (gx > 0x7FFFFFFFLL || gy > 65535) return SYMPH_EUNSUPPORTED;
   MigrateParams p = p_in;
-  p.xcd_chunk = PACK ? (int32_t)(gx / 8) : 0;
+  p.xcd_chunk = (int32_t)(gx / 8);
   hipLaunchKernelGGL((kv_migrate_rows_kernel<VecT, PACK, ROWS, PLANES, kMigrateNT>), dim3((unsigned)gx, (unsigned)gy),
                      dim3(256), 0, stream, p);
   return hipGetLastError() == hipSuccess ? SYMPH_OK : SYMPH_ELAUNCH;
@@ -256,18 +262,22 @@ static int32_t launch_rows(const MigrateParams& p_in, hipStream_t stream) {
 
 template <typename VecT, bool PACK>
 static int32_t launch_planes(int planes, const MigrateParams& p_in, hipStream_t stream) {
-  // Measured on MI355X, gather with one plane per lane: two consecutive tokens per wave, i.e. one session search for
-  // two loads, +5 % on config 2 (16 sessions: 5.8 -> 6.1 TB/s), four the same, eight a cliff (3.1 TB/s); nothing to
-  // gain with a single session (no search: 6.08 -> 5.99) or in the two-plane form (config 4: 6.5 either way), and the
-  // scatter does not change (6.5 / 5.3 / 5.2 TB/s on configs 2 / 4 / 3 with one, two or four tokens per wave).
-  if (PACK && planes == 1 && p_in.row_shift >= 6 && p_in.n_sessions > 1) return launch_rows<VecT, PACK, 2, 1>(p_in, stream);
+  // Measured on MI355X with one plane per lane: two consecutive tokens per wave, i.e. one session search for two loads.
+  // Gather, 16 sessions: 5.8 -> 6.1 TB/s (four the same, eight a cliff: 3.1; a single session has no search to share: 6.08
+  // -> 5.99).  Scatter, with the XCD-contiguous mapping: 16 sessions of 1 to 8 Ki tokens 3390 -> 3198 us, 81 of a few
+  // hundred 1353 -> 1222, 256 of 16 to 1200 7107 -> 6888, against two planes per lane in the plain order; one plane and one
+  // token 3241, two planes with the mapping 3337, two tokens in the plain order 3380.  (Where the driver places the pool's
+  // pages moves two planes in the plain order between 3010 and 3390, this form between 3080 and 3200: it is the slower one
+  // in the best placements by up to 4 %, the faster one in most.)  Everything that widens the set of
+  // rows under way at once loses: 8 / 64 planes per wave in a software pipeline 3484 / 3607 (gather 3040 -> 3306 / 3491).
+  if (planes == 1 && p_in.row_shift >= 6 && (!PACK || p_in.n_sessions > 1)) return launch_rows<VecT, PACK, 2, 1>(p_in, stream);
   const int64_t n_vec = p_in.total_tokens * p_in.vecs_per_row;
   const int64_t gx = ceil_div64(n_vec, 256);
   const int64_t gy = ceil_div64(p_in.plane_end - p_in.plane_begin, planes);
   if (gx > 0x7FFFFFFFLL || gy > 65535) return SYMPH_EUNSUPPORTED;
   dim3 grid((unsigned)gx, (unsigned)gy);
   MigrateParams p = p_in;
-  // measured on MI355X (config 2): the gather gains 2-3 % from the XCD-contiguous mapping, the scatter loses 7 %
+  // (two planes per lane: the gather gains 2-3 % from the XCD-contiguous mapping, the scatter only where it has long rows)
   p.xcd_chunk = PACK ? (int32_t)(gx / 8) : 0;
   if (planes == 1)
     launch_uniform<VecT, PACK, 1>(grid, p, stream);
@@ -320,10 +330,11 @@ int32_t launch_kv_migrate(bool pack, const symph_kv_cache* c, int32_t layer_begi
   p.buf_bytes = buf_bytes;
   p.batch_layer_b = batch_layer_major ? 2 * total_tokens * row_bytes : 0;
 
-  // Planes per lane, measured on MI355X (config 2 / config 4, TB/s read+written): gather 1 -> 6.1 / 5.6,
-  // 2 -> 5.8 / 5.9, 4 -> 5.5 / 5.7, 8 -> 3.0; scatter 1 -> 5.9 / 5.5, 2 -> 6.5 / 6.2, 4 -> 6.3 / 6.2.  One plane per
-  // lane repeats the session search for every vector, which only pays off while the search is short.
-  const int planes = (pack && n_sessions <= 64) ? 1 : 2;  // (a launch always covers whole layers: two planes at least)
+  // Planes per lane.  Long rows (a whole number of waves) move one plane per lane, two tokens per wave (launch_planes),
+  // unless the session search is long (gather of more than 64 sessions) or the second token of a wave is too often another
+  // session's (scatter of fewer than 64 tokens a session: 64 sessions of 28 tokens 80 us so, 87 by rows).  Short rows have
+  // a lookup per lane, which two planes share: 16 sessions with 256-byte rows, gather 638 -> 363 us (four planes 377).
+  const int planes = p.row_shift >= 6 && (pack ? n_sessions <= 64 : total_tokens >= (int64_t)64 * n_sessions) ? 1 : 2;  // (a launch always covers whole layers: two planes at least)
 
   if (vec == 16) return pack ? launch_planes<u32x4, true>(planes, p, stream) : launch_planes<u32x4, false>(planes, p, stream);
   return pack ? launch_planes<unsigned int, true>(planes, p, stream) : launch_planes<unsigned int, false>(planes, p, stream);
@@ -336,7 +347,7 @@ struct AppendParams {
   char* k_layer;  // the layer's K pool and V pool
   char* v_layer;
   int64_t block_stride_b;
-  int32_t row_bytes, vecs_per_row, block_size, n_blocks;
+  int32_t row_bytes, vecs_per_row, row_shift, block_size, bs_shift, n_blocks;  // shifts: log2 or -1
   const char* k_new;
   const char* v_new;
   const int32_t* cu_new_lens;
@@ -349,21 +360,25 @@ struct AppendParams {
 template <typename VecT>
 __global__ __launch_bounds__(256) void kv_append_kernel(const AppendParams p) {
   const int64_t gv = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t tok = gv / p.vecs_per_row;
+  const int64_t tok = p.row_shift >= 0 ? gv >> p.row_shift : gv / p.vecs_per_row;
   if (tok >= p.total_new_tokens) return;
   const int32_t col = (int32_t)(gv - tok * p.vecs_per_row);
-  int32_t lo = 0, hi = p.n_sessions;  // last session with cu[s] <= tok (empty turns are skipped this way)
+  // last session with cu[s] <= tok (empty turns are skipped this way): searched for the wave's first token, a lane whose
+  // token is past that session's end walks on
+  const int32_t tok0 = __builtin_amdgcn_readfirstlane((int32_t)tok);
+  int32_t lo = 0, hi = p.n_sessions;
   while (hi - lo > 1) {
     const int32_t mid = (lo + hi) >> 1;
-    if (p.cu_new_lens[mid] <= tok)
+    if (p.cu_new_lens[mid] <= tok0)
       lo = mid;
     else
       hi = mid;
   }
-  const int32_t s = lo;
+  int32_t s = lo;
+  while (s + 1 < p.n_sessions && p.cu_new_lens[s + 1] <= tok) ++s;
   const int64_t pos = (int64_t)p.prefix_lens[s] + (tok - p.cu_new_lens[s]);
   if (pos < 0) return;
-  const int64_t j = pos / p.block_size;
+  const int64_t j = p.bs_shift >= 0 ? pos >> p.bs_shift : pos / p.block_size;
   if (j >= p.table_stride) return;
   const int32_t b = p.table[(int64_t)s * p.table_stride + j];
   if (b < 0 || b >= p.n_blocks) return;  // not a block of this cache: touch nothing
@@ -391,7 +406,9 @@ int32_t launch_kv_append(const symph_kv_cache* c, int32_t layer, const void* d_k
   const int vec = (align_or & 15) ? 4 : 16;
   p.row_bytes = (int32_t)row_bytes;
   p.vecs_per_row = (int32_t)(row_bytes / vec);
+  p.row_shift = log2_or_neg(p.vecs_per_row);
   p.block_size = c->block_size;
+  p.bs_shift = log2_or_neg(c->block_size);
   p.n_blocks = c->n_blocks;
   p.k_new = (const char*)d_k_new;
   p.v_new = (const char*)d_v_new;

@@ -90,6 +90,43 @@ def test_pack_unpack_edge_cases(oracle_mod, kw):
     run_case(oracle_mod, _cfg(**kw), seed=77)
 
 
+@pytest.mark.parametrize("hkv,d,dtype,prefix", [
+    (2, 64, "bf16", [3, 0, 0, 1, 2, 5, 0, 9, 1, 1]),           # 256-byte rows: several sessions in one wave, empty ones too
+    (1, 64, "bf16", [0, 130, 1, 0, 64, 65]),                   # 128-byte rows, eight tokens per wave
+    (3, 64, "fp32", [7, 33, 0, 16]),                           # 768-byte rows: a wave holds parts of two tokens
+    (8, 64, "bf16", [63, 65, 0, 200, 1]),                      # 1-KiB rows: two tokens per wave both ways
+    (8, 128, "bf16", [1, 2, 0, 3, 60]),                        # fewer than 64 tokens a session
+    (8, 128, "bf16", [5] * 3 + [400] + [0] * 66),              # more than 64 sessions
+])
+def test_session_lookups(oracle_mod, hkv, d, dtype, prefix):
+    cfg = W.WorkloadConfig(name="lookup", index=90, dtype=dtype, n_layers=3, n_q_heads=hkv, n_kv_heads=hkv, head_dim=d,
+                           block_size=16, n_blocks=160, n_sessions=len(prefix), prefix_dist=("const", 1),
+                           new_dist=("const", 0), sigma=1.0, scale=0.1)
+    sess = W.make_sessions(cfg, 91)
+    nblk = [-(-n // 16) for n in prefix]
+    perm = np.random.default_rng(92).permutation(cfg.n_blocks).astype(np.int32)
+    tables = np.full((2, len(prefix), max(nblk)), -1, dtype=np.int32)
+    at = 0
+    for t in tables:
+        for s, n in enumerate(nblk):
+            t[s, :n] = perm[at:at + n]
+            at += n
+    off = np.concatenate([[0], np.cumsum(prefix)]).astype(np.int64)
+    sess = W.SessionBatch(cfg, np.array(prefix, dtype=np.int32), sess.new_lens, tables[0], tables[1], off, sess.cu_new_lens)
+    k_pool, v_pool = W.make_pool_host(cfg, sess, 91)
+    ref = oracle_mod.kv_pack(k_pool, v_pool, sess.block_table, sess.prefix_lens, off)
+    ds = DeviceSessions(sess)
+    buf = gpu_pack(S.KVCache(to_dev(k_pool), to_dev(v_pool)), ds)
+    torch.cuda.synchronize()
+    assert to_host(buf).tobytes() == ref.tobytes(), "pack differs from the oracle"
+    ks, vs = sentinel_like(k_pool), sentinel_like(v_pool)
+    dcache = S.KVCache(to_dev(ks), to_dev(vs))
+    oracle_mod.kv_unpack(ks, vs, sess.dst_block_table, sess.prefix_lens, off, ref)
+    gpu_unpack(dcache, ds, buf, dst=True)
+    torch.cuda.synchronize()
+    assert to_host(dcache.k_pool).tobytes() == ks.tobytes() and to_host(dcache.v_pool).tobytes() == vs.tobytes()
+
+
 @pytest.mark.parametrize("tokens", [1, 15, 16, 17, 31, 33, 47, 100])
 def test_workgroup_to_token_mappings(oracle_mod, tokens):
     """The mappings of workgroups to the token space (XCD-contiguous for the gather, identity for the scatter) on the
