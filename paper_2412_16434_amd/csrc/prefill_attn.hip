@@ -989,7 +989,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
     char* const v_other = PAR ? V0 : V1;  // held V(j-1), free now: receives V(j+1)
     f32x16 (&s_cur)[2] = PAR ? s_odd : s_even;   // S(j)
     f32x16 (&s_nxt)[2] = PAR ? s_even : s_odd;   // receives S(j+1)
-    if (j + 1 < tile_end) {
+    {
       int keep[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) { keep[i] = ids[i]; ids[i] = ids_v[i]; }
@@ -1000,7 +1000,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
     if (j + 2 < tile_end) issue_tile(k_bytes, p.k_new, k_same, j + 2);
     if (wave_works) {
     // ---- block A
-    qk(k_other, s_nxt);                          // S(j+1)   (garbage, and discarded below, when j+1 == tile_end)
+    qk(k_other, s_nxt);                          // S(j+1)
     softmax_exp_half(s_cur[1], mb_cur, pb[1]);   // second half of P(j)
     float ps = row_sum(pb);
     __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);      // K fragments: six reads up front
@@ -1055,7 +1055,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    pb[0][0] = pb_first[0];   // (garbage, and never used, when there was no tile j+1)
+    pb[0][0] = pb_first[0];
     pb[0][1] = pb_first[1];
     asm volatile("" : "+v"(pb[0][0]), "+v"(pb[0][1]));   // computed here, not after the barrier
     }
@@ -1070,10 +1070,33 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
     fetch_ids(j + 3);   // index clamped to the table: harmless past the last tile
     iteration(j, par_c);
   };
-  for (int j = tile_begin; j < tile_end; j += 2) {
+  for (int j = tile_begin; j + 1 < tile_end; j += 2) {
     step(j, std::integral_constant<int, 0>{});
-    if (j + 1 < tile_end) step(j + 1, std::integral_constant<int, 1>{});
+    if (j + 2 < tile_end) step(j + 1, std::integral_constant<int, 1>{});
   }
+  // The last tile has no successor: the second half of its probabilities, then its second product, and nothing beside
+  // them.  (As one more turn of the loop it computed a first product, exponentials and loads that nobody used.)
+  if (wave_works) {
+    const bool odd = (tile_end - 1 - tile_begin) & 1;
+    if (odd) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) s_even[kb] = s_odd[kb];
+    }
+    const char* const v_last = odd ? V1 : V0;
+    softmax_exp_half(s_even[1], mb_cur, pb[1]);
+    float ps = row_sum(pb);
+    if (__any(!(ps <= kRefreshSum) || (m_run == -INFINITY && ps > 0.f))) refresh_reference(s_even, mb_cur, pb, ps);
+    l_run += ps;
+#pragma unroll
+    for (int g = 0; g < 16; ++g) {
+      const char* vp = v_last + v_off[g & 3] + (8 * (g >> 3) + 4 * ((g >> 2) & 1)) * kGroupBytes;
+      const s16x4 lo = lds_read_tr16(reinterpret_cast<const __bf16*>(vp));
+      const s16x4 hi = lds_read_tr16(reinterpret_cast<const __bf16*>(vp + kGroupBytes));
+      const bf16x8 v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      o_acc[g & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pb[g >> 3][(g >> 2) & 1], o_acc[g & 3], 0, 0, 0);
+    }
+  }
+  __syncthreads();  // the tile buffers are free
 
   // rows of this wave in (token, head) order, and which of them exist
   const int row_m = (n - hh * TW) * G + hh;
@@ -1083,7 +1106,7 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
   __bf16* const out_first = p.out + ((int64_t)(cu_s + t0 + wave * TW) * p.n_q_heads + kvh * G) * kD;
   if (it.pslot < 0) {
     const float l_tot = sum_across_halves(l_run);
-    if (wave_works)   // (every wave is past the last barrier of the loop: the tile buffers are free)
+    if (wave_works)
       store_out_rows_staged(out_stage, out_first, (int64_t)p.n_q_heads * kD, G, row_m, valid_bits, o_acc, 1.0f / l_tot, g2,
                             lane);
   } else if constexpr (DIRECT) {
