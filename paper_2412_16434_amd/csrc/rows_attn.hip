@@ -122,7 +122,7 @@ __global__ __launch_bounds__(64) void attn_row_kernel(const RowsParams p) {
 }
 
 // ---- the tiled kernel: one workgroup per (session, kv-head, tile of R query rows).  The rows of a kv-head, token by
-// token and the G heads of a token beside each other (any G), are cut into tiles of R = 32 (bf16) or 16 (fp32); the eight
+// token and the G heads of a token beside each other (any G), are cut into tiles of R = 32 (bf16) or 16 (fp32); the W
 // waves of a workgroup take the tile's key blocks of R keys in turn, each with a softmax of its own, and are combined
 // through LDS at the end.  No scheduling kernel, no workspace, one launch: these shapes are small models and odd group
 // sizes, whose calls are short, so what counts is how few trips to memory stand one behind the other.
@@ -132,16 +132,16 @@ __global__ __launch_bounds__(64) void attn_row_kernel(const RowsParams p) {
 // instruction throughout.
 //
 // Measured against one wave per row (attn_row_kernel below, 32-bit arithmetic on the vector unit, lanes over keys): six
-// sessions of 300 to 2000 tokens, 64-wide heads, 380 -> 22 us; one fp32 session of 256 tokens, 24.6 -> 11.6 us, which is the
-// call itself; three fp32 sessions of 8192, 775 -> 221.  Four waves per tile instead of eight: 24, 13 and 371; registers for
-// two workgroups per compute unit (64-wide heads; spills): 30 us.  The error against 64 bits is the same in bf16 and lower in
-// fp32 (2.9e-7 for 4.7e-7 at 128 x 8000 keys).
+// sessions of 300 to 2000 tokens, 64-wide heads, 380 -> 18 us; one fp32 session of 256 tokens, 24.6 -> 9.9 us, which is the
+// call itself; three fp32 sessions of 8192, 775 -> 193; 16 of 2000 to 4000 with 64-wide heads, 12 805 -> 229.  The error
+// against 64 bits is the same in bf16 and lower in fp32 (2.9e-7 for 4.7e-7 at 128 x 8000 keys).  A block's 24 MFMAs and the
+// exponentials are matched by as many vector instructions again for the split and the addresses, so the vector unit bounds
+// a full chip and the chain load -> product -> softmax -> product a small call.
 //
 // K goes from memory straight into operand registers: a row's D values are the operand's contraction index, and any order
 // of it will do as long as Q has the same.  V is needed transposed: in bf16 through LDS (a tile of the wave's own, rows
 // 64 bytes apart in banks so that the transposing read has no conflicts), in fp32 not at all (its operand has one value
 // per lane).  The next block's rows are asked for before the present one is used, the block ids one block earlier.
-constexpr int kRowsWaves = 8;
 static __device__ __attribute__((aligned(256))) const unsigned kAbsentRow[128] = {};  // a head's row of zeros
 
 template <typename T>
@@ -171,11 +171,11 @@ __device__ __forceinline__ int wave_last(int n, F holds) {
   return lo;
 }
 
-// The eight waves' results of a tile of R rows, DC columns at a time through LDS: out = sum_w f_w O_w / sum_w f_w l_w with
+// The W waves' results of a tile of R rows, DC columns at a time through LDS: out = sum_w f_w O_w / sum_w f_w l_w with
 // f_w = e^(m_w - max_w m_w) (base 2 or e, as the caller's references are).  put(round, f, mine) writes the lane's part of the
 // wave's columns, scaled.  A result that is not finite (an infinity or a NaN among the inputs, which the matrix product
 // spreads over rows that must not see its key) is worked out again row by row.
-template <typename T, int D, int R, int DC, typename Put, typename Exp>
+template <typename T, int D, int R, int DC, int W, typename Put, typename Exp>
 __device__ __forceinline__ void combine_rows(const RowsParams& p, char* lds, const float (*wave_m)[R],
                                              const float (*wave_l)[R], int& redo, Put put, Exp exp_of, int s, int cu_s,
                                              int kvh, int G, int64_t row0, int n_rows) {
@@ -185,17 +185,17 @@ __device__ __forceinline__ void combine_rows(const RowsParams& p, char* lds, con
   const int n = lane & (R - 1);
   float M = -INFINITY;
 #pragma unroll
-  for (int w = 0; w < kRowsWaves; ++w) M = fmaxf(M, wave_m[w][n]);
+  for (int w = 0; w < W; ++w) M = fmaxf(M, wave_m[w][n]);
   const float mine_m = wave_m[wave][n];
   const float f = mine_m == -INFINITY ? 0.f : exp_of(mine_m - M);
   // thread t adds up V columns from c0 on of row t * V / DC
-  constexpr int V = R * DC / (64 * kRowsWaves);
+  constexpr int V = R * DC / (64 * W);
   const int r = tid * V / DC, c0 = tid * V % DC;
   float Mr = -INFINITY, L = 0.f;
 #pragma unroll
-  for (int w = 0; w < kRowsWaves; ++w) Mr = fmaxf(Mr, wave_m[w][r]);
+  for (int w = 0; w < W; ++w) Mr = fmaxf(Mr, wave_m[w][r]);
 #pragma unroll
-  for (int w = 0; w < kRowsWaves; ++w)
+  for (int w = 0; w < W; ++w)
     L += wave_m[w][r] == -INFINITY ? 0.f : wave_l[w][r] * exp_of(wave_m[w][r] - Mr);
   const float inv = 1.0f / L;
   const int64_t row = row0 + r;
@@ -211,7 +211,7 @@ __device__ __forceinline__ void combine_rows(const RowsParams& p, char* lds, con
 #pragma unroll
     for (int v = 0; v < V; ++v) sum[v] = 0.f;
 #pragma unroll
-    for (int w = 0; w < kRowsWaves; ++w)
+    for (int w = 0; w < W; ++w)
 #pragma unroll
       for (int v = 0; v < V; ++v) sum[v] += all[(w * R + r) * kStride + c0 + v];
     if (r < n_rows) {
@@ -228,23 +228,23 @@ __device__ __forceinline__ void combine_rows(const RowsParams& p, char* lds, con
   if (__any(bad)) redo = 1;
   __syncthreads();
   if (!redo) return;
-  for (int i = wave; i < n_rows; i += kRowsWaves) {
+  for (int i = wave; i < n_rows; i += W) {
     const int64_t again = row0 + i;
     const int t = (int)(again / G);
     row_by_lanes<T, D, 32>(p, s, cu_s + t, kvh * G + (int)(again - (int64_t)t * G), all + wave * D);
   }
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(64 * kRowsWaves, 2) void attn_rows_kernel(const RowsParams p) {
+template <typename T, int D, int W>
+__global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p) {
   constexpr bool kBf16 = sizeof(T) == 2;
   constexpr int R = RowsTile<T>::R;
   constexpr int kVRow = D * 2 + 64;                                  // bytes between V rows in LDS (bf16)
-  constexpr int kVBytes = kBf16 ? kRowsWaves * 32 * kVRow : 0;
+  constexpr int kVBytes = kBf16 ? W * 32 * kVRow : 0;
   constexpr int DC = kBf16 ? 32 : D;                                 // columns combined at a time
-  constexpr int kCombBytes = kRowsWaves * R * (DC + 4) * 4;
+  constexpr int kCombBytes = W * R * (DC + 4) * 4;
   __shared__ __attribute__((aligned(16))) char lds[kVBytes > kCombBytes ? kVBytes : kCombBytes];
-  __shared__ float wave_m[kRowsWaves][R], wave_l[kRowsWaves][R];
+  __shared__ float wave_m[W][R], wave_l[W][R];
   __shared__ int redo;
 
   const int Hkv = p.n_kv_heads;
@@ -291,6 +291,18 @@ __global__ __launch_bounds__(64 * kRowsWaves, 2) void attn_rows_kernel(const Row
     return key < total_keys ? (const T*)fresh + ((int64_t)(cu_s + key - P) * Hkv + kvh) * D : (const T*)kAbsentRow;
   };
 
+  // A block of keys that lies in the prefix, its 16-key groups in blocks of the cache each (block sizes that are powers of
+  // two >= 16): a group's rows start at a scalar address and a lane adds a constant.  (The general form, row_of per lane, is
+  // half of the vector instructions of an iteration.)
+  const bool grouped = p.bs_shift >= 4;
+  auto group_id = [&](int id, int g) { return __builtin_amdgcn_readlane(id, 16 * g); };
+  auto in_cache = [&](int id) { return (unsigned)id < (unsigned)p.n_blocks; };
+  auto group_at = [&](const void* pool, int key, int id) {  // row of `key`, a multiple of 16, of this kv-head
+    return (const char*)((const T*)pool + (int64_t)id * p.block_stride +
+                         ((int64_t)(key & (p.block_size - 1)) * Hkv + kvh) * D);
+  };
+  const int row_bytes = Hkv * D * (int)sizeof(T);  // between the rows of consecutive keys
+
   if constexpr (kBf16) {
     constexpr int NS = D / 16;            // contraction steps of the first product
     constexpr int NT = D / 32;            // 32-column tiles of the output
@@ -303,7 +315,23 @@ __global__ __launch_bounds__(64 * kRowsWaves, 2) void attn_rows_kernel(const Row
     const int vlane_row = lane / LPR, vlane_col = (lane % LPR) * 16;
     bf16x8 kr[NS];
     u32x4 vr[NV];
+    const int k_off = (krow & 15) * row_bytes + 16 * kg;
+    const int v_off_mem = vlane_row * row_bytes + vlane_col;
     auto load_block = [&](int blk, int id) {
+      const int id0 = group_id(id, 0), id1 = group_id(id, 1);
+      if (grouped && (blk + 1) * 32 <= P && in_cache(id0) && in_cache(id1)) {
+        const char* const k0 = group_at(p.k_layer, blk * 32, id0);
+        const char* const k1 = group_at(p.k_layer, blk * 32 + 16, id1);
+        const char* const k_row = (krow < 16 ? k0 : k1) + k_off;
+#pragma unroll
+        for (int st = 0; st < NS; ++st) kr[st] = *reinterpret_cast<const bf16x8*>(k_row + 32 * st);
+        const char* const v0 = group_at(p.v_layer, blk * 32, id0);
+        const char* const v1 = group_at(p.v_layer, blk * 32 + 16, id1);
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+          vr[i] = *reinterpret_cast<const u32x4*>((i < NV / 2 ? v0 : v1) + (i % (NV / 2)) * RPI * row_bytes + v_off_mem);
+        return;
+      }
       const T* const k_row = row_of(p.k_layer, p.k_new, blk * 32 + krow, __shfl(id, krow)) + 8 * kg;
 #pragma unroll
       for (int st = 0; st < NS; ++st) kr[st] = *reinterpret_cast<const bf16x8*>(k_row + 16 * st);
@@ -325,24 +353,18 @@ __global__ __launch_bounds__(64 * kRowsWaves, 2) void attn_rows_kernel(const Row
     float m = -INFINITY, l = 0.f;  // in log2 units
     int id_next = fetch_id(wave);
     if (wave < n_blocks_k) load_block(wave, id_next);
-    id_next = fetch_id(wave + kRowsWaves);
-    for (int blk = wave; blk < n_blocks_k; blk += kRowsWaves) {
-      f32x16 sc[2];
+    id_next = fetch_id(wave + W);
+    for (int blk = wave; blk < n_blocks_k; blk += W) {
+      f32x16 x;
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+      for (int e = 0; e < 16; ++e) x[e] = 0.f;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) sc[h][e] = 0.f;
-#pragma unroll
-      for (int st = 0; st < NS; ++st)  // (two chains: a product does not wait for the one before it)
-        sc[st & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[st], q[st], sc[st & 1], 0, 0, 0);
+      for (int st = 0; st < NS; ++st) x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[st], q[st], x, 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < NV; ++i)
         *reinterpret_cast<u32x4*>(v_lds + (i * RPI + vlane_row) * kVRow + vlane_col) = vr[i];
-      if (blk + kRowsWaves < n_blocks_k) load_block(blk + kRowsWaves, id_next);
-      id_next = fetch_id(blk + 2 * kRowsWaves);
-      float x[16];
-#pragma unroll
-      for (int e = 0; e < 16; ++e) x[e] = sc[0][e] + sc[1][e];
+      if (blk + W < n_blocks_k) load_block(blk + W, id_next);
+      id_next = fetch_id(blk + 2 * W);
       if (blk * 32 + 31 > P) {
 #pragma unroll
         for (int e = 0; e < 16; ++e)
@@ -394,7 +416,7 @@ __global__ __launch_bounds__(64 * kRowsWaves, 2) void attn_rows_kernel(const Row
       wave_l[wave][n] = l_row;
     }
     __syncthreads();  // (also: no wave reads its V tile any more, the buffer is free)
-    combine_rows<T, D, R, DC>(p, lds, wave_m, wave_l, redo, [&](int round, float f, float* mine) {
+    combine_rows<T, D, R, DC, W>(p, lds, wave_m, wave_l, redo, [&](int round, float f, float* mine) {
       // (o[round] by a chain of selects: a register array cannot be indexed)
 #pragma unroll
       for (int dt = 0; dt < NT; ++dt)
@@ -413,6 +435,19 @@ __global__ __launch_bounds__(64 * kRowsWaves, 2) void attn_rows_kernel(const Row
     for (int j = 0; j < NS; ++j) q[j] = *reinterpret_cast<const f32x4*>(qp + 16 * j + 4 * kg);
     f32x4 kr[NS], vr[4][NH];
     auto load_block = [&](int blk, int id) {
+      const int id0 = group_id(id, 0);
+      if (grouped && (blk + 1) * 16 <= P && in_cache(id0)) {
+        const char* const k_row = group_at(p.k_layer, blk * 16, id0) + n * row_bytes + 16 * kg;
+#pragma unroll
+        for (int j = 0; j < NS; ++j) kr[j] = *reinterpret_cast<const f32x4*>(k_row + 64 * j);
+        const char* const v_row = group_at(p.v_layer, blk * 16, id0) + 4 * kg * row_bytes + 16 * n;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int h = 0; h < NH; ++h)
+            vr[e][h] = *reinterpret_cast<const f32x4*>(v_row + e * row_bytes + 256 * h);
+        return;
+      }
       const T* const k_row = row_of(p.k_layer, p.k_new, blk * 16 + n, id) + 4 * kg;
 #pragma unroll
       for (int j = 0; j < NS; ++j) kr[j] = *reinterpret_cast<const f32x4*>(k_row + 16 * j);
@@ -447,8 +482,8 @@ __global__ __launch_bounds__(64 * kRowsWaves, 2) void attn_rows_kernel(const Row
     int run = 0;
     int id_next = fetch_id(wave);
     if (wave < n_blocks_k) load_block(wave, id_next);
-    id_next = fetch_id(wave + kRowsWaves);
-    for (int blk = wave; blk < n_blocks_k; blk += kRowsWaves) {
+    id_next = fetch_id(wave + W);
+    for (int blk = wave; blk < n_blocks_k; blk += W) {
       f32x4 sc[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) sc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -461,8 +496,8 @@ __global__ __launch_bounds__(64 * kRowsWaves, 2) void attn_rows_kernel(const Row
       for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int h = 0; h < NH; ++h) v[e][h] = vr[e][h];
-      if (blk + kRowsWaves < n_blocks_k) load_block(blk + kRowsWaves, id_next);
-      id_next = fetch_id(blk + 2 * kRowsWaves);
+      if (blk + W < n_blocks_k) load_block(blk + W, id_next);
+      id_next = fetch_id(blk + 2 * W);
       float x[4];  // key 4 * kg + e
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -510,7 +545,7 @@ __global__ __launch_bounds__(64 * kRowsWaves, 2) void attn_rows_kernel(const Row
       wave_l[wave][n] = l;
     }
     __syncthreads();
-    combine_rows<T, D, R, DC>(p, lds, wave_m, wave_l, redo, [&](int, float f, float* mine) {
+    combine_rows<T, D, R, DC, W>(p, lds, wave_m, wave_l, redo, [&](int, float f, float* mine) {
 #pragma unroll
       for (int h = 0; h < NH; ++h)
 #pragma unroll
@@ -524,6 +559,8 @@ __global__ __launch_bounds__(64 * kRowsWaves, 2) void attn_rows_kernel(const Row
 // ------------------------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------------------------
+constexpr int64_t kComputeUnits = 256;
+
 template <typename T, int D>
 static int32_t launch_rows(const AttnArgs& a, hipStream_t stream) {
   RowsParams p;
@@ -554,9 +591,16 @@ static int32_t launch_rows(const AttnArgs& a, hipStream_t stream) {
   const int64_t groups = slots * a.n_kv_heads;
   // The tiled kernel loads 16 bytes at a time.  (A row of a head is a multiple of that, so the bases and the block stride
   // decide.)
-  if ((address_bits & 15) == 0 && groups <= 0x7FFFFFFFLL)
-    hipLaunchKernelGGL((attn_rows_kernel<T, D>), dim3((unsigned)groups), dim3(64 * kRowsWaves), 0, stream, p);
-  else
+  // Eight waves a tile give the shortest chain of key blocks to a call that does not fill the chip.  With more tiles than
+  // compute units, four waves each (two or three workgroups then share a compute unit) leave a last round less empty:
+  // eight / four waves 28 / 24 us at 504 tiles, 129 / 71 and 305 / 215 at 3100 to 3600; 35 / 49 and 193 / 259 at 112 and
+  // 30 tiles.  (Two waves with over 512 tiles: within 6 % either way.)
+  if ((address_bits & 15) == 0 && groups <= 0x7FFFFFFFLL) {
+    if (groups <= kComputeUnits)
+      hipLaunchKernelGGL((attn_rows_kernel<T, D, 8>), dim3((unsigned)groups), dim3(512), 0, stream, p);
+    else
+      hipLaunchKernelGGL((attn_rows_kernel<T, D, 4>), dim3((unsigned)groups), dim3(256), 0, stream, p);
+  } else
     hipLaunchKernelGGL((attn_row_kernel<T, D>), dim3((unsigned)rows), dim3(64), 0, stream, p);
   return hipGetLastError() == hipSuccess ? SYMPH_OK : SYMPH_ELAUNCH;
 }

@@ -205,6 +205,9 @@ def test_direct_calls(oracle_mod, hkv, group, bs, prefix, new):
     ("fp32", 64, 2, 3, 16, [0, 15, 16, 17, 128], [5, 6, 1, 0, 11]),
     ("fp32", 128, 4, 1, 16, [127, 1100], [16, 17]),                          # more than eight blocks per wave: sums in runs
     ("bf16", 64, 2, 2, 16, [20] * 70, [1, 0] * 35),                          # more sessions than lanes
+    ("bf16", 64, 8, 4, 16, [70] * 40, [3] * 40),                             # more tiles than compute units: four waves each
+    ("fp32", 128, 8, 2, 32, [35, 64, 0] * 12, [9, 1, 4] * 12),
+    ("bf16", 128, 8, 3, 16, [33] * 40, [1, 11] * 20),
 ])
 def test_shapes_without_a_work_list(oracle_mod, dtype, d, hkv, group, bs, prefix, new):
     cfg = _cfg(dtype=dtype, head_dim=d, n_sessions=len(new), n_kv_heads=hkv, n_q_heads=hkv * group, block_size=bs,
