@@ -43,10 +43,9 @@ struct WorkItem {   // 96 bytes
                                   // workgroup's first K,V loads wait for this item only, not for a table read as well
   int32_t pad[5];
 };
-struct MergeItem {  // 16 bytes: one per unit of a direct call; one per key range of the decode kernel, for the unit that
-                    // starts in it and leaves it
-  int32_t row0, n_unit, pslot0, n_chunks;  // its first row of q / out and its tokens; slot (2 * range + 0 / 1) of its
-                                           // first piece; n_chunks 0: no such unit
+struct MergeItem {  // 16 bytes, one per unit of a direct call or of the decode kernel
+  int32_t row0, n_unit, pslot0, n_chunks;  // its first row of q / out and its tokens; the slot of its first piece (decode:
+                                           // 2 * range + 0 / 1); n_chunks 0: nothing to combine
 };
 // Header of the workspace (ints): counts and flags written by the scheduler (by the attention kernel itself where none
 // runs).
@@ -466,9 +465,9 @@ struct MfmaParams {
   int32_t direct_c_min, direct_slots, units_bound;
   MergeItem* unit_recs;
   // attn_decode_kernel: new tokens per unit (the call's max_new_len), the rows of q / out, its ranges, one record per
-  // range, and the pieces of units that several ranges share
-  int32_t dec_m, total_new_tokens, dec_ranges;
-  MergeItem* dec_merges;    // [key ranges]
+  // unit, and the pieces of units that several ranges share
+  int32_t dec_m, total_new_tokens, dec_ranges, dec_records;
+  MergeItem* dec_merges;    // [dec_records]
   float* dec_partials;      // [2 * key ranges][n_kv_heads][dec_slot_floats]
   int32_t dec_slot_floats;  // room for the packed piece of a unit (whole lines)
 };
@@ -1306,7 +1305,7 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
 
   // Every workgroup works its range out from the sessions' lengths by itself: one trip to memory and a scan over the
   // workgroup.  (A scheduling kernel in front, whose result every workgroup then read, was two more trips, a launch and
-  // the gap behind it: 6 us of a decode step.)  Thread t adds up sessions t * c .. t * c + c - 1.
+  // the gap behind it: 6 us of a decode step.)
   const int m = p.dec_m;
   auto span_of = [&](int s, int& cu_s, int& N, int& P) {  // rows past total_new_tokens do not exist (flagged below)
     cu_s = p.cu_new_lens[s];
@@ -1319,68 +1318,106 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
     for (int t0 = 0; t0 < N; t0 += m) n += tiles_to(P, min(N, t0 + m));
     return n;
   };
-  __shared__ int scan_sums[HW];
-  __shared__ int start_of[6];  // where the range begins: session, token, the unit's first tile, its session's N, P, cu
-  const int c = (p.n_sessions + 64 * HW - 1) / (64 * HW);
-  int mine = 0;
-  for (int i = 0; i < c; ++i) {
-    const int s = tid * c + i;
-    if (s >= p.n_sessions) break;
-    int cu_s, N, P;
-    span_of(s, cu_s, N, P);
-    mine += session_tiles(N, P);
-  }
-  int incl = wave_inclusive_scan(mine);
-  if ((tid & 63) == 63) scan_sums[wave] = incl;
-  __syncthreads();
-  int total = 0;
+  __shared__ int scan_sums[HW][2];
+  __shared__ int start_of[7];  // where the range begins: session, token, the unit's first tile, its session's N, P, cu, unit
+  int total, per_wg, range_begin, range_end;
+  auto take_range = [&]() {
+    per_wg = max((total + p.dec_ranges - 1) / p.dec_ranges, kDecMinTiles);
+    range_begin = wg * per_wg;
+    range_end = min(total, range_begin + per_wg);
+  };
+  // Units are numbered in session order.  The range that has a unit's first tile writes its record, block 0 those of the
+  // numbers past the last unit.  (More units than records would be lengths that break the caller's contract.)
+  int s, t0, unit, unit_begin, N, P, cu, n_units;
+  if (p.n_sessions <= 64) {
+    // lane s: session s; every wave does this by itself
+    const int lane_s = tid & 63;
+    int my_cu = 0, my_N = 0, my_P = 0;
+    if (lane_s < p.n_sessions) span_of(lane_s, my_cu, my_N, my_P);
+    const int mine = session_tiles(my_N, my_P), my_units = (my_N + m - 1) / m;
+    const int incl = wave_inclusive_scan(mine), units = wave_inclusive_scan(my_units);
+    total = __builtin_amdgcn_readlane(incl, 63);
+    n_units = __builtin_amdgcn_readlane(units, 63);
+    take_range();
+    const int owner = __builtin_ctzll(__ballot(range_begin < incl) | (1ull << 63));
+    s = owner;
+    N = __builtin_amdgcn_readlane(my_N, owner);
+    P = __builtin_amdgcn_readlane(my_P, owner);
+    cu = __builtin_amdgcn_readlane(my_cu, owner);
+    unit_begin = __builtin_amdgcn_readlane(incl, owner) - __builtin_amdgcn_readlane(mine, owner);
+    unit = __builtin_amdgcn_readlane(units, owner) - __builtin_amdgcn_readlane(my_units, owner);
+    t0 = 0;
+    while (t0 + m < N && unit_begin + tiles_to(P, t0 + m) <= range_begin) {
+      unit_begin += tiles_to(P, t0 + m);
+      t0 += m;
+      ++unit;
+    }
+  } else {
+    // thread t: sessions t * c .. t * c + c - 1
+    const int c = (p.n_sessions + 64 * HW - 1) / (64 * HW);
+    int mine = 0, my_units = 0;
+    for (int i = tid * c; i < min(tid * c + c, p.n_sessions); ++i) {
+      int cu_i, N_i, P_i;
+      span_of(i, cu_i, N_i, P_i);
+      mine += session_tiles(N_i, P_i);
+      my_units += (N_i + m - 1) / m;
+    }
+    int incl = wave_inclusive_scan(mine), units = wave_inclusive_scan(my_units);
+    if ((tid & 63) == 63) {
+      scan_sums[wave][0] = incl;
+      scan_sums[wave][1] = units;
+    }
+    __syncthreads();
+    total = n_units = 0;
 #pragma unroll
-  for (int w = 0; w < HW; ++w) {
-    const int x = scan_sums[w];
-    if (w < wave) incl += x;
-    total += x;
-  }
-  const int per_wg = max((total + p.dec_ranges - 1) / p.dec_ranges, kDecMinTiles);
-  const int range_begin = wg * per_wg;
-  const int range_end = min(total, range_begin + per_wg);
-  MergeItem rec{0, 0, 0, 0};
-  if (blockIdx.x == 0 && tid < kAttnHdrInts) {
-    const bool dropped = p.cu_new_lens[p.n_sessions] > p.total_new_tokens;
-    p.hdr[tid] = tid == kHdrDecTiles ? total : (tid == kHdrFlags && dropped ? 2 : 0);
-  }
-  if (range_begin >= range_end) {
-    if (kvh == 0 && (tid & 63) == 0) p.dec_merges[wg] = rec;
-    return;
-  }
-  if (incl - mine <= range_begin && range_begin < incl) {  // this thread's sessions hold the range's first tile
-    int at = incl - mine;
-    for (int s = tid * c; s < p.n_sessions; ++s) {  // (ends in this thread's sessions: their tiles reach past range_begin)
-      int cu_s, N, P;
-      span_of(s, cu_s, N, P);
-      int t0 = 0;
-      for (; t0 < N; t0 += m) {
-        const int nt = tiles_to(P, min(N, t0 + m));
-        if (at + nt > range_begin) break;
-        at += nt;
+    for (int w = 0; w < HW; ++w) {
+      const int x = scan_sums[w][0], y = scan_sums[w][1];
+      if (w < wave) {
+        incl += x;
+        units += y;
       }
-      if (t0 < N) {
-        start_of[0] = s;
-        start_of[1] = t0;
-        start_of[2] = at;
-        start_of[3] = N;
-        start_of[4] = P;
-        start_of[5] = cu_s;
-        break;
+      total += x;
+      n_units += y;
+    }
+    take_range();
+    if (incl - mine <= range_begin && range_begin < incl) {  // this thread's sessions hold the range's first tile
+      int at = incl - mine, u = units - my_units;
+      for (int i = tid * c; i < p.n_sessions; ++i) {  // (ends in this thread's sessions: their tiles reach past range_begin)
+        int cu_i, N_i, P_i;
+        span_of(i, cu_i, N_i, P_i);
+        int t = 0;
+        for (; t < N_i; t += m, ++u) {
+          const int nt = tiles_to(P_i, min(N_i, t + m));
+          if (at + nt > range_begin) break;
+          at += nt;
+        }
+        if (t < N_i) {
+          start_of[0] = i;
+          start_of[1] = t;
+          start_of[2] = at;
+          start_of[3] = N_i;
+          start_of[4] = P_i;
+          start_of[5] = cu_i;
+          start_of[6] = u;
+          break;
+        }
       }
     }
+    __syncthreads();
+    s = __builtin_amdgcn_readfirstlane(start_of[0]);
+    t0 = __builtin_amdgcn_readfirstlane(start_of[1]);
+    unit_begin = __builtin_amdgcn_readfirstlane(start_of[2]);
+    N = __builtin_amdgcn_readfirstlane(start_of[3]);
+    P = __builtin_amdgcn_readfirstlane(start_of[4]);
+    cu = __builtin_amdgcn_readfirstlane(start_of[5]);
+    unit = __builtin_amdgcn_readfirstlane(start_of[6]);
   }
-  __syncthreads();
-  int s = __builtin_amdgcn_readfirstlane(start_of[0]);
-  int t0 = __builtin_amdgcn_readfirstlane(start_of[1]);
-  int unit_begin = __builtin_amdgcn_readfirstlane(start_of[2]);
-  int N = __builtin_amdgcn_readfirstlane(start_of[3]);
-  int P = __builtin_amdgcn_readfirstlane(start_of[4]);
-  int cu = __builtin_amdgcn_readfirstlane(start_of[5]);
+  if (blockIdx.x == 0) {
+    const bool dropped = p.cu_new_lens[p.n_sessions] > p.total_new_tokens;
+    if (tid < kAttnHdrInts) p.hdr[tid] = tid == kHdrDecTiles ? total : (tid == kHdrFlags && dropped ? 2 : 0);
+    for (int i = n_units + tid; i < p.dec_records; i += 64 * HW) p.dec_merges[i] = MergeItem{0, 0, 0, 0};
+  }
+  if (range_begin >= range_end) return;
   for (int pos = range_begin; pos < range_end;) {
   const int cu_s = cu + t0;                                    // the unit's first row
   const int n_end = min(N, t0 + m);                            // its tokens: t0 .. n_end - 1
@@ -1616,15 +1653,16 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
 
   const float l_row = sum_across_halves(l_run);
   if (whole) {
+    if (kvh == 0 && lane == 0 && unit < p.dec_records) p.dec_merges[unit] = MergeItem{0, 0, 0, 0};
     if (q_valid)
       store_out_row(p.out + ((int64_t)(cu_s + tt) * p.n_q_heads + head) * kD, o_acc, 1.0f / l_row, g2);
   } else {
     // Two slots per range: 2 * wg for a segment that starts where the range starts (a unit continued from the range
     // before), 2 * wg + 1 for one that starts inside it.  The pieces of a unit are then its first one and, for every
-    // further range it reaches into, that range's even slot; the range that has the first piece (at most one unit starts
-    // in a range and leaves it) names it in its record.
+    // further range it reaches into, that range's even slot.
     const int pslot = 2 * wg + (at_range_start ? 0 : 1);
-    if (u_begin == 0) rec = MergeItem{cu_s, n_unit, pslot, (unit_end - 1) / per_wg - wg + 1};
+    if (u_begin == 0 && kvh == 0 && lane == 0 && unit < p.dec_records)
+      p.dec_merges[unit] = MergeItem{cu_s, n_unit, pslot, (unit_end - 1) / per_wg - wg + 1};
     // The piece goes through the wave's LDS buffers into the packed layout, so that every store instruction writes
     // whole lines (the wave's own reads of the buffers are done: it has used the last tile).
     const int rows = G * n_unit;
@@ -1653,6 +1691,7 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
     __builtin_amdgcn_wave_barrier();
   }
   unit_begin = unit_end;
+  ++unit;
   t0 += m;
   if (t0 >= N && pos < range_end) {  // the next session with new tokens (there is one: tiles are left)
     t0 = 0;
@@ -1662,26 +1701,28 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
     } while (N == 0);
   }
   }
-  if (kvh == 0 && (tid & 63) == 0) p.dec_merges[wg] = rec;
 }
 
 // Combine the pieces of a unit that the decode kernel cut at the boundaries of its ranges:
 // out = sum_c w_c O_c / sum_c w_c l_c with w_c = 2^(m_c - max_c m_c), m_c being the piece's softmax reference in log2
 // units (-inf: the piece saw no key of the row).  The first piece is in slot pslot0, piece c >= 1 in the even slot of
 // the c-th range after the one that wrote pslot0.
-// One workgroup per (range, kv-head), eight rows at a time.  Wave w takes pieces w, w + 4, ..: a step that decodes a few
+// One workgroup per (record, kv-head), eight rows at a time.  Wave w takes pieces w, w + 4, ..: a step that decodes a few
 // long sessions cuts them into tens of pieces each, and a thread that reads them one after the other waits for memory
 // every time (one session of 1777 tokens in 56 pieces: 50 us; this way 8 us, and 5 us for its 28 pieces of two tiles).
+// Records are per unit, not per key range, so that the grid follows the batch: 8 instead of 2048 workgroups for one session
+// (14.9 -> 14.4 us with the lengths added up inside a wave for up to 64 sessions, without a barrier).
 constexpr int kMergeRows = 8;
 template <int G>
 __global__ __launch_bounds__(256) void attn_decode_merge_kernel(const MfmaParams p) {
   __shared__ float part_o[4][kMergeRows * 128];
   __shared__ float part_m[4][kMergeRows], part_l[4][kMergeRows];
   const int Hkv = p.n_kv_heads;
-  const int range = blockIdx.x / Hkv;
-  const MergeItem mg = p.dec_merges[range];
+  const int record = blockIdx.x / Hkv;
+  const MergeItem mg = p.dec_merges[record];
   if (mg.n_chunks == 0) return;
-  const int kvh = blockIdx.x - range * Hkv;
+  const int kvh = blockIdx.x - record * Hkv;
+  const int range = mg.pslot0 >> 1;
   const int n_unit = mg.n_unit;
   const int rows = G * n_unit;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1791,8 +1832,8 @@ static AttnTuning resolve_tuning(const symph_attn_tuning* t) {
 
 struct MfmaPlan {
   int32_t bmt, target, target_slots, c_min, coarse, units_bound, items_bound, merges_bound, pslots_bound;
-  // decode kernel: whether this call runs it (alone), its key ranges (a record and, per kv-head, two slots each)
-  int32_t dec_mode, dec_wgs, dec_slot_floats;
+  // decode kernel: whether this call runs it (alone), its key ranges (two slots per kv-head each), its units' records
+  int32_t dec_mode, dec_wgs, dec_records, dec_slot_floats;
   int32_t direct;  // no scheduling kernel: pslots_bound pieces at most, one record per unit
   int64_t off_items, off_dec_merges, off_merge_cnt, off_partials, off_dec_partials, total_bytes;
 };
@@ -1806,7 +1847,7 @@ static void lay_out(MfmaPlan& pl, int32_t n_kv_heads) {
   pl.merges_bound = pl.pslots_bound / 2;              // a split unit has at least two chunks
   pl.off_items = align256(kAttnHdrInts * 4);
   pl.off_dec_merges = align256(pl.off_items + (pl.direct ? 0 : (int64_t)pl.items_bound * sizeof(WorkItem)));
-  pl.off_merge_cnt = align256(pl.off_dec_merges + (int64_t)(pl.direct ? pl.units_bound : pl.dec_wgs) * sizeof(MergeItem));
+  pl.off_merge_cnt = align256(pl.off_dec_merges + (int64_t)(pl.direct ? pl.units_bound : pl.dec_records) * sizeof(MergeItem));
   pl.off_partials = align256(pl.off_merge_cnt + (int64_t)pl.merges_bound * n_kv_heads * 4);
   pl.off_dec_partials = pl.off_partials + (int64_t)pl.pslots_bound * n_kv_heads * kPartialFloats * 4;
   pl.total_bytes = pl.off_dec_partials + (int64_t)2 * pl.dec_wgs * n_kv_heads * pl.dec_slot_floats * 4;
@@ -1837,6 +1878,12 @@ static bool make_plan(MfmaPlan& pl, int32_t n_sessions, int32_t n_q_heads, int32
   pl.dec_slot_floats = pl.dec_mode ? ((G * max_new_len * 130 + 31) & ~31) : 0;
   // ranges of the decode kernel: one wave per (range, kv-head), as many waves as decode_wgs workgroups of four would have
   pl.dec_wgs = pl.dec_mode ? (4 * tu.decode_wgs / n_kv_heads < 1 ? 1 : 4 * tu.decode_wgs / n_kv_heads) : 0;
+  // units of at most max_new_len tokens: one per token, or one per session and full max_new_len tokens
+  pl.dec_records = 0;
+  if (pl.dec_mode) {
+    const int64_t units = (int64_t)total_new_tokens / max_new_len + n_sessions;
+    pl.dec_records = (int32_t)(units < total_new_tokens ? units : total_new_tokens);
+  }
   // Chunks of split units: a unit is split when it has more than C tiles, C >= total tiles * kv-heads / target, so
   // there are at most target / kv-heads split units and their chunks number at most twice that.
   pl.pslots_bound = 2 * (pl.target / n_kv_heads + 1);
@@ -1957,6 +2004,7 @@ static int32_t launch_mfma(const AttnArgs& a, hipStream_t stream) {
   p.dec_m = a.max_new_len;
   p.total_new_tokens = a.total_new_tokens;
   p.dec_ranges = pl.dec_wgs;
+  p.dec_records = pl.dec_records;
   p.direct_c_min = a.tuning && a.tuning->c_min > 0 ? a.tuning->c_min : kDirectCMin;
   p.direct_slots = pl.target_slots;
   p.units_bound = pl.units_bound;
@@ -1968,7 +2016,7 @@ static int32_t launch_mfma(const AttnArgs& a, hipStream_t stream) {
   const int64_t g_main = (int64_t)pl.items_bound * a.n_kv_heads;
   const int dec_hw = a.n_kv_heads % 8 == 0 ? 8 : 1;   // kv-heads (= waves) per workgroup of the decode kernel
   const int64_t g_dec = (int64_t)pl.dec_wgs * (a.n_kv_heads / dec_hw);
-  const int64_t g_merge = (int64_t)pl.dec_wgs * a.n_kv_heads;
+  const int64_t g_merge = (int64_t)pl.dec_records * a.n_kv_heads;
   if (g_main > 0x7FFFFFFFLL || g_merge > 0x7FFFFFFFLL) return SYMPH_EUNSUPPORTED;
   // The scheduler keeps one table entry per session in LDS (and the decode kernel adds the sessions up in every
   // workgroup): larger batches run as consecutive slices of sessions (same stream, same workspace; the bounds of the
