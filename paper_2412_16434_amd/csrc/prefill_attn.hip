@@ -1817,9 +1817,10 @@ __global__ __launch_bounds__(256) void attn_decode_merge_kernel(const MfmaParams
 // Tuning values with the defaults filled in (a field of symph_attn_tuning that is 0 keeps its default).
 struct AttnTuning {
   int32_t slots, c_min, coarse, decode, decode_wgs;
+  int32_t direct = 1;  // (no field of symph_attn_tuning: 0 asks make_plan for the work list)
 };
 static AttnTuning resolve_tuning(const symph_attn_tuning* t) {
-  AttnTuning r{512, 8, 1, 1, 512};  // 512 slots: 256 compute units x 2 resident workgroups
+  AttnTuning r{512, 8, 1, 1, 512, 1};  // 512 slots: 256 compute units x 2 resident workgroups
   if (t) {
     if (t->slots > 0) r.slots = t->slots;
     if (t->c_min > 0) r.c_min = t->c_min;
@@ -1892,7 +1893,7 @@ static bool make_plan(MfmaPlan& pl, int32_t n_sessions, int32_t n_q_heads, int32
   // grow with its place in the turn, and the work list's longest-first order is worth more than the scheduling kernel:
   // 2 x 2000 new tokens over 30, 4 kv-heads: 35 us by the list, 41 without; 2 x 900 over 500, 8 heads: 44 and 47.)
   const int64_t wg_units = pl.units_bound * (int64_t)n_kv_heads;
-  pl.direct = !pl.dec_mode && tu.coarse && pl.units_bound <= kDirectUnits && wg_units <= tu.slots &&
+  pl.direct = tu.direct && !pl.dec_mode && tu.coarse && pl.units_bound <= kDirectUnits && wg_units <= tu.slots &&
               (max_new_len <= max_prefix_len || 4 * wg_units <= tu.slots);
   if (pl.direct) {
     const int32_t listed = pl.pslots_bound;
@@ -1940,10 +1941,14 @@ int64_t prefill_attn_workspace_bytes(const symph_kv_cache* c, int32_t n_sessions
                                      const symph_attn_tuning* tuning) {
   if (n_q_heads % c->n_kv_heads != 0) return -1;
   if (!mfma_path_ok(c->dtype, c->head_dim, n_q_heads, c->n_kv_heads, c->block_size)) return 0;
-  MfmaPlan pl;
-  make_plan(pl, n_sessions, n_q_heads, c->n_kv_heads, total_new_tokens, max_new_len, max_prefix_len,
-            resolve_tuning(tuning), 0);
-  return pl.total_bytes;
+  MfmaPlan pl, listed;
+  AttnTuning tu = resolve_tuning(tuning);
+  make_plan(pl, n_sessions, n_q_heads, c->n_kv_heads, total_new_tokens, max_new_len, max_prefix_len, tu, 0);
+  // Never less than the work list needs, so that a workspace serves the same batch whichever kernels its tuning values or
+  // its bounds choose (the other plans are smaller).
+  tu.decode = tu.direct = 0;
+  make_plan(listed, n_sessions, n_q_heads, c->n_kv_heads, total_new_tokens, max_new_len, max_prefix_len, tu, 0);
+  return pl.total_bytes > listed.total_bytes ? pl.total_bytes : listed.total_bytes;
 }
 
 template <int G>

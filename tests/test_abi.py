@@ -4,6 +4,8 @@ import ctypes as C
 import os
 import re
 
+import pytest
+
 import paper_2412_16434_amd as S
 from paper_2412_16434_amd.binding import _CacheStruct
 
@@ -102,6 +104,20 @@ def test_host_validation_rejects_without_launching():
     assert lib.symph_mfma_reference(0, None, 0x10, None) == EINVAL
     assert lib.symph_mfma_reference(8, None, None, None) == EINVAL
     assert S.status_string(0) == "ok" and "unsupported" in S.status_string(-2)
+
+
+@pytest.mark.parametrize("sessions,tokens,max_new,max_prefix", [(1, 1, 1, 1777), (96, 96, 1, 16384), (1, 45, 45, 3001),
+                                                                (64, 300, 8, 900), (256, 16384, 64, 4096)])
+def test_workspace_query_serves_every_tuning(sessions, tokens, max_new, max_prefix):
+    """A workspace of the default size is enough for the same batch with the decode kernel switched off or on and with
+    every unit cut (a program that switches does not allocate again)."""
+    lib = S.load_library()
+    c = _cache(n_layers=1)
+    ask = lambda **kw: lib.symph_prefix_prefill_attn_workspace_bytes_tuned(C.byref(c), sessions, 32, tokens, max_new, max_prefix,
+                                                                           C.byref(S.AttnTuning(**kw)))
+    default = ask()
+    assert default > 0
+    assert default >= max(ask(decode=-1), ask(decode=1), ask(coarse=-1), ask(decode=-1, coarse=-1))
 
 
 def test_bench_refuses_more_than_one_gpu():
