@@ -85,8 +85,10 @@ __global__ __launch_bounds__(256) void kv_migrate_kernel(const MigrateParams p) 
   // session s with offsets[s] <= tg < offsets[s+1] (sessions of length 0 are skipped by taking the last match).  The search
   // is for the wave's first token, on the scalar unit; where a wave holds several tokens (short rows) a lane whose token
   // lies past that session's end walks on.  (A search per lane is a chain of log2(sessions) vector loads.)
-  const int64_t tg0 = ((int64_t)__builtin_amdgcn_readfirstlane((int32_t)(tg >> 32)) << 32) |
-                      (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)tg);
+  int64_t tg0 = tg;
+  if constexpr (!UNIFORM)
+    tg0 = ((int64_t)__builtin_amdgcn_readfirstlane((int32_t)(tg >> 32)) << 32) |
+          (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)tg);
   int32_t lo = 0, hi = p.n_sessions;
   while (hi - lo > 1) {
     const int32_t mid = (lo + hi) >> 1;
@@ -262,14 +264,14 @@ static int32_t launch_rows(const MigrateParams& p_in, hipStream_t stream) {
 
 template <typename VecT, bool PACK>
 static int32_t launch_planes(int planes, const MigrateParams& p_in, hipStream_t stream) {
-  // Measured on MI355X with one plane per lane: two consecutive tokens per wave, i.e. one session search for two loads.
-  // Gather, 16 sessions: 5.8 -> 6.1 TB/s (four the same, eight a cliff: 3.1; a single session has no search to share: 6.08
-  // -> 5.99).  Scatter, with the XCD-contiguous mapping: 16 sessions of 1 to 8 Ki tokens 3390 -> 3198 us, 81 of a few
-  // hundred 1353 -> 1222, 256 of 16 to 1200 7107 -> 6888, against two planes per lane in the plain order; one plane and one
-  // token 3241, two planes with the mapping 3337, two tokens in the plain order 3380.  (Where the driver places the pool's
-  // pages moves two planes in the plain order between 3010 and 3390, this form between 3080 and 3200: it is the slower one
-  // in the best placements by up to 4 %, the faster one in most.)  Everything that widens the set of
-  // rows under way at once loses: 8 / 64 planes per wave in a software pipeline 3484 / 3607 (gather 3040 -> 3306 / 3491).
+  // Measured on MI355X, gather with one plane per lane: two consecutive tokens per wave, i.e. one session search for two
+  // loads, 16 sessions 5.8 -> 6.1 TB/s; four the same, eight a cliff (3.1 TB/s); a single session has no search to share
+  // (6.08 -> 5.99).  Scatter of several layers: two tokens per wave, one plane, the XCD-contiguous mapping.  What the scatter
+  // reaches depends on where the driver places the pools and the buffer (a library that is a megabyte larger moves them):
+  // 18 GB of 16 sessions take 3080 to 3200 us in this form wherever that is, and 2880 to 3390 with two planes per lane in
+  // the plain order (mean of six processes 3134 and 3185; a 128 GiB pool, 8.6 GB: 2.65 or 2.93 ms, this form 2.85 where the
+  // other takes 2.93).  Everything that widens the set of rows under way at once loses: 8 / 64 planes per wave in a software
+  // pipeline, gather 3040 -> 3306 / 3491 us, scatter 3390 -> 3484 / 3607.
   if (planes == 1 && p_in.row_shift >= 6 && (!PACK || p_in.n_sessions > 1)) return launch_rows<VecT, PACK, 2, 1>(p_in, stream);
   const int64_t n_vec = p_in.total_tokens * p_in.vecs_per_row;
   const int64_t gx = ceil_div64(n_vec, 256);
@@ -277,7 +279,8 @@ static int32_t launch_planes(int planes, const MigrateParams& p_in, hipStream_t 
   if (gx > 0x7FFFFFFFLL || gy > 65535) return SYMPH_EUNSUPPORTED;
   dim3 grid((unsigned)gx, (unsigned)gy);
   MigrateParams p = p_in;
-  // (two planes per lane: the gather gains 2-3 % from the XCD-contiguous mapping, the scatter only where it has long rows)
+  // measured on MI355X (16 sessions): the gather gains 2-3 % from the XCD-contiguous mapping, the scatter loses 7 % in the
+  // good placements and gains 1 % in the others
   p.xcd_chunk = PACK ? (int32_t)(gx / 8) : 0;
   if (planes == 1)
     launch_uniform<VecT, PACK, 1>(grid, p, stream);
@@ -330,11 +333,13 @@ int32_t launch_kv_migrate(bool pack, const symph_kv_cache* c, int32_t layer_begi
   p.buf_bytes = buf_bytes;
   p.batch_layer_b = batch_layer_major ? 2 * total_tokens * row_bytes : 0;
 
-  // Planes per lane.  Long rows (a whole number of waves) move one plane per lane, two tokens per wave (launch_planes),
-  // unless the session search is long (gather of more than 64 sessions) or the second token of a wave is too often another
-  // session's (scatter of fewer than 64 tokens a session: 64 sessions of 28 tokens 80 us so, 87 by rows).  Short rows have
-  // a lookup per lane, which two planes share: 16 sessions with 256-byte rows, gather 638 -> 363 us (four planes 377).
-  const int planes = p.row_shift >= 6 && (pack ? n_sessions <= 64 : total_tokens >= (int64_t)64 * n_sessions) ? 1 : 2;  // (a launch always covers whole layers: two planes at least)
+  // Planes per lane.  One plane (and two tokens per wave, launch_planes) for the gather of long rows (a whole number of
+  // waves) while its session search is short: 16 sessions 6.1 TB/s against 5.8 with two, 256 sessions 5.6 against 5.9; four
+  // planes 5.5 and 5.7, eight 3.0.  For the scatter of long rows with more than one layer and 64 tokens a session or more
+  // (64 sessions of 28: 80 us with two planes, 87 so; 256 units of one layer: 1.6 ms and 2.2).  Short rows have a lookup per
+  // lane, which two planes share: 16 sessions with 256-byte rows, gather 638 -> 363 us (four planes 377).
+  const bool one = pack ? n_sessions <= 64 : p.plane_end - p.plane_begin > 2 && total_tokens >= (int64_t)64 * n_sessions;
+  const int planes = p.row_shift >= 6 && one ? 1 : 2;  // (a launch covers whole layers: two planes at least)
 
   if (vec == 16) return pack ? launch_planes<u32x4, true>(planes, p, stream) : launch_planes<u32x4, false>(planes, p, stream);
   return pack ? launch_planes<unsigned int, true>(planes, p, stream) : launch_planes<unsigned int, false>(planes, p, stream);
