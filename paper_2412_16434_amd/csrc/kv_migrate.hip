@@ -336,9 +336,13 @@ int32_t launch_kv_migrate(bool pack, const symph_kv_cache* c, int32_t layer_begi
   // Planes per lane.  One plane (and two tokens per wave, launch_planes) for the gather of long rows (a whole number of
   // waves) while its session search is short: 16 sessions 6.1 TB/s against 5.8 with two, 256 sessions 5.6 against 5.9; four
   // planes 5.5 and 5.7, eight 3.0.  For the scatter of long rows with more than one layer and 64 tokens a session or more
-  // (64 sessions of 28: 80 us with two planes, 87 so; 256 units of one layer: 1.6 ms and 2.2).  Short rows have a lookup per
-  // lane, which two planes share: 16 sessions with 256-byte rows, gather 638 -> 363 us (four planes 377).
-  const bool one = pack ? n_sessions <= 64 : p.plane_end - p.plane_begin > 2 && total_tokens >= (int64_t)64 * n_sessions;
+  // (64 sessions of 28: 80 us with two planes, 87 so; 256 units of one layer: 1.6 ms and 2.2), in pools of up to 32 GiB each:
+  // 8 sessions in 4 GiB pools 5.7 TB/s against 5.6, one in 20 GiB 5.8 and 5.5, 256 in 32 GiB 5.4 and 5.3, 16 in 64 GiB 6.0
+  // and 6.5 or 5.9.  Short rows have a lookup per lane, which two planes share: 16 sessions with 256-byte rows, gather 638
+  // -> 363 us (four planes 377).
+  const bool one = pack ? n_sessions <= 64
+                        : p.plane_end - p.plane_begin > 2 && total_tokens >= (int64_t)64 * n_sessions &&
+                              p.layer_stride_b <= ((int64_t)32 << 30) / c->n_layers;
   const int planes = p.row_shift >= 6 && one ? 1 : 2;  // (a launch covers whole layers: two planes at least)
 
   if (vec == 16) return pack ? launch_planes<u32x4, true>(planes, p, stream) : launch_planes<u32x4, false>(planes, p, stream);
