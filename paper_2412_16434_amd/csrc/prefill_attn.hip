@@ -1280,10 +1280,6 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const MfmaParams p) {
 constexpr int kSub = 32;                    // keys per tile of this kernel
 constexpr int kSubBytes = 8 * kGroupBytes;  // 8320
 constexpr int kDecWaveBytes = 2 * kSubBytes;  // K and V of one tile, per wave
-// Shortest range, in tiles.  What a step with little to read takes is the launch, a few trips to memory and the merge of
-// its pieces: 1 / 2 / 4 tiles measured 16.6 / 15.4 / 16.7 us for one session of 1777 tokens.
-constexpr int kDecMinTiles = 2;
-
 template <int G, int LB, int HW>
 __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(const MfmaParams p) {
   constexpr int BMTD = 32 / G;   // query tokens this kernel covers per session
@@ -1322,7 +1318,10 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
   __shared__ int start_of[7];  // where the range begins: session, token, the unit's first tile, its session's N, P, cu, unit
   int total, per_wg, range_begin, range_end;
   auto take_range = [&]() {
-    per_wg = max((total + p.dec_ranges - 1) / p.dec_ranges, kDecMinTiles);
+    // A step with fewer tiles than ranges has pieces of one tile, each rounded against its own maximum.  (Two tiles to a
+    // piece, the second rounded against the first one's maximum, made one session of 1777 tokens 14.2 instead of 15.7 us and
+    // its error against 64 bits 2.16e-3 instead of 2.02e-3.)
+    per_wg = (total + p.dec_ranges - 1) / p.dec_ranges;
     range_begin = wg * per_wg;
     range_end = min(total, range_begin + per_wg);
   };
@@ -1709,7 +1708,7 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
 // the c-th range after the one that wrote pslot0.
 // One workgroup per (record, kv-head), eight rows at a time.  Wave w takes pieces w, w + 4, ..: a step that decodes a few
 // long sessions cuts them into tens of pieces each, and a thread that reads them one after the other waits for memory
-// every time (one session of 1777 tokens in 56 pieces: 50 us; this way 8 us, and 5 us for its 28 pieces of two tiles).
+// every time (one session of 1777 tokens in 56 pieces: 50 us; this way 8 us).
 // Records are per unit, not per key range, so that the grid follows the batch: 8 instead of 2048 workgroups for one session
 // (14.9 -> 14.4 us with the lengths added up inside a wave for up to 64 sessions, without a barrier).
 constexpr int kMergeRows = 8;

@@ -174,6 +174,44 @@ def test_decode_units_and_merges(oracle_mod, hkv, group, prefix, new, stated):
     assert np.sqrt(np.sum((f(got) - f(main)) ** 2) / np.sum(f(main) ** 2)) <= 1e-2
 
 
+@pytest.mark.parametrize("hkv,group,prefix,new", [
+    (8, 4, [1777], [1]),
+    (2, 8, [900, 31, 250], [1, 4, 2]),
+    (1, 4, [5000], [8]),
+])
+def test_short_decode_steps_round_every_tile_against_its_own_maximum(hkv, group, prefix, new):
+    """A decode step with no more 32-key tiles than key ranges has one tile to a piece: its probabilities are rounded to bf16
+    against that tile's maximum.  The same worked out in 64 bits differs from the output in sums and exponentials only
+    (2^-20 of a probability, which moves few roundings): by far less than the 1.4e-3 that other references make."""
+    cfg = _cfg(n_sessions=len(new), n_kv_heads=hkv, n_q_heads=hkv * group, n_blocks=512, prefix_dist=("const", max(prefix)))
+    sess = W.make_sessions(cfg, 83, new_lens=np.array(new))
+    sess.prefix_lens[:] = prefix
+    sess.buf_token_offsets[1:] = np.cumsum(prefix)
+    inputs = W.make_attn_inputs(cfg, sess, 83)
+    got = widen(gpu_attention(cfg, sess, inputs))
+    assert sum(-(-(p + n) // 32) for p, n in zip(prefix, new)) <= 4 * 512 // hkv    # (ranges of the default tuning)
+    k_pool, v_pool, q, k_new, v_new = (widen(a) for a in inputs)
+    f32_to_bf16 = lambda x: W.bf16_bits_to_f32(W.f32_to_bf16_bits(x.astype(np.float32))).astype(np.float64)
+    want = np.empty_like(got)
+    for s, (P, N) in enumerate(zip(prefix, new)):
+        a = int(sess.cu_new_lens[s])
+        blocks = sess.block_table[s, :-(-P // 16)]
+        for g in range(hkv):
+            k, v = (np.concatenate([pool[blocks, :, g].reshape(-1, 128)[:P], fresh[a:a + N, g]])
+                    for pool, fresh in ((k_pool, k_new), (v_pool, v_new)))
+            for i in range(N):
+                for h in range(g * group, (g + 1) * group):
+                    sc = (k[:P + i + 1] @ q[a + i, h]) * (cfg.scale * np.log2(np.e))
+                    top = sc.max()
+                    o, l = 0.0, 0.0
+                    for j in range(0, P + i + 1, 32):
+                        m = sc[j:j + 32].max()
+                        w = f32_to_bf16(np.exp2(sc[j:j + 32] - m)) * np.exp2(m - top)
+                        o, l = o + w @ v[j:min(j + 32, P + i + 1)], l + w.sum()
+                    want[a + i, h] = f32_to_bf16(o / l)
+    assert np.sqrt(np.sum((got - want) ** 2) / np.sum(want ** 2)) <= 5e-4
+
+
 @pytest.mark.parametrize("hkv,group,bs,prefix,new", [
     (8, 4, 16, [3001], [45]),                            # one turn in many pieces, its last tile half empty
     (8, 4, 16, [0, 1, 63, 64, 4000], [33, 1, 32, 0, 70]),    # no prefix, no new tokens, whole and split units together
