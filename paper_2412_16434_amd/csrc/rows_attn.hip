@@ -255,7 +255,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
   auto first_slot = [&](int s) { return (int)((int64_t)p.cu_new_lens[s] * G / R) + s; };
   const int s = wave_last(p.n_sessions, [&](int i) { return first_slot(i) <= slot; });
   const int cu_s = p.cu_new_lens[s];
-  const int N = p.cu_new_lens[s + 1] - cu_s;
+  const int N = max(min(p.cu_new_lens[s + 1], p.total_new_tokens) - cu_s, 0);  // (rows past total_new_tokens do not exist)
   const int P = p.prefix_lens[s];
   const int64_t row0 = (int64_t)(slot - first_slot(s)) * R;
   const int64_t rows = (int64_t)N * G;

@@ -256,6 +256,36 @@ def test_shapes_without_a_work_list(oracle_mod, dtype, d, hkv, group, bs, prefix
     check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 71), label="rows")
 
 
+@pytest.mark.parametrize("dtype,d,group,new,beyond", [
+    ("bf16", 64, 4, [10], 90),          # a tile of 32 rows past the end of a turn
+    ("bf16", 128, 3, [7, 14], 3),
+    ("fp32", 64, 2, [5, 0, 6], 40),
+    ("fp32", 128, 1, [17], 1),
+])
+def test_rows_past_the_stated_total_are_left_alone(oracle_mod, dtype, d, group, new, beyond):
+    """Lengths on the device that go on past total_new_tokens: rows that do not exist are neither read nor written, the ones
+    that do are right."""
+    import torch
+    from gpu_util import DEV, DeviceSessions, to_dev, to_host
+    cfg = _cfg(dtype=dtype, head_dim=d, n_sessions=len(new), n_kv_heads=2, n_q_heads=2 * group)
+    sess = W.make_sessions(cfg, 89, new_lens=np.array(new))
+    inputs = k_pool, v_pool, q, k_new, v_new = W.make_attn_inputs(cfg, sess, 89)
+    ref = oracle_mod.prefix_prefill_attn(*inputs, sess.cu_new_lens, sess.prefix_lens, sess.block_table, cfg.scale)
+    ds, total = DeviceSessions(sess), sum(new)
+    ds.cu_new_lens[-1] += beyond
+    held = [torch.zeros((total + 128, *a.shape[1:]), dtype=to_dev(a).dtype, device=DEV) for a in (q, k_new, v_new)]
+    for t, a in zip(held, (q, k_new, v_new)):
+        t[:total] = to_dev(a)
+        t[total:] = float("nan")
+    out = torch.full_like(held[0], 7.0)
+    S.prefix_prefill_attn(S.KVCache(to_dev(k_pool)[None], to_dev(v_pool)[None]), 0, held[0][:total], held[1][:total],
+                          held[2][:total], out[:total], ds.cu_new_lens, ds.prefix_lens, ds.table, max(new), sess.max_prefix_len,
+                          cfg.scale)
+    assert bool((out[total:] == 7.0).all()), "rows behind the output were written"
+    max_abs, rel = attn_errors(to_host(out[:total]), ref)
+    assert max_abs <= TOL[dtype][0] and rel <= TOL[dtype][1]
+
+
 @pytest.mark.parametrize("dtype,d,group", [("bf16", 64, 4), ("bf16", 128, 3), ("fp32", 64, 2), ("fp32", 128, 1)])
 def test_rows_do_not_see_what_they_must_not(oracle_mod, dtype, d, group):
     """An infinity and a NaN among the values of a later token of the turn: earlier tokens are finite and right (a matrix
