@@ -127,14 +127,16 @@ __global__ __launch_bounds__(64) void attn_row_kernel(const RowsParams p) {
 // through LDS at the end.  No scheduling kernel, no workspace, one launch: these shapes are small models and odd group
 // sizes, whose calls are short, so what counts is how few trips to memory stand one behind the other.
 //
-// What is held in 32 bits: probabilities too.  The bf16 kernel splits them into two bf16 values (p = hi + lo to 2^-17) and
-// multiplies V with both, which leaves the rounding of the output as the only one; the fp32 kernel uses the fp32 matrix
-// instruction throughout.
+// What is held in 32 bits: probabilities too.  The bf16 kernel splits them into three bf16 values whose sum is the 32-bit
+// value (8 bits of the 24 each) and multiplies V with all three, which leaves the rounding of the output and the 32-bit sums
+// as the only ones; the fp32 kernel uses the fp32 matrix instruction throughout.  (Two values, 2^-17, were 6 to 13 % faster
+// on full chips, 6 % on the first of the calls below, and rounded ten times as many outputs to the other neighbour of the
+// 64-bit result: 1.7e-3 of them for 1.1e-4 to 1.7e-4.)
 //
-// Measured against one wave per row (attn_row_kernel below, 32-bit arithmetic on the vector unit, lanes over keys): six
-// sessions of 300 to 2000 tokens, 64-wide heads, 380 -> 18 us; one fp32 session of 256 tokens, 24.6 -> 9.9 us, which is the
-// call itself; three fp32 sessions of 8192, 775 -> 193; 16 of 2000 to 4000 with 64-wide heads, 12 805 -> 229.  The error
-// against 64 bits is the same in bf16 and lower in fp32 (2.9e-7 for 4.7e-7 at 128 x 8000 keys).  A block's 24 MFMAs and the
+// Measured against one wave per row (attn_row_kernel above, 32-bit arithmetic on the vector unit, lanes over keys): six
+// sessions of 300 to 2000 tokens, 64-wide heads, 380 -> 19 us; one fp32 session of 256 tokens, 24.6 -> 9.9 us, which is the
+// call itself; three fp32 sessions of 8192, 775 -> 193; 16 of 2000 to 4000 with 64-wide heads, 12 805 -> 260.  The error
+// against 64 bits is the same in bf16 and lower in fp32 (2.9e-7 for 4.7e-7 at 128 x 8000 keys).  A block's 32 MFMAs and the
 // exponentials are matched by as many vector instructions again for the split and the addresses, so the vector unit bounds
 // a full chip and the chain load -> product -> softmax -> product a small call.
 //
@@ -384,14 +386,16 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
           for (int e = 0; e < 16; ++e) o[dt][e] *= a;
       }
       const float ref = m == -INFINITY ? 0.f : m;
-      bf16x8 hi[2], lo[2];
+      bf16x8 hi[2], mid[2], lo[2];  // the probabilities, 8 bits each
       float sum = 0.f;
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const float w = __builtin_amdgcn_exp2f(fmaf(x[e], cs, -ref));
         sum += w;
         hi[e >> 3][e & 7] = (__bf16)w;
-        lo[e >> 3][e & 7] = (__bf16)(w - (float)hi[e >> 3][e & 7]);
+        const float rest = w - (float)hi[e >> 3][e & 7];
+        mid[e >> 3][e & 7] = (__bf16)rest;
+        lo[e >> 3][e & 7] = (__bf16)(rest - (float)mid[e >> 3][e & 7]);
       }
       l += sum;
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -405,6 +409,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
           const s16x4 a1 = lds_read_tr16(reinterpret_cast<const __bf16*>(vp + 4 * kVRow));
           const bf16x8 v = __builtin_bit_cast(bf16x8, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
           o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, hi[u], o[dt], 0, 0, 0);
+          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, mid[u], o[dt], 0, 0, 0);
           o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, lo[u], o[dt], 0, 0, 0);
         }
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

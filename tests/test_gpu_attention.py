@@ -256,6 +256,22 @@ def test_shapes_without_a_work_list(oracle_mod, dtype, d, hkv, group, bs, prefix
     check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 71), label="rows")
 
 
+@pytest.mark.parametrize("d,hkv,group,bs", [(64, 4, 4, 16), (128, 2, 3, 16), (128, 4, 2, 8)])
+def test_probabilities_of_bf16_rows_are_held_in_32_bits(oracle_mod, d, hkv, group, bs):
+    """The shapes without a work list round to bf16 once, at the output: hardly any value is rounded to the other neighbour
+    of the 64-bit result.  A relative error e before that rounding does so to a share of about 0.7 * 2^8 * e of the values.
+    Outputs are a tenth of the terms they are summed from, so sums in 32 bits (2^-24 of the terms, some of them) give e = 1e-6
+    and a share of 2e-4, probabilities of 17 bits ten times that; the bound lies between."""
+    cfg = _cfg(head_dim=d, n_sessions=3, n_kv_heads=hkv, n_q_heads=hkv * group, block_size=bs, n_blocks=512, scale=1 / np.sqrt(d))
+    sess = W.make_sessions(cfg, 97, new_lens=np.array([90, 64, 77]))
+    inputs = W.make_attn_inputs(cfg, sess, 97)
+    ref = oracle_mod.prefix_prefill_attn(*inputs, sess.cu_new_lens, sess.prefix_lens, sess.block_table, cfg.scale)
+    got = gpu_attention(cfg, sess, inputs)
+    other = float(np.mean(got != W.f32_to_bf16_bits(ref.astype(np.float32))))
+    print(f"[rows] {got.size} values, {other:.2e} rounded to the other neighbour")
+    assert got.size > 100000 and other <= 5e-4
+
+
 @pytest.mark.parametrize("dtype,d,group,new,beyond", [
     ("bf16", 64, 4, [10], 90),          # a tile of 32 rows past the end of a turn
     ("bf16", 128, 3, [7, 14], 3),
