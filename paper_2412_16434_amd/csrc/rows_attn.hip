@@ -25,8 +25,11 @@ __device__ __forceinline__ float to_f32(__bf16 x) { return (float)x; }
 __device__ __forceinline__ void from_f32(float* p, float x) { *p = x; }
 __device__ __forceinline__ void from_f32(__bf16* p, float x) { *p = (__bf16)x; }
 
+constexpr int kRedoColumns = 32;
+
 // ---- one wave per (token, query head), lanes over keys, fp32 throughout.  q_s: D floats in LDS of the wave's own.  CH
-// output columns at a time (the scores are worked out again for each: where registers matter more than time).
+// output columns at a time (the scores are worked out again for each: where registers matter more than time: 64 columns
+// for the rows worked out again by the tiled kernel made it spill 90 scalar registers).
 template <typename T, int D, int CH>
 __device__ __forceinline__ void row_by_lanes(const RowsParams& p, int32_t s, int32_t tok, int32_t h, float* q_s) {
   const int lane = threadIdx.x & 63;
@@ -175,12 +178,13 @@ __device__ __forceinline__ int wave_last(int n, F holds) {
 
 // The W waves' results of a tile of R rows, DC columns at a time through LDS: out = sum_w f_w O_w / sum_w f_w l_w with
 // f_w = e^(m_w - max_w m_w) (base 2 or e, as the caller's references are).  put(round, f, mine) writes the lane's part of the
-// wave's columns, scaled.  A result that is not finite (an infinity or a NaN among the inputs, which the matrix product
-// spreads over rows that must not see its key) is worked out again row by row.
+// wave's columns, scaled.  A row with a result that is not finite (an infinity or a NaN among the inputs, which the matrix
+// product spreads over rows that must not see its key) is worked out again by itself.  Its q is read again for that, so it is
+// not written before: out may be q.
 template <typename T, int D, int R, int DC, int W, typename Put, typename Exp>
 __device__ __forceinline__ void combine_rows(const RowsParams& p, char* lds, const float (*wave_m)[R],
-                                             const float (*wave_l)[R], int& redo, Put put, Exp exp_of, int s, int cu_s,
-                                             int kvh, int G, int64_t row0, int n_rows) {
+                                             const float (*wave_l)[R], unsigned& bad_rows, Put put, Exp exp_of, int s,
+                                             int cu_s, int kvh, int G, int64_t row0, int n_rows) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int kStride = DC + 4;  // floats between rows (the padding spreads them over the banks)
   float* const all = reinterpret_cast<float*>(lds);
@@ -191,7 +195,7 @@ __device__ __forceinline__ void combine_rows(const RowsParams& p, char* lds, con
   const float mine_m = wave_m[wave][n];
   const float f = mine_m == -INFINITY ? 0.f : exp_of(mine_m - M);
   // thread t adds up V columns from c0 on of row t * V / DC
-  constexpr int V = R * DC / (64 * W);
+  constexpr int V = R * DC / (64 * W), kRounds = D / DC;
   const int r = tid * V / DC, c0 = tid * V % DC;
   float Mr = -INFINITY, L = 0.f;
 #pragma unroll
@@ -200,12 +204,11 @@ __device__ __forceinline__ void combine_rows(const RowsParams& p, char* lds, con
   for (int w = 0; w < W; ++w)
     L += wave_m[w][r] == -INFINITY ? 0.f : wave_l[w][r] * exp_of(wave_m[w][r] - Mr);
   const float inv = 1.0f / L;
-  const int64_t row = row0 + r;
-  const int tok = (int)(row / G);
-  T* const op = (T*)p.out + ((int64_t)(cu_s + tok) * p.n_q_heads + kvh * G + (int)(row - (int64_t)tok * G)) * D;
+  typedef T vec __attribute__((ext_vector_type(V)));
+  vec x[kRounds];
   bool bad = false;
 #pragma unroll
-  for (int round = 0; round < D / DC; ++round) {
+  for (int round = 0; round < kRounds; ++round) {
     if (round > 0) __syncthreads();  // the columns before have been added up
     put(round, f, all + wave * R * kStride);
     __syncthreads();
@@ -216,24 +219,28 @@ __device__ __forceinline__ void combine_rows(const RowsParams& p, char* lds, con
     for (int w = 0; w < W; ++w)
 #pragma unroll
       for (int v = 0; v < V; ++v) sum[v] += all[(w * R + r) * kStride + c0 + v];
-    if (r < n_rows) {
-      typedef T vec __attribute__((ext_vector_type(V)));
-      vec x;
 #pragma unroll
-      for (int v = 0; v < V; ++v) {
-        bad = bad || !(fabsf(sum[v] * inv) < INFINITY);
-        x[v] = (T)(sum[v] * inv);
-      }
-      *reinterpret_cast<vec*>(op + round * DC + c0) = x;
+    for (int v = 0; v < V; ++v) {
+      bad = bad || !(fabsf(sum[v] * inv) < INFINITY);
+      x[round][v] = (T)(sum[v] * inv);
     }
   }
-  if (__any(bad)) redo = 1;
+  if (bad && r < n_rows) atomicOr(&bad_rows, 1u << r);
   __syncthreads();
-  if (!redo) return;
-  for (int i = wave; i < n_rows; i += W) {
-    const int64_t again = row0 + i;
-    const int t = (int)(again / G);
-    row_by_lanes<T, D, 32>(p, s, cu_s + t, kvh * G + (int)(again - (int64_t)t * G), all + wave * D);
+  const unsigned again = __builtin_amdgcn_readfirstlane(bad_rows);
+  if (r < n_rows && !((again >> r) & 1)) {
+    const int64_t row = row0 + r;
+    const int tok = (int)(row / G);
+    T* const op = (T*)p.out + ((int64_t)(cu_s + tok) * p.n_q_heads + kvh * G + (int)(row - (int64_t)tok * G)) * D;
+#pragma unroll
+    for (int round = 0; round < kRounds; ++round) *reinterpret_cast<vec*>(op + round * DC + c0) = x[round];
+  }
+  int turn = 0;
+  for (unsigned left = again; left; left &= left - 1) {
+    if (turn++ % W != wave) continue;
+    const int64_t row = row0 + __builtin_ctz(left);
+    const int tok = (int)(row / G);
+    row_by_lanes<T, D, 32>(p, s, cu_s + tok, kvh * G + (int)(row - (int64_t)tok * G), all + wave * D);
   }
 }
 
@@ -247,7 +254,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
   constexpr int kCombBytes = W * R * (DC + 4) * 4;
   __shared__ __attribute__((aligned(16))) char lds[kVBytes > kCombBytes ? kVBytes : kCombBytes];
   __shared__ float wave_m[W][R], wave_l[W][R];
-  __shared__ int redo;
+  __shared__ unsigned bad_rows;
 
   const int Hkv = p.n_kv_heads;
   const int G = p.n_q_heads / Hkv;
@@ -274,7 +281,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
   const int total_keys = P + N;
   const int n_blocks_k = (P + (int)((row0 + n_rows - 1) / G) + R) / R;  // key blocks up to the last row's limit
   const T* const qp = (const T*)p.q + ((int64_t)(cu_s + tok) * p.n_q_heads + kvh * G + (int)(my_row - (int64_t)tok * G)) * D;
-  if (tid == 0) redo = 0;
+  if (tid == 0) bad_rows = 0;
 
   // ---- rows of K and V: block ids are read one per lane (lane i: key i of the block) and passed between lanes
   const int32_t* const table_row = p.table + (int64_t)s * p.table_stride;
@@ -421,7 +428,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
       wave_l[wave][n] = l_row;
     }
     __syncthreads();  // (also: no wave reads its V tile any more, the buffer is free)
-    combine_rows<T, D, R, DC, W>(p, lds, wave_m, wave_l, redo, [&](int round, float f, float* mine) {
+    combine_rows<T, D, R, DC, W>(p, lds, wave_m, wave_l, bad_rows, [&](int round, float f, float* mine) {
       // (o[round] by a chain of selects: a register array cannot be indexed)
 #pragma unroll
       for (int dt = 0; dt < NT; ++dt)
@@ -550,7 +557,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
       wave_l[wave][n] = l;
     }
     __syncthreads();
-    combine_rows<T, D, R, DC, W>(p, lds, wave_m, wave_l, redo, [&](int, float f, float* mine) {
+    combine_rows<T, D, R, DC, W>(p, lds, wave_m, wave_l, bad_rows, [&](int, float f, float* mine) {
 #pragma unroll
       for (int h = 0; h < NH; ++h)
 #pragma unroll

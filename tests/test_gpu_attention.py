@@ -323,6 +323,32 @@ def test_rows_do_not_see_what_they_must_not(oracle_mod, dtype, d, group):
     assert err.max() <= TOL[dtype][0]
 
 
+@pytest.mark.parametrize("dtype,d,group", [("bf16", 64, 4), ("bf16", 128, 3), ("fp32", 64, 2), ("fp32", 128, 1)])
+def test_rows_written_in_place_of_their_queries(dtype, d, group):
+    """out in place of q, with an infinity and a NaN among the values (rows beside them are worked out a second time): the
+    rows that are finite are those of a call with an output of its own, and so are the others."""
+    import torch
+    from gpu_util import DeviceSessions, to_dev
+    cfg = _cfg(dtype=dtype, head_dim=d, n_sessions=3, n_kv_heads=2, n_q_heads=2 * group)
+    sess = W.make_sessions(cfg, 101, new_lens=np.array([40, 9, 23]))
+    k_pool, v_pool, q, k_new, v_new = W.make_attn_inputs(cfg, sess, 101)
+    bits = (lambda x: W.f32_to_bf16_bits(np.float32([x]))[0]) if dtype == "bf16" else np.float32
+    v_new[17, 0, 5] = bits(np.inf)
+    v_new[44, 1, 3] = np.float32(np.nan) if dtype == "fp32" else W.SENTINEL16
+    ds, cache = DeviceSessions(sess), S.KVCache(to_dev(k_pool)[None], to_dev(v_pool)[None])
+    kd, vd = to_dev(k_new), to_dev(v_new)
+
+    def run(q_dev, out):
+        S.prefix_prefill_attn(cache, 0, q_dev, kd, vd, out, ds.cu_new_lens, ds.prefix_lens, ds.table, sess.max_new_len,
+                              sess.max_prefix_len, cfg.scale)
+        return out
+    apart, q_dev = run(to_dev(q), torch.empty_like(to_dev(q))), to_dev(q)
+    together = run(q_dev, q_dev)
+    finite = torch.isfinite(apart)
+    assert not bool(finite.all()) and bool((torch.isfinite(together) == finite).all())
+    assert torch.equal(together[finite], apart[finite])
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("fp32", 128)])
 def test_unaligned_pools_agree_with_aligned_ones(dtype, d):
     """Pools that start one element past a 16-byte boundary take the kernel with narrow loads."""
