@@ -25,8 +25,6 @@ __device__ __forceinline__ float to_f32(__bf16 x) { return (float)x; }
 __device__ __forceinline__ void from_f32(float* p, float x) { *p = x; }
 __device__ __forceinline__ void from_f32(__bf16* p, float x) { *p = (__bf16)x; }
 
-constexpr int kRedoColumns = 32;
-
 // ---- one wave per (token, query head), lanes over keys, fp32 throughout.  q_s: D floats in LDS of the wave's own.  CH
 // output columns at a time (the scores are worked out again for each: where registers matter more than time: 64 columns
 // for the rows worked out again by the tiled kernel made it spill 90 scalar registers).
@@ -225,7 +223,8 @@ __device__ __forceinline__ void combine_rows(const RowsParams& p, char* lds, con
       x[round][v] = (T)(sum[v] * inv);
     }
   }
-  if (bad && r < n_rows) atomicOr(&bad_rows, 1u << r);
+  // (a sum that is NaN comes from a score that is: every value of the row is NaN, worked out either way)
+  if (bad && L == L && r < n_rows) atomicOr(&bad_rows, 1u << r);
   __syncthreads();
   const unsigned again = __builtin_amdgcn_readfirstlane(bad_rows);
   if (r < n_rows && !((again >> r) & 1)) {

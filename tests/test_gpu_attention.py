@@ -324,6 +324,22 @@ def test_rows_do_not_see_what_they_must_not(oracle_mod, dtype, d, group):
 
 
 @pytest.mark.parametrize("dtype,d,group", [("bf16", 64, 4), ("bf16", 128, 3), ("fp32", 64, 2), ("fp32", 128, 1)])
+def test_a_key_that_is_not_a_number(oracle_mod, dtype, d, group):
+    """A NaN in the key of a later token: the rows that see it are NaN in every column, all others finite and right."""
+    cfg = _cfg(dtype=dtype, head_dim=d, n_sessions=2, n_kv_heads=2, n_q_heads=2 * group)
+    sess = W.make_sessions(cfg, 73, new_lens=np.array([40, 9]))
+    k_pool, v_pool, q, k_new, v_new = W.make_attn_inputs(cfg, sess, 73)
+    ref = oracle_mod.prefix_prefill_attn(k_pool, v_pool, q, k_new, v_new, sess.cu_new_lens, sess.prefix_lens,
+                                         sess.block_table, cfg.scale)
+    k_new[17, 0, 5] = np.float32(np.nan) if dtype == "fp32" else W.SENTINEL16
+    got = widen(gpu_attention(cfg, sess, (k_pool, v_pool, q, k_new, v_new), scale=cfg.scale))
+    sees = np.zeros(got.shape, dtype=bool)
+    sees[17:40, :group] = True
+    assert np.isnan(got[sees]).all() and np.isfinite(got[~sees]).all()
+    assert np.abs(got - ref)[~sees].max() <= TOL[dtype][0]
+
+
+@pytest.mark.parametrize("dtype,d,group", [("bf16", 64, 4), ("bf16", 128, 3), ("fp32", 64, 2), ("fp32", 128, 1)])
 def test_rows_written_in_place_of_their_queries(dtype, d, group):
     """out in place of q, with an infinity and a NaN among the values (rows beside them are worked out a second time): the
     rows that are finite are those of a call with an output of its own, and so are the others."""
