@@ -1299,24 +1299,25 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
   const int lb = LB ? LB : p.log_bs;
   const int bs_mask = (1 << lb) - 1;
 
-  // Every workgroup works its range out from the sessions' lengths by itself: one trip to memory and a scan over the
-  // workgroup.  (A scheduling kernel in front, whose result every workgroup then read, was two more trips, a launch and
-  // the gap behind it: 6 us of a decode step.)
+  // Every workgroup works its range out from the sessions' lengths by itself, 64 sessions at a time, one per lane.  (A
+  // scheduling kernel in front, whose result every workgroup then read, was two more trips to memory, a launch and the gap
+  // behind it: 6 us of a decode step.)
   const int m = p.dec_m;
+  const int lane_s = tid & 63;
   auto span_of = [&](int s, int& cu_s, int& N, int& P) {  // rows past total_new_tokens do not exist (flagged below)
     cu_s = p.cu_new_lens[s];
     N = max(min(p.cu_new_lens[s + 1], p.total_new_tokens) - cu_s, 0);
     P = max(p.prefix_lens[s], 0);
   };
   auto tiles_to = [](int P, int end) { return (P + end + kSub - 1) / kSub; };  // of a unit whose last token is end - 1
-  auto session_tiles = [&](int N, int P) {
-    int n = 0;
-    for (int t0 = 0; t0 < N; t0 += m) n += tiles_to(P, min(N, t0 + m));
-    return n;
+  int my_cu, my_N, my_P, my_tiles, my_units;  // of session 64 * chunk + lane
+  auto take_chunk = [&](int chunk) {
+    my_cu = my_N = my_P = my_tiles = 0;
+    if (64 * chunk + lane_s < p.n_sessions) span_of(64 * chunk + lane_s, my_cu, my_N, my_P);
+    for (int t = 0; t < my_N; t += m) my_tiles += tiles_to(my_P, min(my_N, t + m));
+    my_units = (my_N + m - 1) / m;
   };
-  __shared__ int scan_sums[HW][2];
-  __shared__ int start_of[7];  // where the range begins: session, token, the unit's first tile, its session's N, P, cu, unit
-  int total, per_wg, range_begin, range_end;
+  int total, n_units, per_wg, range_begin, range_end;
   auto take_range = [&]() {
     // A step with fewer tiles than ranges has pieces of one tile, each rounded against its own maximum.  (Two tiles to a
     // piece, the second rounded against the first one's maximum, made one session of 1777 tokens 14.2 instead of 15.7 us and
@@ -1325,91 +1326,57 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
     range_begin = wg * per_wg;
     range_end = min(total, range_begin + per_wg);
   };
-  // Units are numbered in session order.  The range that has a unit's first tile writes its record, block 0 those of the
-  // numbers past the last unit.  (More units than records would be lengths that break the caller's contract.)
-  int s, t0, unit, unit_begin, N, P, cu, n_units;
+  auto first_past = [&](int incl) { return __builtin_ctzll(__ballot(range_begin < incl) | (1ull << 63)); };
+  // Above 64 sessions the waves add up the chunks of 64 in turn first, and the range's chunk is read once more.  (A thread
+  // that walked n_sessions / threads sessions one after the other: 4096 sessions of up to 128 tokens, one kv-head 95 us, four
+  // 187, eight 289; this way 62, 151 and 289.)
+  static_assert(kSchedMaxSessions <= 64 * 64, "one lane per chunk");
+  __shared__ int chunk_sums[64][2];
+  int chunk = 0, incl, units;  // inclusive sums up to the lane's session
   if (p.n_sessions <= 64) {
-    // lane s: session s; every wave does this by itself
-    const int lane_s = tid & 63;
-    int my_cu = 0, my_N = 0, my_P = 0;
-    if (lane_s < p.n_sessions) span_of(lane_s, my_cu, my_N, my_P);
-    const int mine = session_tiles(my_N, my_P), my_units = (my_N + m - 1) / m;
-    const int incl = wave_inclusive_scan(mine), units = wave_inclusive_scan(my_units);
+    take_chunk(0);
+    incl = wave_inclusive_scan(my_tiles);
+    units = wave_inclusive_scan(my_units);
     total = __builtin_amdgcn_readlane(incl, 63);
     n_units = __builtin_amdgcn_readlane(units, 63);
     take_range();
-    const int owner = __builtin_ctzll(__ballot(range_begin < incl) | (1ull << 63));
-    s = owner;
-    N = __builtin_amdgcn_readlane(my_N, owner);
-    P = __builtin_amdgcn_readlane(my_P, owner);
-    cu = __builtin_amdgcn_readlane(my_cu, owner);
-    unit_begin = __builtin_amdgcn_readlane(incl, owner) - __builtin_amdgcn_readlane(mine, owner);
-    unit = __builtin_amdgcn_readlane(units, owner) - __builtin_amdgcn_readlane(my_units, owner);
-    t0 = 0;
-    while (t0 + m < N && unit_begin + tiles_to(P, t0 + m) <= range_begin) {
-      unit_begin += tiles_to(P, t0 + m);
-      t0 += m;
-      ++unit;
-    }
   } else {
-    // thread t: sessions t * c .. t * c + c - 1
-    const int c = (p.n_sessions + 64 * HW - 1) / (64 * HW);
-    int mine = 0, my_units = 0;
-    for (int i = tid * c; i < min(tid * c + c, p.n_sessions); ++i) {
-      int cu_i, N_i, P_i;
-      span_of(i, cu_i, N_i, P_i);
-      mine += session_tiles(N_i, P_i);
-      my_units += (N_i + m - 1) / m;
-    }
-    int incl = wave_inclusive_scan(mine), units = wave_inclusive_scan(my_units);
-    if ((tid & 63) == 63) {
-      scan_sums[wave][0] = incl;
-      scan_sums[wave][1] = units;
+    const int n_chunks = (p.n_sessions + 63) >> 6;
+#pragma unroll 4
+    for (int c = wave; c < n_chunks; c += HW) {
+      take_chunk(c);
+      const int t = wave_inclusive_scan(my_tiles), u = wave_inclusive_scan(my_units);
+      if (lane_s == 63) {
+        chunk_sums[c][0] = t;
+        chunk_sums[c][1] = u;
+      }
     }
     __syncthreads();
-    total = n_units = 0;
-#pragma unroll
-    for (int w = 0; w < HW; ++w) {
-      const int x = scan_sums[w][0], y = scan_sums[w][1];
-      if (w < wave) {
-        incl += x;
-        units += y;
-      }
-      total += x;
-      n_units += y;
-    }
+    const int t = lane_s < n_chunks ? chunk_sums[lane_s][0] : 0, u = lane_s < n_chunks ? chunk_sums[lane_s][1] : 0;
+    const int t_incl = wave_inclusive_scan(t), u_incl = wave_inclusive_scan(u);
+    total = __builtin_amdgcn_readlane(t_incl, 63);
+    n_units = __builtin_amdgcn_readlane(u_incl, 63);
     take_range();
-    if (incl - mine <= range_begin && range_begin < incl) {  // this thread's sessions hold the range's first tile
-      int at = incl - mine, u = units - my_units;
-      for (int i = tid * c; i < p.n_sessions; ++i) {  // (ends in this thread's sessions: their tiles reach past range_begin)
-        int cu_i, N_i, P_i;
-        span_of(i, cu_i, N_i, P_i);
-        int t = 0;
-        for (; t < N_i; t += m, ++u) {
-          const int nt = tiles_to(P_i, min(N_i, t + m));
-          if (at + nt > range_begin) break;
-          at += nt;
-        }
-        if (t < N_i) {
-          start_of[0] = i;
-          start_of[1] = t;
-          start_of[2] = at;
-          start_of[3] = N_i;
-          start_of[4] = P_i;
-          start_of[5] = cu_i;
-          start_of[6] = u;
-          break;
-        }
-      }
-    }
-    __syncthreads();
-    s = __builtin_amdgcn_readfirstlane(start_of[0]);
-    t0 = __builtin_amdgcn_readfirstlane(start_of[1]);
-    unit_begin = __builtin_amdgcn_readfirstlane(start_of[2]);
-    N = __builtin_amdgcn_readfirstlane(start_of[3]);
-    P = __builtin_amdgcn_readfirstlane(start_of[4]);
-    cu = __builtin_amdgcn_readfirstlane(start_of[5]);
-    unit = __builtin_amdgcn_readfirstlane(start_of[6]);
+    chunk = first_past(t_incl);
+    take_chunk(chunk);
+    incl = wave_inclusive_scan(my_tiles) + __builtin_amdgcn_readlane(t_incl, chunk) - __builtin_amdgcn_readlane(t, chunk);
+    units = wave_inclusive_scan(my_units) + __builtin_amdgcn_readlane(u_incl, chunk) - __builtin_amdgcn_readlane(u, chunk);
+  }
+  // Where the range begins.  Units are numbered in session order.  The range that has a unit's first tile writes its record,
+  // block 0 those of the numbers past the last unit.  (More units than records would be lengths that break the caller's
+  // contract.)
+  const int owner = first_past(incl);
+  int s = 64 * chunk + owner;
+  int N = __builtin_amdgcn_readlane(my_N, owner);
+  int P = __builtin_amdgcn_readlane(my_P, owner);
+  int cu = __builtin_amdgcn_readlane(my_cu, owner);
+  int unit_begin = __builtin_amdgcn_readlane(incl, owner) - __builtin_amdgcn_readlane(my_tiles, owner);
+  int unit = __builtin_amdgcn_readlane(units, owner) - __builtin_amdgcn_readlane(my_units, owner);
+  int t0 = 0;
+  while (t0 + m < N && unit_begin + tiles_to(P, t0 + m) <= range_begin) {
+    unit_begin += tiles_to(P, t0 + m);
+    t0 += m;
+    ++unit;
   }
   if (blockIdx.x == 0) {
     const bool dropped = p.cu_new_lens[p.n_sessions] > p.total_new_tokens;

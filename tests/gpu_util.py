@@ -51,11 +51,17 @@ def gpu_unpack(cache: S.KVCache, ds: DeviceSessions, buf: torch.Tensor, dst: boo
                 buf, stream=stream)
 
 
+# The counts at the start of the attention workspace (kHdr* of prefill_attn.hip): pieces of the work list or of a direct call,
+# its longest piece, units the work list split, slots their chunks took, 32-key tiles of a decode step.
+HDR_ITEMS, HDR_CHUNK, HDR_SPLIT_UNITS, HDR_SLOTS, HDR_DECODE_TILES = 0, 1, 2, 3, 5
+
+
 def gpu_attention(cfg: W.WorkloadConfig, sess: W.SessionBatch, inputs, layer: int = 0, scale=None, tuning=None,
-                  max_new_len=None, expect_flags: int = 0) -> np.ndarray:
+                  max_new_len=None, expect_flags: int = 0, header=None) -> np.ndarray:
     """Run symph_prefix_prefill_attn on host inputs (one-layer pools) and return the output as numpy.  ``tuning``: an
     S.AttnTuning for the _tuned entry points; ``max_new_len``: the bound handed to the library when it is not the true
-    one.  The scheduler's flags are read back after every call and must be ``expect_flags``."""
+    one.  The scheduler's flags are read back after every call and must be ``expect_flags``; ``header``: a list that receives the
+    eight counts at the start of the workspace (HDR_*)."""
     k_pool, v_pool, q, k_new, v_new = inputs
     ds = DeviceSessions(sess)
     cache = S.KVCache(to_dev(k_pool)[None], to_dev(v_pool)[None])
@@ -69,6 +75,8 @@ def gpu_attention(cfg: W.WorkloadConfig, sess: W.SessionBatch, inputs, layer: in
                           mnl, sess.max_prefix_len, cfg.scale if scale is None else scale, workspace=ws, tuning=tuning)
     torch.cuda.synchronize()
     assert S.debug_attn_flags(ws) == expect_flags, "the device-side scheduler reported a problem"
+    if header is not None:
+        header.extend(ws[:32].view(torch.int32).tolist())
     return to_host(out)
 
 

@@ -9,7 +9,7 @@ import pytest
 
 import paper_2412_16434_amd as S
 import workloads as W
-from gpu_util import TOL, attn_errors, gpu_attention, widen
+from gpu_util import HDR_DECODE_TILES, TOL, attn_errors, gpu_attention, widen
 
 pytestmark = pytest.mark.gpu
 
@@ -210,6 +210,30 @@ def test_short_decode_steps_round_every_tile_against_its_own_maximum(hkv, group,
                         o, l = o + w @ v[j:min(j + 32, P + i + 1)], l + w.sum()
                     want[a + i, h] = f32_to_bf16(o / l)
     assert np.sqrt(np.sum((got - want) ** 2) / np.sum(want ** 2)) <= 5e-4
+
+
+@pytest.mark.parametrize("hkv,group,n_sessions,stated,long_turns", [
+    (8, 4, 65, 1, {0: 9, 64: 17}),            # one session past a chunk of 64; the long turns in both chunks
+    (8, 4, 128, 2, {63: 8, 64: 33, 127: 3}),  # two full chunks
+    (3, 8, 300, 1, {5: 64, 299: 31}),         # single-wave workgroups
+    (1, 1, 700, 1, {350: 300}),               # one turn with most of the tokens
+    (16, 2, 520, 3, {}),                      # more chunks than waves
+])
+def test_decode_ranges_of_more_than_64_sessions(oracle_mod, hkv, group, n_sessions, stated, long_turns):
+    """Above 64 sessions a workgroup finds its range by chunks of 64; half of the sessions are idle, and some turns are longer
+    than stated (several units each)."""
+    rng = np.random.default_rng(103)
+    new = rng.integers(0, 2, n_sessions)
+    for s, n in long_turns.items():
+        new[s] = n
+    assert sum(new) <= n_sessions * stated
+    cfg = _cfg(n_sessions=n_sessions, n_kv_heads=hkv, n_q_heads=hkv * group, n_blocks=n_sessions * 7 + 8,
+               prefix_dist=("uniform", 0, 90))
+    sess = W.make_sessions(cfg, 103, new_lens=new)
+    header = []
+    check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 103), label=f"{n_sessions} sessions", max_new_len=stated,
+          header=header)
+    assert header[HDR_DECODE_TILES] > 0, "no decode step"
 
 
 @pytest.mark.parametrize("hkv,group,bs,prefix,new", [
