@@ -464,12 +464,13 @@ struct MfmaParams {
   // direct mode of attn_mfma_kernel: shortest piece (tiles), workgroups the pieces are cut for, one record per unit
   int32_t direct_c_min, direct_slots, units_bound;
   MergeItem* unit_recs;
-  // attn_decode_kernel: new tokens per unit (the call's max_new_len), the rows of q / out, its ranges, one record per
+  // attn_decode_kernel: new tokens per unit, the rows of q / out, its ranges, one record per
   // unit, and the pieces of units that several ranges share
   int32_t dec_m, total_new_tokens, dec_ranges, dec_records;
   MergeItem* dec_merges;    // [dec_records]
-  float* dec_partials;      // [2 * key ranges][n_kv_heads][dec_slot_floats]
-  int32_t dec_slot_floats;  // room for the packed piece of a unit (whole lines)
+  float* dec_partials;      // [2 * key ranges][n_kv_heads][dec_slot_floats], for units of up to dec_stated tokens
+  float* dec_long_partials; // the same for longer units
+  int32_t dec_stated, dec_slot_floats, dec_long_slot_floats;  // room for the packed piece of a unit (whole lines)
 };
 
 
@@ -1263,7 +1264,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const MfmaParams p) {
 
 // ------------------------------------------------------------------------------------------------------------
 // Short turns (decode-like rows): a session whose new rows fit one wave (n_new * G <= 32) reads its whole K,V for
-// 32 query rows or fewer, so the work is moving K,V, not arithmetic.  A unit is (session, max_new_len of its new tokens):
+// 32 query rows or fewer, so the work is moving K,V, not arithmetic.  A unit is (session, up to 32 / G of its new tokens):
 // one per session, more only where the caller understated max_new_len.  The units' key ranges, laid end to end,
 // are cut into equal ranges; a workgroup takes one range for a group of kv-heads, ONE WAVE PER KV-HEAD (eight waves
 // for the usual eight heads, else single-wave workgroups).  A wave loads each 32-key tile of its head into an LDS
@@ -1280,6 +1281,20 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const MfmaParams p) {
 constexpr int kSub = 32;                    // keys per tile of this kernel
 constexpr int kSubBytes = 8 * kGroupBytes;  // 8320
 constexpr int kDecWaveBytes = 2 * kSubBytes;  // K and V of one tile, per wave
+// Slots of a unit's pieces.  Units of the stated length have slots of their own: one stride for all, of 32 rows, spread a step's
+// pieces over eight times the memory and made 96 sessions take 509 instead of 502 us.
+struct DecSlots {
+  float* head;        // slot 0 of this kv-head
+  int32_t per_slot;   // floats between slots
+  __device__ __forceinline__ DecSlots(const MfmaParams& p, int n_unit, int kvh) {
+    const bool as_stated = n_unit <= p.dec_stated;
+    const int32_t floats = as_stated ? p.dec_slot_floats : p.dec_long_slot_floats;
+    head = (as_stated ? p.dec_partials : p.dec_long_partials) + kvh * floats;
+    per_slot = p.n_kv_heads * floats;
+  }
+  __device__ __forceinline__ float* operator[](int slot) const { return head + (int64_t)slot * per_slot; }
+};
+
 template <int G, int LB, int HW>
 __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(const MfmaParams p) {
   constexpr int BMTD = 32 / G;   // query tokens this kernel covers per session
@@ -1652,7 +1667,7 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
     if (n_floats + lane < n_padded) stage[n_floats + lane] = 0.f;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    float* part = p.dec_partials + ((int64_t)pslot * Hkv + kvh) * p.dec_slot_floats;
+    float* part = DecSlots(p, n_unit, kvh)[pslot];
     for (int idx = lane; idx < n_padded; idx += 64) part[idx] = stage[idx];
     __builtin_amdgcn_wave_barrier();
   }
@@ -1692,10 +1707,8 @@ __global__ __launch_bounds__(256) void attn_decode_merge_kernel(const MfmaParams
   const int n_unit = mg.n_unit;
   const int rows = G * n_unit;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  auto piece = [&](int c) {
-    const int slot = c == 0 ? mg.pslot0 : 2 * (range + c);
-    return p.dec_partials + ((int64_t)slot * Hkv + kvh) * p.dec_slot_floats;
-  };
+  const DecSlots slots(p, n_unit, kvh);
+  auto piece = [&](int c) { return slots[c == 0 ? mg.pslot0 : 2 * (range + c)]; };
   for (int r0 = 0; r0 < rows; r0 += kMergeRows) {
     // lane l holds elements 4 * (l % 32) .. + 3 of rows r0 + 2 * i + l / 32
     f32x4 o[4];
@@ -1799,10 +1812,11 @@ static AttnTuning resolve_tuning(const symph_attn_tuning* t) {
 
 struct MfmaPlan {
   int32_t bmt, target, target_slots, c_min, coarse, units_bound, items_bound, merges_bound, pslots_bound;
-  // decode kernel: whether this call runs it (alone), its key ranges (two slots per kv-head each), its units' records
-  int32_t dec_mode, dec_wgs, dec_records, dec_slot_floats;
+  // decode kernel: whether this call runs it (alone), its key ranges (two slots per kv-head each), the new tokens of a unit,
+  // its units' records
+  int32_t dec_mode, dec_wgs, dec_m, dec_records, dec_slot_floats, dec_long_slot_floats;
   int32_t direct;  // no scheduling kernel: pslots_bound pieces at most, one record per unit
-  int64_t off_items, off_dec_merges, off_merge_cnt, off_partials, off_dec_partials, total_bytes;
+  int64_t off_items, off_dec_merges, off_merge_cnt, off_partials, off_dec_partials, off_dec_long, total_bytes;
 };
 
 constexpr int kDirectCMin = 2;  // shortest piece of a direct call, in tiles
@@ -1817,7 +1831,8 @@ static void lay_out(MfmaPlan& pl, int32_t n_kv_heads) {
   pl.off_merge_cnt = align256(pl.off_dec_merges + (int64_t)(pl.direct ? pl.units_bound : pl.dec_records) * sizeof(MergeItem));
   pl.off_partials = align256(pl.off_merge_cnt + (int64_t)pl.merges_bound * n_kv_heads * 4);
   pl.off_dec_partials = pl.off_partials + (int64_t)pl.pslots_bound * n_kv_heads * kPartialFloats * 4;
-  pl.total_bytes = pl.off_dec_partials + (int64_t)2 * pl.dec_wgs * n_kv_heads * pl.dec_slot_floats * 4;
+  pl.off_dec_long = pl.off_dec_partials + (int64_t)2 * pl.dec_wgs * n_kv_heads * pl.dec_slot_floats * 4;
+  pl.total_bytes = pl.off_dec_long + (int64_t)2 * pl.dec_wgs * n_kv_heads * pl.dec_long_slot_floats * 4;
 }
 
 // Sizes that depend only on host-visible bounds and the tuning values, so that the workspace query and the launch
@@ -1836,30 +1851,47 @@ static bool make_plan(MfmaPlan& pl, int32_t n_sessions, int32_t n_q_heads, int32
   // A batch in which no session has more new rows than one wave holds (decode steps) takes the decode kernel: one
   // equal share of the keys per workgroup, two partial-result slots per workgroup.  Mixed batches do not: their short
   // turns are memory-bound pieces that share the CUs with the compute-bound ones inside the main kernel, which
-  // measured faster than two kernels one after the other.  A session longer than max_new_len is taken max_new_len tokens
-  // at a time and its prefix is streamed once for each of them; more tokens than n_sessions * max_new_len show that the
-  // bound is wrong by more than a few such passes, and the batch is then no decode step.
+  // measured faster than two kernels one after the other.  A session longer than max_new_len is taken dec_m tokens at a time
+  // and its prefix is streamed once for each of them; more tokens than n_sessions * max_new_len show that the bound is wrong,
+  // and the batch is then no decode step.
   pl.dec_mode = tu.decode && max_new_len >= 1 && max_new_len <= 32 / G &&
                 total_new_tokens <= (int64_t)n_sessions * max_new_len;
-  // A piece has at most G * max_new_len rows of 130 values: slots of that size, in whole lines.
-  pl.dec_slot_floats = pl.dec_mode ? ((G * max_new_len * 130 + 31) & ~31) : 0;
   // ranges of the decode kernel: one wave per (range, kv-head), as many waves as decode_wgs workgroups of four would have
   pl.dec_wgs = pl.dec_mode ? (4 * tu.decode_wgs / n_kv_heads < 1 ? 1 : 4 * tu.decode_wgs / n_kv_heads) : 0;
-  // units of at most max_new_len tokens: one per token, or one per session and full max_new_len tokens
-  pl.dec_records = 0;
-  if (pl.dec_mode) {
-    const int64_t units = (int64_t)total_new_tokens / max_new_len + n_sessions;
+  pl.dec_m = pl.dec_records = pl.dec_slot_floats = pl.dec_long_slot_floats = 0;
+  // Units of m tokens: at most one per token, or one per session and full m tokens; a piece has at most G rows of 130 values
+  // per token of its unit, in a slot of whole lines.
+  auto set_unit_tokens = [&](int32_t m) {
+    const int64_t units = (int64_t)total_new_tokens / m + n_sessions;
+    pl.dec_m = m;
     pl.dec_records = (int32_t)(units < total_new_tokens ? units : total_new_tokens);
-  }
+    pl.dec_slot_floats = (G * max_new_len * 130 + 31) & ~31;
+    pl.dec_long_slot_floats = m > max_new_len ? (G * m * 130 + 31) & ~31 : 0;
+  };
   // Chunks of split units: a unit is split when it has more than C tiles, C >= total tiles * kv-heads / target, so
   // there are at most target / kv-heads split units and their chunks number at most twice that.
   pl.pslots_bound = 2 * (pl.target / n_kv_heads + 1);
-  if (pl.dec_mode) pl.units_bound = pl.pslots_bound = 0;  // no work list
+  if (pl.dec_mode) {
+    // No work list.  A unit has as many tokens as a wave has rows for, so that a session longer than stated (96 tokens over
+    // 16 384, stated as 1) is streamed 12 times and not 96: 151 instead of 600 us; shorter ones are one unit either way.
+    // Where the slots do not fit, units go down to the stated length, then the ranges are halved.
+    pl.units_bound = pl.pslots_bound = pl.direct = 0;
+    set_unit_tokens(32 / G);
+    lay_out(pl, n_kv_heads);
+    while (budget_bytes > 0 && pl.total_bytes > budget_bytes && (pl.dec_m > max_new_len || pl.dec_wgs > 1)) {
+      if (pl.dec_m > max_new_len)
+        set_unit_tokens(pl.dec_m / 2 > max_new_len ? pl.dec_m / 2 : max_new_len);
+      else
+        pl.dec_wgs /= 2;
+      lay_out(pl, n_kv_heads);
+    }
+    return budget_bytes <= 0 || pl.total_bytes <= budget_bytes;
+  }
   // Direct calls: few units, and not one long turn over a shorter prefix that would fill the chip.  (There a unit's keys
   // grow with its place in the turn, and the work list's longest-first order is worth more than the scheduling kernel:
   // 2 x 2000 new tokens over 30, 4 kv-heads: 35 us by the list, 41 without; 2 x 900 over 500, 8 heads: 44 and 47.)
   const int64_t wg_units = pl.units_bound * (int64_t)n_kv_heads;
-  pl.direct = tu.direct && !pl.dec_mode && tu.coarse && pl.units_bound <= kDirectUnits && wg_units <= tu.slots &&
+  pl.direct = tu.direct && tu.coarse && pl.units_bound <= kDirectUnits && wg_units <= tu.slots &&
               (max_new_len <= max_prefix_len || 4 * wg_units <= tu.slots);
   if (pl.direct) {
     const int32_t listed = pl.pslots_bound;
@@ -1871,13 +1903,6 @@ static bool make_plan(MfmaPlan& pl, int32_t n_sessions, int32_t n_q_heads, int32
   }
   lay_out(pl, n_kv_heads);
   if (budget_bytes <= 0 || pl.total_bytes <= budget_bytes) return true;
-  if (pl.dec_mode) {  // the ranges are halved until their pieces fit
-    while (pl.dec_wgs > 1 && pl.total_bytes > budget_bytes) {
-      pl.dec_wgs /= 2;
-      lay_out(pl, n_kv_heads);
-    }
-    return pl.total_bytes <= budget_bytes;
-  }
   // the work list gets as many partial-result slots as the room beside the uncut list holds
   const int64_t slot_bytes = (int64_t)n_kv_heads * kPartialFloats * 4;
   const int32_t wanted = pl.pslots_bound;
@@ -1972,7 +1997,7 @@ static int32_t launch_mfma(const AttnArgs& a, hipStream_t stream) {
   p.hdr = sp.hdr;
   p.items = sp.items;
   p.merge_cnt = sp.merge_cnt;
-  p.dec_m = a.max_new_len;
+  p.dec_m = pl.dec_m;
   p.total_new_tokens = a.total_new_tokens;
   p.dec_ranges = pl.dec_wgs;
   p.dec_records = pl.dec_records;
@@ -1981,7 +2006,10 @@ static int32_t launch_mfma(const AttnArgs& a, hipStream_t stream) {
   p.units_bound = pl.units_bound;
   p.dec_merges = p.unit_recs = (MergeItem*)(ws + pl.off_dec_merges);
   p.dec_partials = (float*)(ws + pl.off_dec_partials);
+  p.dec_long_partials = (float*)(ws + pl.off_dec_long);
+  p.dec_stated = a.max_new_len;
   p.dec_slot_floats = pl.dec_slot_floats;
+  p.dec_long_slot_floats = pl.dec_long_slot_floats;
   p.partials = (float*)(ws + pl.off_partials);
 
   const int64_t g_main = (int64_t)pl.items_bound * a.n_kv_heads;

@@ -236,6 +236,34 @@ def test_decode_ranges_of_more_than_64_sessions(oracle_mod, hkv, group, n_sessio
     assert header[HDR_DECODE_TILES] > 0, "no decode step"
 
 
+@pytest.mark.parametrize("hkv,group", [(8, 4), (2, 16), (1, 1)])
+def test_an_understated_turn_is_streamed_once_per_wave_of_rows(oracle_mod, hkv, group):
+    """One turn of 40 tokens stated as 1 among 60 idle sessions: units of 32 / group tokens, not of one, so its prefix is read
+    that many times less often."""
+    new = np.zeros(60, dtype=np.int64)
+    new[21] = 40
+    cfg = _cfg(n_sessions=60, n_kv_heads=hkv, n_q_heads=hkv * group, n_blocks=60 * 40 + 8, prefix_dist=("const", 600))
+    sess = W.make_sessions(cfg, 107, new_lens=new)
+    header = []
+    check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 107), label="understated", max_new_len=1, header=header)
+    ends = list(range(32 // group, 40, 32 // group)) + [40]
+    assert header[HDR_DECODE_TILES] == sum(-(-(600 + e) // 32) for e in ends)
+
+
+@pytest.mark.parametrize("hkv,group", [(8, 4), (2, 16), (1, 1)])
+def test_an_understated_turn_is_streamed_once_per_wave_of_rows(oracle_mod, hkv, group):
+    """One turn of 40 tokens stated as 1 among 60 idle sessions: units of 32 / group tokens, not of one, so its prefix is read
+    that many times less often."""
+    new = np.zeros(60, dtype=np.int64)
+    new[21] = 40
+    cfg = _cfg(n_sessions=60, n_kv_heads=hkv, n_q_heads=hkv * group, n_blocks=60 * 40 + 8, prefix_dist=("const", 600))
+    sess = W.make_sessions(cfg, 107, new_lens=new)
+    header = []
+    check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 107), label="understated", max_new_len=1, header=header)
+    ends = list(range(32 // group, 40, 32 // group)) + [40]
+    assert header[HDR_DECODE_TILES] == sum(-(-(600 + e) // 32) for e in ends)
+
+
 @pytest.mark.parametrize("hkv,group,bs,prefix,new", [
     (8, 4, 16, [3001], [45]),                            # one turn in many pieces, its last tile half empty
     (8, 4, 16, [0, 1, 63, 64, 4000], [33, 1, 32, 0, 70]),    # no prefix, no new tokens, whole and split units together
