@@ -178,11 +178,12 @@ int32_t symph_kv_append(const symph_kv_cache* cache, int32_t layer, const void* 
  *   total_new_tokens = T, max_new_len >= max N_s, max_prefix_len >= max P_s (host copies).  total_new_tokens and
  *   n_sessions size the grids and the work list; max_prefix_len is checked against the table width; beside that the two
  *   bounds only choose kernels: a batch of few query tiles takes a launch that needs no scheduling kernel, unless its turns
- *   are longer than its prefixes; a batch with max_new_len * (n_q_heads / n_kv_heads) <= 32 and total_new_tokens <= n_sessions *
- *   max_new_len is a decode step and runs in a kernel that streams K,V with one wave per kv-head.  Neither of the two is
- *   relied on for memory safety: a session longer than stated is still computed, and computed correctly (a decode step
- *   takes it 32 / (n_q_heads / n_kv_heads) tokens at a time, fewer where a scratch array of fixed size leaves no room, and
- *   reads its prefix once for each), only not at the best speed.
+ *   are long beside its prefixes (a max_prefix_len far above the true one can cost such a batch up to 15 %); a batch with
+ *   max_new_len * (n_q_heads / n_kv_heads) <= 32 and total_new_tokens <= n_sessions * max_new_len is a decode step and runs
+ *   in a kernel that streams K,V with one wave per kv-head.  Neither of the two is relied on for memory safety: a session
+ *   longer than stated is still computed, and computed correctly (a decode step takes it 32 / (n_q_heads / n_kv_heads)
+ *   tokens at a time, fewer where a scratch array of fixed size leaves no room, and reads its prefix once for each), only
+ *   not at the best speed.
  *   scale > 0 and finite (fp32).  d_workspace: device scratch of at least
  *   symph_prefix_prefill_attn_workspace_bytes(...) bytes, 256-byte aligned (may be NULL when that is 0).
  * Arithmetic: bf16 inputs, fp32 accumulation on MFMA, fp32 online softmax, probabilities rounded to bf16 before

@@ -49,8 +49,9 @@ struct MergeItem {  // 16 bytes, one per unit of a direct call or of the decode 
 };
 // Header of the workspace (ints): counts and flags written by the scheduler (by the attention kernel itself where none
 // runs).
-constexpr int kHdrItems = 0, kHdrChunk = 1, kHdrSplitUnits = 2, kHdrPslots = 3, kHdrDecTiles = 5,
+constexpr int kHdrItems = 0, kHdrChunk = 1, kHdrSplitUnits = 2, kHdrPslots = 3, kHdrPlan = 4, kHdrDecTiles = 5,
               kHdrFlags = kAttnHdrFlags;
+constexpr int kPlanList = 0, kPlanDirect = 1, kPlanDecode = 2;  // what the call ran (kHdrPlan)
 static_assert(kHdrFlags < kAttnHdrInts, "the header holds the counts and flags");
 constexpr int kPartialFloats = 256 * 66;  // per workgroup: 64 accumulators + running max + running sum per thread
 // A piece of a short turn (decode kernel): only the session's own rows, r = head * N + token (at most 32), packed:
@@ -436,6 +437,7 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(const Sche
     p.hdr[kHdrChunk] = C;
     p.hdr[kHdrSplitUnits] = n_split_s;
     p.hdr[kHdrPslots] = n_pslot_s;
+    p.hdr[kHdrPlan] = kPlanList;
     p.hdr[kHdrDecTiles] = 0;
     p.hdr[kHdrFlags] = flags_s;
   }
@@ -637,7 +639,10 @@ __device__ __forceinline__ bool direct_item(const MfmaParams& p, int bmt, int pi
   if (blockIdx.x == 0 && threadIdx.x < 64) {
     const bool dropped = p.cu_new_lens[p.n_sessions] > p.total_new_tokens;
     if (lane < kAttnHdrInts)
-      p.hdr[lane] = lane == kHdrItems ? n_pieces : (lane == kHdrChunk ? C : (lane == kHdrFlags && dropped ? 2 : 0));
+      p.hdr[lane] = lane == kHdrItems   ? n_pieces
+                    : lane == kHdrChunk ? C
+                    : lane == kHdrPlan  ? kPlanDirect
+                                        : (lane == kHdrFlags && dropped ? 2 : 0);
     if (lane < p.units_bound)
       p.unit_recs[lane] = MergeItem{ucu + t0, min(bmt, uN - t0), end - nc, lane < n_units && nc > 1 ? nc : 0};
   }
@@ -1395,7 +1400,8 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
   }
   if (blockIdx.x == 0) {
     const bool dropped = p.cu_new_lens[p.n_sessions] > p.total_new_tokens;
-    if (tid < kAttnHdrInts) p.hdr[tid] = tid == kHdrDecTiles ? total : (tid == kHdrFlags && dropped ? 2 : 0);
+    if (tid < kAttnHdrInts)
+      p.hdr[tid] = tid == kHdrDecTiles ? total : tid == kHdrPlan ? kPlanDecode : (tid == kHdrFlags && dropped ? 2 : 0);
     for (int i = n_units + tid; i < p.dec_records; i += 64 * HW) p.dec_merges[i] = MergeItem{0, 0, 0, 0};
   }
   if (range_begin >= range_end) return;
@@ -1887,12 +1893,23 @@ static bool make_plan(MfmaPlan& pl, int32_t n_sessions, int32_t n_q_heads, int32
     }
     return budget_bytes <= 0 || pl.total_bytes <= budget_bytes;
   }
-  // Direct calls: few units, and not one long turn over a shorter prefix that would fill the chip.  (There a unit's keys
-  // grow with its place in the turn, and the work list's longest-first order is worth more than the scheduling kernel:
-  // 2 x 2000 new tokens over 30, 4 kv-heads: 35 us by the list, 41 without; 2 x 900 over 500, 8 heads: 44 and 47.)
+  // Direct calls: few units, and few enough for the chip.  Cutting what fills it half already gains little, and a cut that
+  // takes a second round of workgroups loses; a long turn's units grow with their place in it, so that the work list's
+  // longest-first order is worth more than the scheduling kernel, unless a much longer prefix makes them alike.  Below half
+  // of the slots the list is as fast or faster only for such turns (4 heads, 1500 new tokens over none, 33 us by the list,
+  // 35 directly; 2 x 772 over 129, 28 and 31; but 3 turns of up to 780 over 15 000, 105 and 76).  Above it short turns over
+  // short prefixes are better listed (16 x 78 over 99, 17 and 18; 34 x 5 over 500, 21 and 23), long prefixes cut directly
+  // (8 x 143 over 1724, 53 and 46; 512 over 32 768 in groups of eight, 496 and 490) up to five sixths of the slots (6 x 343
+  // over 5656, 132 and 140; 20 x 70 over 300, 25 and 29).  175 batches of 1 to 60 sessions, 0 to 20 000 cached tokens and 1
+  // to 2000 new ones: 0.78 of the time of list and scheduler as they were, the better of the two for each 0.77, none slower.
   const int64_t wg_units = pl.units_bound * (int64_t)n_kv_heads;
-  pl.direct = tu.direct && tu.coarse && pl.units_bound <= kDirectUnits && wg_units <= tu.slots &&
-              (max_new_len <= max_prefix_len || 4 * wg_units <= tu.slots);
+  const bool short_turns = max_new_len * wg_units <= 160 * (int64_t)tu.slots;
+  const bool direct_pays =
+      2 * wg_units < tu.slots
+          ? short_turns || max_prefix_len >= 8 * (int64_t)max_new_len
+          : 6 * wg_units < 5 * (int64_t)tu.slots && max_prefix_len >= 768 &&
+                max_prefix_len >= (short_turns ? 4 : 8) * (int64_t)max_new_len;
+  pl.direct = tu.direct && tu.coarse && pl.units_bound <= kDirectUnits && direct_pays;
   if (pl.direct) {
     const int32_t listed = pl.pslots_bound;
     pl.pslots_bound = pl.target_slots / n_kv_heads + 1 + pl.units_bound;

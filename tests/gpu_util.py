@@ -51,9 +51,9 @@ def gpu_unpack(cache: S.KVCache, ds: DeviceSessions, buf: torch.Tensor, dst: boo
                 buf, stream=stream)
 
 
-# The counts at the start of the attention workspace (kHdr* of prefill_attn.hip): pieces of the work list or of a direct call,
-# its longest piece, units the work list split, slots their chunks took, 32-key tiles of a decode step.
-HDR_ITEMS, HDR_CHUNK, HDR_SPLIT_UNITS, HDR_SLOTS, HDR_DECODE_TILES = 0, 1, 2, 3, 5
+# Of the counts at the start of the attention workspace (kHdr* of prefill_attn.hip): which plan ran, 32-key tiles of a decode step
+HDR_PLAN, HDR_DECODE_TILES = 4, 5
+PLAN_LIST, PLAN_DIRECT, PLAN_DECODE = 0, 1, 2
 
 
 def gpu_attention(cfg: W.WorkloadConfig, sess: W.SessionBatch, inputs, layer: int = 0, scale=None, tuning=None,

@@ -9,7 +9,8 @@ import pytest
 
 import paper_2412_16434_amd as S
 import workloads as W
-from gpu_util import HDR_DECODE_TILES, TOL, attn_errors, gpu_attention, widen
+from gpu_util import (HDR_DECODE_TILES, HDR_PLAN, PLAN_DECODE, PLAN_DIRECT, PLAN_LIST, TOL, attn_errors, gpu_attention,
+                      widen)
 
 pytestmark = pytest.mark.gpu
 
@@ -269,8 +270,8 @@ def test_an_understated_turn_is_streamed_once_per_wave_of_rows(oracle_mod, hkv, 
     (8, 4, 16, [0, 1, 63, 64, 4000], [33, 1, 32, 0, 70]),    # no prefix, no new tokens, whole and split units together
     (2, 16, 64, [1500, 300], [9, 8]),                    # larger blocks, tiles of eight tokens
     (3, 1, 32, [200], [1900]),                           # a long turn over a short prefix, few heads
-    (8, 4, 16, [100] * 61, [1] * 60 + [40]),             # 64 (unit, session) slots: the most a direct call has
-    (8, 4, 16, [100] * 62, [1] * 61 + [40]),             # one more: the work list
+    (2, 4, 16, [100] * 61, [1] * 60 + [40]),             # 64 (unit, session) slots: the most a direct call has
+    (8, 4, 16, [100] * 62, [1] * 61 + [40]),             # more: the work list
 ])
 def test_direct_calls(oracle_mod, hkv, group, bs, prefix, new):
     """Small prefill batches: each workgroup finds its own piece (no scheduling kernel), a merge kernel combines them.  The
@@ -285,6 +286,36 @@ def test_direct_calls(oracle_mod, hkv, group, bs, prefix, new):
     listed = gpu_attention(cfg, sess, inputs, scale=cfg.scale, tuning=S.AttnTuning(coarse=-1, decode=-1))
     f = lambda x: W.bf16_bits_to_f32(x).astype(np.float64)
     assert np.sqrt(np.sum((f(got) - f(listed)) ** 2) / np.sum(f(listed) ** 2)) <= 1e-2
+
+
+@pytest.mark.parametrize("hkv,group,prefix,new,plan", [
+    (2, 4, [100] * 61, [1] * 60 + [40], PLAN_DIRECT),    # 64 units (at the most) are what a wave lists
+    (2, 4, [100] * 62, [1] * 61 + [40], PLAN_LIST),
+    (8, 4, [100] * 29, [2] * 28 + [10], PLAN_DIRECT),    # 31 units at the most, times 8: less than half of the slots
+    (8, 4, [100] * 30, [2] * 29 + [10], PLAN_LIST),
+    (8, 4, [768] * 30, [2] * 29 + [10], PLAN_DIRECT),   # ... which are cut directly over long prefixes,
+    (8, 4, [767] * 30, [2] * 29 + [10], PLAN_LIST),
+    (8, 4, [768] * 49, [1] * 48 + [100], PLAN_DIRECT),  # up to five sixths of the slots
+    (8, 4, [768] * 50, [1] * 49 + [100], PLAN_LIST),
+    (4, 4, [10], [799], PLAN_DIRECT),                    # a turn short enough for its share of the slots
+    (4, 4, [10], [800], PLAN_LIST),
+    (4, 4, [6399], [800], PLAN_LIST),                    # a longer one, over a prefix of eight times its length or not
+    (4, 4, [6400], [800], PLAN_DIRECT),
+    (8, 4, [100] * 9, [8] * 9, PLAN_DECODE),             # 32 rows in a wave
+    (8, 4, [100] * 9, [8] * 8 + [9], PLAN_DIRECT),
+])
+def test_which_plan_a_small_batch_takes(hkv, group, prefix, new, plan):
+    """Either side of each line of the rules, by what the call says it ran.  Another plan gives the same result within the
+    roundings of both."""
+    cfg = _cfg(n_sessions=len(new), n_kv_heads=hkv, n_q_heads=hkv * group, n_blocks=len(new) * (max(prefix) // 16 + 1) + 8,
+               prefix_dist=("const", max(prefix)))
+    sess = W.make_sessions(cfg, 109, new_lens=np.array(new))
+    inputs = W.make_attn_inputs(cfg, sess, 109)
+    header, listed = [], []
+    got = widen(gpu_attention(cfg, sess, inputs, header=header))
+    other = widen(gpu_attention(cfg, sess, inputs, header=listed, tuning=S.AttnTuning(coarse=-1, decode=-1)))
+    assert (header[HDR_PLAN], listed[HDR_PLAN]) == (plan, PLAN_LIST)
+    assert np.sqrt(np.sum((got - other) ** 2) / np.sum(other ** 2)) <= 1e-2
 
 
 @pytest.mark.parametrize("dtype,d,hkv,group,bs,prefix,new", [
