@@ -127,6 +127,54 @@ def test_session_lookups(oracle_mod, hkv, d, dtype, prefix):
     assert to_host(dcache.k_pool).tobytes() == ks.tobytes() and to_host(dcache.v_pool).tobytes() == vs.tobytes()
 
 
+@pytest.mark.parametrize("hkv,d,dtype,lens", [
+    (2, 64, "bf16", [33] + [0] * 4000 + [31]),                 # 256-byte rows: one wave lies on both sides of 4000 empty sessions
+    (1, 64, "bf16", [3] + ([0] * 300 + [2, 1]) * 12 + [0] * 7),    # 128-byte rows, eight tokens per wave
+    (3, 64, "fp32", [1] + [0] * 1023 + [1, 1] + [0] * 64 + [1]),   # 768-byte rows
+])
+def test_long_runs_of_empty_sessions(hkv, d, dtype, lens):
+    """Short rows around sessions that move nothing: the same bytes as without those sessions, by all three calls, and not as
+    many trips to memory one after the other as there are empty sessions (a hundred of those trips take 7 us)."""
+    import time
+    live = [n for n in lens if n]
+    total, rng = sum(lens), np.random.default_rng(93)
+    table_live = torch.from_numpy(rng.permutation(3 * len(live)).astype(np.int32).reshape(len(live), 3)).to(DEV)
+    table = torch.full((len(lens), 3), -1, dtype=torch.int32, device=DEV)
+    table[torch.tensor([i for i, n in enumerate(lens) if n], device=DEV)] = table_live
+    shape = (2, 3 * len(live), 16, hkv, d)
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    k_pool, v_pool = (torch.randn(shape, device=DEV).to(t) for _ in range(2))
+    fresh = [torch.randn((total, hkv, d), device=DEV).to(t) for _ in range(2)]
+
+    def run(ls, tab):
+        at = np.concatenate([[0], np.cumsum(ls)])
+        n = torch.tensor(ls, dtype=torch.int32, device=DEV)
+        off, cu = torch.from_numpy(at.astype(np.int64)).to(DEV), torch.from_numpy(at.astype(np.int32)).to(DEV)
+        buf = torch.zeros(total * 4 * hkv * d, dtype=t, device=DEV)
+        back, app = (S.KVCache(torch.zeros_like(k_pool), torch.zeros_like(v_pool)) for _ in range(2))
+        calls = (lambda: S.kv_pack(S.KVCache(k_pool, v_pool), tab, n, off, total, buf),
+                 lambda: S.kv_unpack(back, tab, n, off, total, buf),
+                 lambda: S.kv_append(app, 1, *fresh, cu, torch.zeros_like(n), tab))
+        best = []
+        for call in calls:
+            times = []
+            for _ in range(5):
+                torch.cuda.synchronize()
+                t0 = time.perf_counter()
+                for _ in range(20):
+                    call()
+                torch.cuda.synchronize()
+                times.append((time.perf_counter() - t0) / 20)
+            best.append(min(times))
+        return [buf, back.k_pool, back.v_pool, app.k_pool, app.v_pool], best
+    (alone, t_alone), (among, t_among) = run(live, table_live), run(lens, table)
+    for a, b in zip(alone, among):
+        assert torch.equal(a, b)
+    assert alone[0].any() and alone[3].any()
+    for a, b in zip(t_alone, t_among):
+        assert b <= a + 100e-6, (a, b)
+
+
 @pytest.mark.parametrize("tokens", [1, 15, 16, 17, 31, 33, 47, 100])
 def test_workgroup_to_token_mappings(oracle_mod, tokens):
     """The mappings of workgroups to the token space (XCD-contiguous for the gather, identity for the scatter) on the
