@@ -276,7 +276,7 @@ static int32_t launch_rows(const MigrateParams& p_in, hipStream_t stream) {
   const int64_t gy = ceil_div64(p_in.plane_end - p_in.plane_begin, PLANES);
   if (gx > 0x7FFFFFFFLL || gy > 65535) return SYMPH_EUNSUPPORTED;
   MigrateParams p = p_in;
-  p.xcd_chunk = (int32_t)(gx / 8);
+  p.xcd_chunk = PACK ? (int32_t)(gx / 8) : 0;
   hipLaunchKernelGGL((kv_migrate_rows_kernel<VecT, PACK, ROWS, PLANES, kMigrateNT>), dim3((unsigned)gx, (unsigned)gy),
                      dim3(256), 0, stream, p);
   return hipGetLastError() == hipSuccess ? SYMPH_OK : SYMPH_ELAUNCH;
@@ -285,14 +285,14 @@ static int32_t launch_rows(const MigrateParams& p_in, hipStream_t stream) {
 template <typename VecT, bool PACK>
 static int32_t launch_planes(int planes, const MigrateParams& p_in, hipStream_t stream) {
   // Measured on MI355X, gather with one plane per lane: two consecutive tokens per wave, i.e. one session search for two
-  // loads, 16 sessions 5.8 -> 6.1 TB/s; four the same, eight a cliff (3.1 TB/s); a single session has no search to share
-  // (6.08 -> 5.99).  Scatter of several layers: two tokens per wave, one plane, the XCD-contiguous mapping.  What the scatter
-  // reaches depends on where the driver places the pools and the buffer (a library that is a megabyte larger moves them):
-  // 18 GB of 16 sessions take 3080 to 3200 us in this form wherever that is, and 2880 to 3390 with two planes per lane in
-  // the plain order (mean of six processes 3134 and 3185; a 128 GiB pool, 8.6 GB: 2.65 or 2.93 ms, this form 2.85 where the
-  // other takes 2.93).  Everything that widens the set of rows under way at once loses: 8 / 64 planes per wave in a software
-  // pipeline, gather 3040 -> 3306 / 3491 us, scatter 3390 -> 3484 / 3607.
-  if (planes == 1 && p_in.row_shift >= 6 && (!PACK || p_in.n_sessions > 1)) return launch_rows<VecT, PACK, 2, 1>(p_in, stream);
+  // loads, 16 sessions 5.8 -> 6.1 TB/s; four the same, eight a cliff (3.1 TB/s); nothing to gain with a single session (no
+  // search to share: 6.08 -> 5.99) or in the two-plane form.  The scatter in that form, with the XCD-contiguous mapping, gains
+  // and loses by where the driver places pools and buffer (in a fresh process, or with 37 to 90 GiB held by others): 16
+  // sessions of 4096 tokens take 2960 to 3020 us wherever that is, and 3140 or 2590 with two planes per lane in the plain
+  // order; 256 of 600, 6940 to 7480 and 7590 or 6190; the 16 chats (18 GB) 3160 to 3190 and 3300 to 3390.  Everything that
+  // widens the set of rows under way at once loses: 8 / 64 planes per wave in a software pipeline, gather 3040 -> 3306 /
+  // 3491 us, scatter 3390 -> 3484 / 3607.
+  if (PACK && planes == 1 && p_in.row_shift >= 6 && p_in.n_sessions > 1) return launch_rows<VecT, PACK, 2, 1>(p_in, stream);
   const int64_t n_vec = p_in.total_tokens * p_in.vecs_per_row;
   const int64_t gx = ceil_div64(n_vec, 256);
   const int64_t gy = ceil_div64(p_in.plane_end - p_in.plane_begin, planes);
@@ -355,15 +355,10 @@ int32_t launch_kv_migrate(bool pack, const symph_kv_cache* c, int32_t layer_begi
 
   // Planes per lane.  One plane (and two tokens per wave, launch_planes) for the gather of long rows (a whole number of
   // waves) while its session search is short: 16 sessions 6.1 TB/s against 5.8 with two, 256 sessions 5.6 against 5.9; four
-  // planes 5.5 and 5.7, eight 3.0.  For the scatter of long rows with more than one layer and 64 tokens a session or more
-  // (64 sessions of 28: 80 us with two planes, 87 so; 256 units of one layer: 1.6 ms and 2.2), in pools of up to 32 GiB each:
-  // 8 sessions in 4 GiB pools 5.7 TB/s against 5.6, one in 20 GiB 5.8 and 5.5, 256 in 32 GiB 5.4 and 5.3, 16 in 64 GiB 6.0
-  // and 6.5 or 5.9.  Short rows have a lookup per lane, which two planes share: 16 sessions with 256-byte rows, gather 638
+  // planes 5.5 and 5.7, eight 3.0.  Two for the scatter: 16 sessions 6.5 against 5.9 with one, a single one 6.2 and 5.5, four
+  // planes 6.3 and 6.2.  Short rows have a lookup per lane, which two planes share: 16 sessions with 256-byte rows, gather 638
   // -> 363 us (four planes 377).
-  const bool one = pack ? n_sessions <= 64
-                        : p.plane_end - p.plane_begin > 2 && total_tokens >= (int64_t)64 * n_sessions &&
-                              p.layer_stride_b <= ((int64_t)32 << 30) / c->n_layers;
-  const int planes = p.row_shift >= 6 && one ? 1 : 2;  // (a launch covers whole layers: two planes at least)
+  const int planes = pack && p.row_shift >= 6 && n_sessions <= 64 ? 1 : 2;  // (a launch covers whole layers: two at least)
 
   if (vec == 16) return pack ? launch_planes<u32x4, true>(planes, p, stream) : launch_planes<u32x4, false>(planes, p, stream);
   return pack ? launch_planes<unsigned int, true>(planes, p, stream) : launch_planes<unsigned int, false>(planes, p, stream);

@@ -94,9 +94,9 @@ def test_pack_unpack_edge_cases(oracle_mod, kw):
     (2, 64, "bf16", [3, 0, 0, 1, 2, 5, 0, 9, 1, 1]),           # 256-byte rows: several sessions in one wave, empty ones too
     (1, 64, "bf16", [0, 130, 1, 0, 64, 65]),                   # 128-byte rows, eight tokens per wave
     (3, 64, "fp32", [7, 33, 0, 16]),                           # 768-byte rows: a wave holds parts of two tokens
-    (8, 64, "bf16", [63, 65, 0, 200, 1]),                      # 1-KiB rows: two tokens per wave both ways
-    (8, 128, "bf16", [1, 2, 0, 3, 60]),                        # fewer than 64 tokens a session
-    (8, 128, "bf16", [5] * 3 + [400] + [0] * 66),              # more than 64 sessions
+    (8, 64, "bf16", [63, 65, 0, 200, 1]),                      # 1-KiB rows: two tokens per wave of the gather
+    (8, 128, "bf16", [1, 2, 0, 3, 60]),                        # a wave of the gather on both sides of an empty session
+    (8, 128, "bf16", [5] * 3 + [400] + [0] * 66),              # more than 64 sessions: the gather with two planes
 ])
 def test_session_lookups(oracle_mod, hkv, d, dtype, prefix):
     cfg = W.WorkloadConfig(name="lookup", index=90, dtype=dtype, n_layers=3, n_q_heads=hkv, n_kv_heads=hkv, head_dim=d,
