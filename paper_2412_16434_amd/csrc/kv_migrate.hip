@@ -261,14 +261,6 @@ __global__ __launch_bounds__(256) void kv_migrate_rows_kernel(const MigrateParam
 // Non-temporal loads and stores (every byte is touched once): bit 0 loads, bit 1 stores.
 constexpr int kMigrateNT = 3;
 
-template <typename VecT, bool PACK, int PLANES>
-static void launch_uniform(dim3 grid, const MigrateParams& p, hipStream_t stream) {
-  if (p.row_shift >= 6)  // a row is a whole number of waves: scalar session search and table read
-    hipLaunchKernelGGL((kv_migrate_kernel<VecT, PACK, PLANES, kMigrateNT, true>), grid, dim3(256), 0, stream, p);
-  else
-    hipLaunchKernelGGL((kv_migrate_kernel<VecT, PACK, PLANES, kMigrateNT, false>), grid, dim3(256), 0, stream, p);
-}
-
 template <typename VecT, bool PACK, int ROWS, int PLANES>
 static int32_t launch_rows(const MigrateParams& p_in, hipStream_t stream) {
   const int64_t n_vec = ceil_div64(p_in.total_tokens, ROWS) * p_in.vecs_per_row;
@@ -282,6 +274,7 @@ static int32_t launch_rows(const MigrateParams& p_in, hipStream_t stream) {
   return hipGetLastError() == hipSuccess ? SYMPH_OK : SYMPH_ELAUNCH;
 }
 
+// planes: 1 for the gather of rows that fill whole waves, else 2
 template <typename VecT, bool PACK>
 static int32_t launch_planes(int planes, const MigrateParams& p_in, hipStream_t stream) {
   // Measured on MI355X, gather with one plane per lane: two consecutive tokens per wave, i.e. one session search for two
@@ -292,7 +285,9 @@ static int32_t launch_planes(int planes, const MigrateParams& p_in, hipStream_t 
   // order; 256 of 600, 6940 to 7480 and 7590 or 6190; the 16 chats (18 GB) 3160 to 3190 and 3300 to 3390.  Everything that
   // widens the set of rows under way at once loses: 8 / 64 planes per wave in a software pipeline, gather 3040 -> 3306 /
   // 3491 us, scatter 3390 -> 3484 / 3607.
-  if (PACK && planes == 1 && p_in.row_shift >= 6 && p_in.n_sessions > 1) return launch_rows<VecT, PACK, 2, 1>(p_in, stream);
+  if constexpr (PACK) {
+    if (planes == 1 && p_in.n_sessions > 1) return launch_rows<VecT, PACK, 2, 1>(p_in, stream);
+  }
   const int64_t n_vec = p_in.total_tokens * p_in.vecs_per_row;
   const int64_t gx = ceil_div64(n_vec, 256);
   const int64_t gy = ceil_div64(p_in.plane_end - p_in.plane_begin, planes);
@@ -302,10 +297,16 @@ static int32_t launch_planes(int planes, const MigrateParams& p_in, hipStream_t 
   // measured on MI355X (16 sessions): the gather gains 2-3 % from the XCD-contiguous mapping, the scatter loses 7 % in the
   // good placements and gains 1 % in the others
   p.xcd_chunk = PACK ? (int32_t)(gx / 8) : 0;
-  if (planes == 1)
-    launch_uniform<VecT, PACK, 1>(grid, p, stream);
+  if constexpr (PACK) {
+    if (planes == 1) {
+      hipLaunchKernelGGL((kv_migrate_kernel<VecT, PACK, 1, kMigrateNT, true>), grid, dim3(256), 0, stream, p);
+      return hipGetLastError() == hipSuccess ? SYMPH_OK : SYMPH_ELAUNCH;
+    }
+  }
+  if (p.row_shift >= 6)  // a row is a whole number of waves: scalar session search and table read
+    hipLaunchKernelGGL((kv_migrate_kernel<VecT, PACK, 2, kMigrateNT, true>), grid, dim3(256), 0, stream, p);
   else
-    launch_uniform<VecT, PACK, 2>(grid, p, stream);
+    hipLaunchKernelGGL((kv_migrate_kernel<VecT, PACK, 2, kMigrateNT, false>), grid, dim3(256), 0, stream, p);
   return hipGetLastError() == hipSuccess ? SYMPH_OK : SYMPH_ELAUNCH;
 }
 
