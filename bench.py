@@ -566,7 +566,7 @@ def measure_config(args, name: str) -> dict:
     out["prefix_prefill_attn"] = {**_attn_figures(sess, attn_ms), "sessions": sess.n_sessions,
                                   "new_tokens": sess.total_new_tokens, "prefix_tokens": sess.total_prefix_tokens}
     if cfg.dtype != "bf16":
-        out["prefix_prefill_attn"]["note"] = "fp32 runs the plain one-wave-per-row kernel: correctness path, no roofline claim"
+        out["prefix_prefill_attn"]["note"] = "fp32 runs the kernel without a work list (fp32 matrix instruction): correctness path, no roofline claim"
     del acache, k_pool, v_pool, ws
     torch.cuda.empty_cache()
     return out

@@ -189,9 +189,10 @@ int32_t symph_kv_append(const symph_kv_cache* cache, int32_t layer, const void* 
  * Arithmetic: bf16 inputs, fp32 accumulation on MFMA, fp32 online softmax, probabilities rounded to bf16 before
  * the P*V product, output rounded to nearest even; fp32 inputs are computed in fp32 throughout.
  * Supported: head_dim 64 or 128; n_q_heads a multiple of n_kv_heads.  Sessions with N_s == 0 produce no rows;
- * P_s == 0 is a plain causal prefill.  The matrix-core kernels cover bf16, head_dim 128, group sizes 1, 2, 4, 8, 16 and
- * block sizes that are powers of two >= 16; every other supported shape (fp32, head_dim 64, other group sizes, smaller
- * blocks) runs a kernel without a work list, which keeps probabilities in 32 bits; its workspace query returns 0.
+ * P_s == 0 is a plain causal prefill.  bf16 with head_dim 128, group sizes 1, 2, 4, 8, 16 and block sizes that are powers of
+ * two >= 16 runs the kernels described so far; every other supported shape (fp32, head_dim 64, other group sizes, smaller
+ * or odd blocks) runs a matrix-core kernel without a work list, which keeps probabilities in 32 bits (pointers or strides
+ * that are no multiple of 16 bytes: one wave per row on the vector unit); its workspace query returns 0.
  */
 int32_t symph_prefix_prefill_attn(const symph_kv_cache* cache, int32_t layer, const void* d_q, const void* d_k_new,
                                   const void* d_v_new, void* d_out, const int32_t* d_cu_new_lens,
@@ -213,9 +214,10 @@ int64_t symph_prefix_prefill_attn_workspace_bytes(const symph_kv_cache* cache, i
  */
 typedef struct {
   int32_t slots;       /* workgroups resident on the GPU at once, which the work list is balanced for (default 512) */
-  int32_t c_min;       /* shortest piece of a (session, query tile) unit that is split, in 64-key tiles (default 8) */
+  int32_t c_min;       /* shortest piece of a (session, query tile) unit that is split, in 64-key tiles (default 8; 2 in
+                          batches of few query tiles that run without a scheduling kernel) */
   int32_t coarse;      /* > 0 (default): with at least two units per slot only the longest units are split; < 0: every
-                          unit is cut so that there are about two pieces per slot */
+                          unit is cut so that there are about two pieces per slot, always by the scheduling kernel */
   int32_t decode;      /* > 0 (default): decode steps (see max_new_len above) take the streaming kernel; < 0: never */
   int32_t decode_wgs;  /* that kernel runs 4 * decode_wgs waves, one per (key range, kv-head): 4 * decode_wgs /
                           n_kv_heads ranges (default 512: with 8 kv-heads one 8-wave workgroup per compute unit) */

@@ -60,9 +60,12 @@ int32_t symph_prefix_prefill_attn_static(const symph_kv_cache* cache, int32_t la
   void* ws = nullptr;
   const int32_t rc = static_scratch(&ws);
   if (rc != SYMPH_OK) return rc;
-  // fit_workspace: the work list is cut so that its partial results fit the array; SYMPH_EWORKSPACE if the list of
-  // query tiles alone does not.  Nothing is cleared here: the scheduling kernel rewrites every count, counter and the
-  // page of zeros at the start of each call, and nothing else is read before it is written.
+  // fit_workspace: the plan is made to fit the array (a coarser cut of the work list, shorter units and fewer ranges of a decode
+  // step); SYMPH_EWORKSPACE if the list of query tiles alone does not.  Nothing is cleared here, because a call reads nothing
+  // that it has not written.  Work list: the scheduling kernel writes the header, every item up to the count in it and all
+  // counters of split units.  Direct call: workgroup 0 writes the header and one record for each unit of the plan.  Decode
+  // step: workgroup 0 writes the header and the records past the last unit, the range that holds a unit's first tile that
+  // unit's.  Partial results are read only from the slots that these name, after they have been written.
   return prefill_attn_entry(cache, layer, d_q, d_k_new, d_v_new, d_out, d_cu_new_lens, d_prefix_lens, d_block_table,
                             table_stride, n_sessions, n_q_heads, total_new_tokens, max_new_len, max_prefix_len, scale,
                             ws, kStaticScratchBytes, stream, nullptr, true);

@@ -70,10 +70,10 @@ def _cfg(**kw):
     dict(n_q_heads=4, n_kv_heads=2),                                        # G = 2
     dict(n_q_heads=16, n_kv_heads=2, new_dist=("uniform", 1, 40)),          # G = 8
     dict(n_q_heads=32, n_kv_heads=2, new_dist=("uniform", 1, 20)),          # G = 16
-    dict(n_q_heads=6, n_kv_heads=2),                                        # G = 3: generic path
+    dict(n_q_heads=6, n_kv_heads=2),                                        # G = 3: no work list
     dict(block_size=8, n_blocks=512),
     dict(block_size=32, n_blocks=128),
-    dict(head_dim=64, scale=0.125),                                         # bf16 d=64: generic path
+    dict(head_dim=64, scale=0.125),                                         # bf16 d=64: no work list
     dict(dtype="fp32", head_dim=128),
     dict(dtype="fp32", head_dim=64, n_q_heads=4, scale=0.125, prefix_dist=("uniform", 1, 500)),
 ])
