@@ -136,10 +136,11 @@ __global__ __launch_bounds__(64) void attn_row_kernel(const RowsParams p) {
 //
 // Measured against one wave per row (attn_row_kernel above, 32-bit arithmetic on the vector unit, lanes over keys): six
 // sessions of 300 to 2000 tokens, 64-wide heads, 380 -> 19 us; one fp32 session of 256 tokens, 24.6 -> 9.9 us, which is the
-// call itself; three fp32 sessions of 8192, 775 -> 193; 16 of 2000 to 4000 with 64-wide heads, 12 805 -> 260.  The error
-// against 64 bits is the same in bf16 and lower in fp32 (2.9e-7 for 4.7e-7 at 128 x 8000 keys).  A block's 32 MFMAs and the
-// exponentials are matched by as many vector instructions again for the split and the addresses, so the vector unit bounds
-// a full chip and the chain load -> product -> softmax -> product a small call.
+// call itself; three fp32 sessions of 8192, 775 -> 193; 100 new tokens of eight sessions of 2000 with 64-wide heads,
+// 1949 -> 56.  The error against 64 bits is the same in bf16 and lower in fp32 (2.9e-7 for 4.7e-7 at 128 x 8000 keys).  A
+// small call is a chain load -> product -> softmax -> product: in the first of these a wave issues in 44 % of its cycles,
+// vector instructions in 29 %, and the matrix cores are busy for 8 % of the launch.  On a full chip the vector unit counts,
+// which has as many instructions for the split and the addresses as for the exponentials.
 //
 // K goes from memory straight into operand registers: a row's D values are the operand's contraction index, and any order
 // of it will do as long as Q has the same.  V is needed transposed: in bf16 through LDS (a tile of the wave's own, rows
@@ -603,9 +604,10 @@ static int32_t launch_rows(const AttnArgs& a, hipStream_t stream) {
   // The tiled kernel loads 16 bytes at a time.  (A row of a head is a multiple of that, so the bases and the block stride
   // decide.)
   // Eight waves a tile give the shortest chain of key blocks to a call that does not fill the chip.  With more tiles than
-  // compute units, four waves each (two or three workgroups then share a compute unit) leave a last round less empty:
-  // eight / four waves 28 / 24 us at 504 tiles, 129 / 71 and 305 / 215 at 3100 to 3600; 35 / 49 and 193 / 259 at 112 and
-  // 30 tiles.  (Two waves with over 512 tiles: within 6 % either way.)
+  // compute units, four waves each (two or three workgroups then share a compute unit) leave a last round less empty.  Eight
+  // / four waves, sessions of 1000 tokens, bf16 with 64-wide heads: 12.7 / 14.0 us at 112 tiles, 36 / 26 at 264, 50 / 34 at
+  // 504, 399 / 283 at 3200; fp32 with 128-wide heads: 39 / 51, 104 / 106, 158 / 139, 963 / 819; 32 tiles of 8000 keys 51 / 74
+  // and 204 / 268.  (Just below the line, at 248 tiles, four are ahead already: 26 / 20 and 74 / 67.)
   if ((address_bits & 15) == 0 && groups <= 0x7FFFFFFFLL) {
     if (groups <= kComputeUnits)
       hipLaunchKernelGGL((attn_rows_kernel<T, D, 8>), dim3((unsigned)groups), dim3(512), 0, stream, p);
