@@ -25,9 +25,8 @@ __device__ __forceinline__ float to_f32(__bf16 x) { return (float)x; }
 __device__ __forceinline__ void from_f32(float* p, float x) { *p = x; }
 __device__ __forceinline__ void from_f32(__bf16* p, float x) { *p = (__bf16)x; }
 
-// ---- one wave per (token, query head), lanes over keys, fp32 throughout.  q_s: D floats in LDS of the wave's own.  CH
-// output columns at a time (the scores are worked out again for each: where registers matter more than time: 64 columns
-// for the rows worked out again by the tiled kernel made it spill 90 scalar registers).
+// ---- one wave per (token, query head), lanes over keys, fp32 throughout.  q_s: 2 * D floats in LDS of the wave's own (q, the
+// result).  CH output columns at a time (the scores are worked out again for each: where registers matter more than time).
 template <typename T, int D, int CH>
 __device__ __forceinline__ void row_by_lanes(const RowsParams& p, int32_t s, int32_t tok, int32_t h, float* q_s) {
   const int lane = threadIdx.x & 63;
@@ -100,15 +99,18 @@ __device__ __forceinline__ void row_by_lanes(const RowsParams& p, int32_t s, int
       float a = acc[c] * f;
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) a += __shfl_xor(a, o);
-      if (lane == ((c0 + c) & 63)) from_f32(out + c0 + c, a * inv);
+      if (lane == 0) q_s[D + c0 + c] = a * inv;  // (a store by lane c each would keep CH lane masks in scalar registers)
     }
   }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  for (int c = lane; c < D; c += 64) from_f32(out + c, q_s[D + c]);
 }
 
 // Addresses that the tiled kernel below cannot load 16 bytes wide from.
 template <typename T, int D>
 __global__ __launch_bounds__(64) void attn_row_kernel(const RowsParams p) {
-  __shared__ float q_s[D];
+  __shared__ float q_s[2 * D];
   const int64_t row = blockIdx.x;  // (token, head)
   const int32_t tok = (int32_t)(row / p.n_q_heads);
   int32_t lo = 0, hi = p.n_sessions;  // session with cu[s] <= tok < cu[s+1]
@@ -240,7 +242,7 @@ __device__ __forceinline__ void combine_rows(const RowsParams& p, char* lds, con
     if (turn++ % W != wave) continue;
     const int64_t row = row0 + __builtin_ctz(left);
     const int tok = (int)(row / G);
-    row_by_lanes<T, D, 32>(p, s, cu_s + tok, kvh * G + (int)(row - (int64_t)tok * G), all + wave * D);
+    row_by_lanes<T, D, 64>(p, s, cu_s + tok, kvh * G + (int)(row - (int64_t)tok * G), all + wave * 2 * D);
   }
 }
 
