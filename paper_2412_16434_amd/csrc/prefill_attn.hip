@@ -1694,16 +1694,19 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
 // out = sum_c w_c O_c / sum_c w_c l_c with w_c = 2^(m_c - max_c m_c), m_c being the piece's softmax reference in log2
 // units (-inf: the piece saw no key of the row).  The first piece is in slot pslot0, piece c >= 1 in the even slot of
 // the c-th range after the one that wrote pslot0.
-// One workgroup per (record, kv-head), eight rows at a time.  Wave w takes pieces w, w + 4, ..: a step that decodes a few
-// long sessions cuts them into tens of pieces each, and a thread that reads them one after the other waits for memory
-// every time (one session of 1777 tokens in 56 pieces: 50 us; this way 8 us).
+// A workgroup takes RW rows of a (record, kv-head) at a time: half-wave h has row h % RW of them and every (8 / RW)-th piece
+// from h / RW on, eight in flight.  A merge is nothing but trips to memory, so few units get a workgroup per row, which asks
+// for up to 64 pieces at once: one session of 1777 tokens in 56 pieces, 50 us by a thread that read one piece after the
+// other, 8 us by four waves that asked for sixteen at once, 3.7 us this way.  Many units have few pieces each and get
+// four rows per workgroup: fewer workgroups, no half-wave without a piece to read.
 // Records are per unit, not per key range, so that the grid follows the batch: 8 instead of 2048 workgroups for one session
 // (14.9 -> 14.4 us with the lengths added up inside a wave for up to 64 sessions, without a barrier).
-constexpr int kMergeRows = 8;
-template <int G>
+template <int G, int RW>
 __global__ __launch_bounds__(256) void attn_decode_merge_kernel(const MfmaParams p) {
-  __shared__ float part_o[4][kMergeRows * 128];
-  __shared__ float part_m[4][kMergeRows], part_l[4][kMergeRows];
+  constexpr int kParts = 8 / RW;  // half-waves per row
+  constexpr int kAtOnce = 8;
+  __shared__ f32x4 part_o[8][32];
+  __shared__ float part_m[8], part_l[8];
   const int Hkv = p.n_kv_heads;
   const int record = blockIdx.x / Hkv;
   const MergeItem mg = p.dec_merges[record];
@@ -1712,86 +1715,73 @@ __global__ __launch_bounds__(256) void attn_decode_merge_kernel(const MfmaParams
   const int range = mg.pslot0 >> 1;
   const int n_unit = mg.n_unit;
   const int rows = G * n_unit;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int half = threadIdx.x >> 5, c4 = threadIdx.x & 31;  // columns 4 * c4 .. + 3
   const DecSlots slots(p, n_unit, kvh);
   auto piece = [&](int c) { return slots[c == 0 ? mg.pslot0 : 2 * (range + c)]; };
-  for (int r0 = 0; r0 < rows; r0 += kMergeRows) {
-    // lane l holds elements 4 * (l % 32) .. + 3 of rows r0 + 2 * i + l / 32
-    f32x4 o[4];
-    float m_run[4], l_run[4];
-    int row[4];
+  for (int r0 = RW * blockIdx.y; r0 < rows; r0 += RW * gridDim.y) {
+    const int row = r0 + half % RW;
+    f32x4 o{0.f, 0.f, 0.f, 0.f};
+    float m_run = -INFINITY, l_run = 0.f;
+    for (int c0 = half / RW; c0 < mg.n_chunks; c0 += kParts * kAtOnce) {
+      f32x4 oc[kAtOnce];
+      float mc[kAtOnce], lc[kAtOnce];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-      m_run[i] = -INFINITY;
-      l_run[i] = 0.f;
-      row[i] = r0 + 2 * i + (lane >> 5);
-    }
-    for (int c0 = wave; c0 < mg.n_chunks; c0 += 16) {  // pieces c0, c0 + 4, c0 + 8, c0 + 12: all asked for at once
-      f32x4 oc[4][4];
-      float mc[4][4], lc[4][4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const bool there = c0 + 4 * k < mg.n_chunks;
-        const float* src = piece(there ? c0 + 4 * k : c0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          mc[k][i] = -INFINITY;
-          if (there && row[i] < rows) {
-            oc[k][i] = *reinterpret_cast<const f32x4*>(src + row[i] * 128 + 4 * (lane & 31));
-            mc[k][i] = src[rows * 128 + row[i]];
-            lc[k][i] = src[rows * 129 + row[i]];
-          }
+      for (int k = 0; k < kAtOnce; ++k) {
+        const int c = c0 + kParts * k;
+        mc[k] = -INFINITY;
+        lc[k] = 0.f;
+        if (c < mg.n_chunks && row < rows) {
+          const float* const src = piece(c);
+          oc[k] = *reinterpret_cast<const f32x4*>(src + row * 128 + 4 * c4);
+          mc[k] = src[rows * 128 + row];
+          lc[k] = src[rows * 129 + row];
         }
       }
+      float m_new = m_run;
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
+      for (int k = 0; k < kAtOnce; ++k) m_new = fmaxf(m_new, mc[k]);
+      if (m_new == -INFINITY) continue;
+      const float a = __builtin_amdgcn_exp2f(m_run - m_new);  // (0 for the first pieces)
+      m_run = m_new;
+      l_run *= a;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (mc[k][i] == -INFINITY) continue;  // absent, or it saw no key of the row
-          const float m_new = fmaxf(m_run[i], mc[k][i]);
-          const float a = __builtin_amdgcn_exp2f(m_run[i] - m_new);  // (0 for the first piece)
-          const float w = __builtin_amdgcn_exp2f(mc[k][i] - m_new);
-          m_run[i] = m_new;
-          l_run[i] = fmaf(w, lc[k][i], l_run[i] * a);
+      for (int e = 0; e < 4; ++e) o[e] *= a;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[i][e] = fmaf(w, oc[k][i][e], o[i][e] * a);
-        }
-    }
-    if (r0 > 0) __syncthreads();  // the rows before have been read
+      for (int k = 0; k < kAtOnce; ++k) {
+        if (mc[k] == -INFINITY) continue;  // absent, or it saw no key of the row
+        const float w = __builtin_amdgcn_exp2f(mc[k] - m_new);
+        l_run = fmaf(w, lc[k], l_run);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int rr = 2 * i + (lane >> 5);
-      *reinterpret_cast<f32x4*>(&part_o[wave][rr * 128 + 4 * (lane & 31)]) = o[i];
-      if ((lane & 31) == 0) {
-        part_m[wave][rr] = m_run[i];
-        part_l[wave][rr] = l_run[i];
+        for (int e = 0; e < 4; ++e) o[e] = fmaf(w, oc[k][e], o[e]);
       }
+    }
+    if (r0 > RW * (int)blockIdx.y) __syncthreads();  // the rows before have been read
+    part_o[half][c4] = o;
+    if (c4 == 0) {
+      part_m[half] = m_run;
+      part_l[half] = l_run;
     }
     __syncthreads();
-    // the four waves' sums, in wave order: thread t has elements 4 * (t % 32) .. of row t / 32
-    const int rr = threadIdx.x >> 5, r = r0 + rr;
-    if (r < rows) {
+    if (half < RW && row < rows) {  // the row's half-waves, in order
       float M = -INFINITY, L = 0.f;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) M = fmaxf(M, part_m[w][rr]);
+      for (int k = 0; k < kParts; ++k) M = fmaxf(M, part_m[half + RW * k]);
       f32x4 sum{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const float mw = part_m[w][rr];
-        const float f = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - M);
-        L = fmaf(f, part_l[w][rr], L);
-        const f32x4 ow = *reinterpret_cast<const f32x4*>(&part_o[w][rr * 128 + 4 * (threadIdx.x & 31)]);
+      for (int k = 0; k < kParts; ++k) {
+        const float mk = part_m[half + RW * k];
+        const float f = mk == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mk - M);
+        L = fmaf(f, part_l[half + RW * k], L);
+        const f32x4 ok = part_o[half + RW * k][c4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum[e] = fmaf(f, ow[e], sum[e]);
+        for (int e = 0; e < 4; ++e) sum[e] = fmaf(f, ok[e], sum[e]);
       }
       const float inv = 1.0f / L;
-      const int hh = r / n_unit, tt = r - hh * n_unit;
+      const int hh = row / n_unit, tt = row - hh * n_unit;
       bf16x4 v;
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = (__bf16)(sum[e] * inv);
-      *reinterpret_cast<bf16x4*>(p.out + ((int64_t)(mg.row0 + tt) * p.n_q_heads + (kvh * G + hh)) * kD +
-                                 4 * (threadIdx.x & 31)) = v;
+      *reinterpret_cast<bf16x4*>(p.out + ((int64_t)(mg.row0 + tt) * p.n_q_heads + (kvh * G + hh)) * kD + 4 * c4) = v;
     }
   }
 }
@@ -1815,6 +1805,11 @@ static AttnTuning resolve_tuning(const symph_attn_tuning* t) {
   }
   return r;
 }
+
+// A workgroup per row in the merge of a decode step up to this many rows (1 / 4 rows per workgroup: one session of 1777 tokens
+// 12.3 / 13.7 us, of 16 000 in one kv-head 17.1 / 41.8, 8 of 2000 to 4000 26.1 / 27.0, 16 and 32 sessions the same, 64 70.8 /
+// 69.7, 256 79.3 / 75.0); above it at most this many workgroups, as far as one per record and kv-head allows.
+constexpr int64_t kMergeSingleRows = 1024, kMergeGroups = 4096;
 
 struct MfmaPlan {
   int32_t bmt, target, target_slots, c_min, coarse, units_bound, items_bound, merges_bound, pslots_bound;
@@ -2059,7 +2054,16 @@ static int32_t launch_mfma(const AttnArgs& a, hipStream_t stream) {
         else
           hipLaunchKernelGGL((attn_decode_kernel<G, 0, 1>), dim3((unsigned)g_dec), dim3(64), 0, stream, p);
       }
-      hipLaunchKernelGGL((attn_decode_merge_kernel<G>), dim3((unsigned)g_merge), dim3(256), 0, stream, p);
+      // (rows that no workgroup starts with, those of units longer than stated among them, are taken in further turns)
+      const int stated_rows = G * a.max_new_len;
+      if (g_merge * stated_rows <= kMergeSingleRows) {
+        hipLaunchKernelGGL((attn_decode_merge_kernel<G, 1>), dim3((unsigned)g_merge, (unsigned)stated_rows), dim3(256), 0,
+                           stream, p);
+      } else {
+        const int64_t wanted = (stated_rows + 3) / 4, room = kMergeGroups / g_merge;
+        const unsigned gy = (unsigned)(wanted < room ? wanted : (room < 1 ? 1 : room));
+        hipLaunchKernelGGL((attn_decode_merge_kernel<G, 4>), dim3((unsigned)g_merge, gy), dim3(256), 0, stream, p);
+      }
     } else if (pl.direct) {
       const unsigned g_pieces = (unsigned)(pl.pslots_bound * a.n_kv_heads);
       if (a.block_size == 16)
