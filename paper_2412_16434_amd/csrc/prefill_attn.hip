@@ -574,12 +574,13 @@ constexpr int kTileBytes = 16 * kGroupBytes;  // 16640
 // What a cut into W workgroups of at most C tiles costs, in microseconds, fitted to 280 timings of 27 batches (1 to 48
 // sessions of 500 to 32 768 tokens, 8 to 1000 new ones, 2 to 8 kv-heads; the cut it chooses is on average 0.5 % slower
 // than the best one tried): a tile takes 1.1 while every workgroup has its CU to itself and up to 1.65 when two share it,
-// a further round of workgroups 14 beside its tiles and a piece that has to be combined 0.018 (its 66 KB written and
-// read back).  Against the scheduling kernel and the combining last piece: 45 new tokens over 3001, 30.0 -> 20.2 us (47
-// before either was reworked); 17 over 16 000, 53 -> 28; 8 x 64 .. 128 over 1500 .. 3000, 69 -> 55; 512 over 32 768 in
-// groups of eight heads, 496 -> 490.
+// a further round of workgroups 14 beside its tiles and a piece that has to be combined 0.012 (its 66 KB written and
+// read back; 0.018 with the merge kernel the timings were taken with, and with today's one 23 batches are 0.5 % slower that
+// way: 8 x 143 over 1724 43.6 us for 42.0, one turn of 160 over 3001 26.1 for 26.6).  Against the scheduling kernel and the
+// combining last piece: 45 new tokens over 3001, 30.0 -> 17.1 us (47 before either was reworked); 17 over 16 000, 53 -> 24;
+// 8 x 64 .. 128 over 1500 .. 3000, 69 -> 55; 512 over 32 768 in groups of eight heads, 496 -> 490.
 constexpr int kDirectUnits = 64;
-constexpr float kTileAlone = 1.1f, kTilePaired = 1.65f, kRoundFixed = 14.f, kPieceMerge = 0.018f;
+constexpr float kTileAlone = 1.1f, kTilePaired = 1.65f, kRoundFixed = 14.f, kPieceMerge = 0.012f;
 
 __device__ __forceinline__ bool direct_item(const MfmaParams& p, int bmt, int piece, WorkItem& it) {
   const int lane = threadIdx.x & 63;
@@ -594,9 +595,13 @@ __device__ __forceinline__ bool direct_item(const MfmaParams& p, int bmt, int pi
   const int n_units = min(__builtin_amdgcn_readlane(q_end, 63), kDirectUnits);
   // lane u: the session of unit u is the first one whose units end past u
   int lo = 0;
+  if (p.n_sessions <= 8) {  // (a step by a lane's value costs a quarter of a shuffle: 2.6 us for the piece of a single session's
+    for (int i = 0; i < p.n_sessions; ++i) lo += __builtin_amdgcn_readlane(q_end, i) <= lane;  // call, 2.0 with what follows)
+  } else {
 #pragma unroll
-  for (int step = 32; step > 0; step >>= 1)
-    if (__shfl(q_end, lo + step - 1) <= lane) lo += step;
+    for (int step = 32; step > 0; step >>= 1)
+      if (__shfl(q_end, lo + step - 1) <= lane) lo += step;
+  }
   const int s = min(lo, 63);
   const int t0 = (lane - (__shfl(q_end, s) - __shfl(nq, s))) * bmt;
   const int uN = __shfl(N, s), uP = __shfl(P, s), ucu = __shfl(cu, s);
@@ -604,7 +609,11 @@ __device__ __forceinline__ bool direct_item(const MfmaParams& p, int bmt, int pi
   const int total = __builtin_amdgcn_readlane(wave_inclusive_scan(nt), 63);
   const int max_nt = __builtin_amdgcn_readlane(wave_inclusive_max(nt), 63);
   // (no cut finer than c_lo: the slots for partial results are sized by it)
-  const int c_lo = max((int)(((int64_t)total * p.n_kv_heads + p.direct_slots - 1) / p.direct_slots), p.direct_c_min);
+  const int64_t work = (int64_t)total * p.n_kv_heads;
+  int c_lo = (int)((float)work / (float)p.direct_slots);  // ceil(work / slots): an estimate, then exact steps
+  while ((int64_t)c_lo * p.direct_slots < work) ++c_lo;
+  while (c_lo > 0 && (int64_t)(c_lo - 1) * p.direct_slots >= work) --c_lo;
+  c_lo = max(c_lo, p.direct_c_min);
   // lanes 0 .. 31: 1, 1.25, .. 8.75 pieces of the longest unit; lanes 32 .. 63: 9, 10.75, .. 63.25
   const float cuts = lane < 32 ? 1.f + 0.25f * (float)lane : 9.f + 1.75f * (float)(lane - 32);
   int C = max((int)ceilf((float)max_nt / cuts), c_lo);
@@ -621,17 +630,11 @@ __device__ __forceinline__ bool direct_item(const MfmaParams& p, int bmt, int pi
     const float w = (pieces + (float)n_units) * heads;
     const float shared = fminf(fmaxf(2.f * w / slots - 1.f, 0.f), 1.f);
     const float tile = kTileAlone + (kTilePaired - kTileAlone) * __builtin_amdgcn_sqrtf(shared);
-    float cost = ceilf(w / slots) * fmaf((float)C, tile, kRoundFixed) + split * heads * kPieceMerge;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const float other = __shfl_xor(cost, o);
-      const int other_c = __shfl_xor(C, o);
-      if (other < cost || (other == cost && other_c < C)) {
-        cost = other;
-        C = other_c;
-      }
-    }
-    C = __builtin_amdgcn_readfirstlane(C);
+    const float cost = ceilf(w / slots) * fmaf((float)C, tile, kRoundFixed) + split * heads * kPieceMerge;
+    // (positive floats compare as their bits do; of equal costs the last lane, which cuts finest)
+    const int inv_cost = 0x7FFFFFFF - __builtin_bit_cast(int, cost);
+    const int best = __builtin_amdgcn_readlane(wave_inclusive_max(inv_cost), 63);
+    C = __builtin_amdgcn_readlane(C, 63 - __builtin_clzll(__ballot(inv_cost == best)));
   }
   const int nc = (nt + C - 1) / C;
   const int end = wave_inclusive_scan(nc);
@@ -652,8 +655,9 @@ __device__ __forceinline__ bool direct_item(const MfmaParams& p, int bmt, int pi
   const int n = of_unit(nc), tiles = of_unit(nt), ch = piece - (of_unit(end) - n);
   it.s = of_unit(s);
   it.t0 = of_unit(t0);
-  it.tile_begin = (int)((int64_t)ch * tiles / n);  // near-equal pieces
-  it.tile_end = (int)((int64_t)(ch + 1) * tiles / n);
+  const unsigned each = (unsigned)tiles / (unsigned)n, rest = (unsigned)tiles - each * n;
+  it.tile_begin = ch * each + ch * rest / (unsigned)n;  // ch * tiles / n: near-equal pieces
+  it.tile_end = (ch + 1) * each + (ch + 1) * rest / (unsigned)n;
   it.pslot = n > 1 ? piece : -1;
   it.n_chunks = n;
   it.cu_s = of_unit(ucu);
@@ -1205,26 +1209,30 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
   }
 }
 
-// Combines the pieces of split units in direct mode: four workgroups per (unit, kv-head), one for each quarter of the
-// head dimension; eight pieces are asked for at a time.
-template <int G>
+// Combines the pieces of split units in direct mode: PARTS workgroups per (unit, kv-head), an equal part of the sixteen 16-byte
+// vectors of a thread's slot for each.  Few units are cut into many pieces, and what counts is how few trips to memory a thread
+// makes: sixteen workgroups of one vector, sixteen pieces at a time (45 new tokens over 3001, 12 pieces: 18.8 us with four
+// workgroups and eight pieces at a time, 17.6; 17 over 16 000, 32 pieces: 27.1 and 23.6).  Many units have few pieces each, and
+// every workgroup reads their references and sums again: four workgroups (8 x 100 over 3000: 43.3 us, 44.7 with eight).
+template <int G, int PARTS>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const MfmaParams p) {
   constexpr int TW = 128 / G / 4;  // tokens per wave, as in attn_mfma_kernel
+  constexpr int kVecs = 16 / PARTS;
   const int Hkv = p.n_kv_heads;
-  const int u = blockIdx.x / (4 * Hkv);
+  const int u = blockIdx.x / (PARTS * Hkv);
   const MergeItem mg = p.unit_recs[u];
   if (mg.n_chunks == 0) return;
-  const int dt = blockIdx.x & 3, kvh = (blockIdx.x >> 2) - u * Hkv;
+  const int part_of = blockIdx.x % PARTS, kvh = blockIdx.x / PARTS - u * Hkv;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 31, g2 = lane >> 5;
   const int hh = n / TW, tt = wave * TW + (n - hh * TW);
   if (wave * TW >= mg.n_unit) return;
-  f32x4 o[4];
+  f32x4 o[kVecs];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < kVecs; ++i) o[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   float M = -INFINITY, L = 0.f;
-  constexpr int kAtOnce = 8;
+  constexpr int kAtOnce = PARTS == 16 ? 16 : 8;
   for (int ch = 0; ch < mg.n_chunks; ch += kAtOnce) {
-    f32x4 oc[kAtOnce][4];
+    f32x4 oc[kAtOnce][kVecs];
     f32x2 ml[kAtOnce];
 #pragma unroll
     for (int k = 0; k < kAtOnce; ++k) {
@@ -1233,7 +1241,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const MfmaParams p) {
         const float* part = p.partials + ((int64_t)(mg.pslot0 + ch + k) * Hkv + kvh) * kPartialFloats;
         ml[k] = *reinterpret_cast<const f32x2*>(part + 64 * 256 + tid * 2);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) oc[k][i] = *reinterpret_cast<const f32x4*>(part + ((dt * 4 + i) * 256 + tid) * 4);
+        for (int i = 0; i < kVecs; ++i)
+          oc[k][i] = *reinterpret_cast<const f32x4*>(part + ((part_of * kVecs + i) * 256 + tid) * 4);
       }
     }
     float m_new = M;
@@ -1243,27 +1252,28 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const MfmaParams p) {
     M = m_new;
     L *= a;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] *= a;
+    for (int i = 0; i < kVecs; ++i) o[i] *= a;
 #pragma unroll
     for (int k = 0; k < kAtOnce; ++k) {
       if (ml[k][0] == -INFINITY) continue;  // absent, or it saw no key of the row
       const float w = __builtin_amdgcn_exp2f(ml[k][0] - M);
       L = fmaf(w, ml[k][1], L);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < kVecs; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[i][e] = fmaf(w, oc[k][i][e], o[i][e]);
     }
   }
   const float inv = 1.0f / sum_across_halves(L);
   if (tt >= mg.n_unit) return;
-  __bf16* const op = p.out + ((int64_t)(mg.row0 + tt) * p.n_q_heads + kvh * G + hh) * kD + 32 * dt + 4 * g2;
+  // vector j of the slot is columns 32 * (j / 4) + 8 * (j % 4) + 4 * g2 .. + 3
+  __bf16* const op = p.out + ((int64_t)(mg.row0 + tt) * p.n_q_heads + kvh * G + hh) * kD + 4 * g2;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < kVecs; ++i) {
     bf16x4 v;
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = (__bf16)(o[i][e] * inv);
-    *reinterpret_cast<bf16x4*>(op + 8 * i) = v;
+    *reinterpret_cast<bf16x4*>(op + 8 * (part_of * kVecs + i)) = v;
   }
 }
 
@@ -1811,6 +1821,9 @@ static AttnTuning resolve_tuning(const symph_attn_tuning* t) {
 // 69.7, 256 79.3 / 75.0); above it at most this many workgroups, as far as one per record and kv-head allows.
 constexpr int64_t kMergeSingleRows = 1024, kMergeGroups = 4096;
 
+// Direct calls: (unit, kv-head) pairs up to which a merge has sixteen workgroups each
+constexpr unsigned kMergeFewPairs = 32;
+
 struct MfmaPlan {
   int32_t bmt, target, target_slots, c_min, coarse, units_bound, items_bound, merges_bound, pslots_bound;
   // decode kernel: whether this call runs it (alone), its key ranges (two slots per kv-head each), the new tokens of a unit,
@@ -2070,7 +2083,11 @@ static int32_t launch_mfma(const AttnArgs& a, hipStream_t stream) {
         hipLaunchKernelGGL((attn_mfma_kernel<G, 4, true>), dim3(g_pieces), dim3(256), 0, stream, p);
       else
         hipLaunchKernelGGL((attn_mfma_kernel<G, 0, true>), dim3(g_pieces), dim3(256), 0, stream, p);
-      hipLaunchKernelGGL((attn_merge_kernel<G>), dim3((unsigned)(4 * pl.units_bound * a.n_kv_heads)), dim3(256), 0, stream, p);
+      const unsigned pairs = (unsigned)(pl.units_bound * a.n_kv_heads);
+      if (pairs <= kMergeFewPairs)
+        hipLaunchKernelGGL((attn_merge_kernel<G, 16>), dim3(16 * pairs), dim3(256), 0, stream, p);
+      else
+        hipLaunchKernelGGL((attn_merge_kernel<G, 4>), dim3(4 * pairs), dim3(256), 0, stream, p);
     } else {
       hipLaunchKernelGGL(attn_schedule_kernel, dim3(1), dim3(kSchedThreads), 0, stream, sp);
       if (a.block_size == 16)

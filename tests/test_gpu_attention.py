@@ -308,6 +308,24 @@ def test_direct_calls(oracle_mod, hkv, group, bs, prefix, new):
     assert np.sqrt(np.sum((f(got) - f(listed)) ** 2) / np.sum(f(listed) ** 2)) <= 1e-2
 
 
+@pytest.mark.parametrize("hkv,group,prefix,new", [
+    (8, 4, [9000], [17]),                                # more pieces than a merge asks for at once
+    (2, 16, [5000], [100]),                              # 26 (unit, kv-head) pairs, tiles of eight tokens
+    (4, 4, [900] * 7, [9] + [5] * 6),                    # 32 (8 units at the most): the most with a workgroup per vector
+    (3, 4, [900] * 9, [10] * 9),                         # 33: four workgroups per pair; sessions found by halves
+    (1, 1, [4000, 200], [128, 129]),                     # one head per group: 32 tokens per wave
+    (8, 8, [3000, 0, 3000, 0, 0, 70, 1, 64], [5, 0, 0, 17, 0, 1, 0, 2]),   # eight sessions, some without a turn
+])
+def test_direct_merges_and_pieces(oracle_mod, hkv, group, prefix, new):
+    cfg = _cfg(n_sessions=len(new), n_kv_heads=hkv, n_q_heads=hkv * group, n_blocks=1600, prefix_dist=("const", max(prefix)))
+    sess = W.make_sessions(cfg, 97, new_lens=np.array(new))
+    sess.prefix_lens[:] = prefix
+    sess.buf_token_offsets[1:] = np.cumsum(prefix)
+    header = []
+    check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 97), label="direct merges", header=header)
+    assert header[HDR_PLAN] == PLAN_DIRECT
+
+
 @pytest.mark.parametrize("hkv,group,prefix,new,plan", [
     (2, 4, [100] * 61, [1] * 60 + [40], PLAN_DIRECT),    # 64 units (at the most) are what a wave lists
     (2, 4, [100] * 62, [1] * 61 + [40], PLAN_LIST),
