@@ -18,6 +18,8 @@ struct RowsParams {
   const int32_t* table;
   int32_t table_stride, n_sessions, total_new_tokens;
   float scale;
+  uint32_t group_bytes;  // bytes between blocks where 16 consecutive keys lie in one block (a power of two >= 16 of tokens)
+                         // and a block fits 32 bits; else 0
 };
 
 __device__ __forceinline__ float to_f32(float x) { return x; }
@@ -131,18 +133,20 @@ __global__ __launch_bounds__(64) void attn_row_kernel(const RowsParams p) {
 // sizes, whose calls are short, so what counts is how few trips to memory stand one behind the other.
 //
 // What is held in 32 bits: probabilities too.  The bf16 kernel splits them into three bf16 values whose sum is the 32-bit
-// value (8 bits of the 24 each) and multiplies V with all three, which leaves the rounding of the output and the 32-bit sums
-// as the only ones; the fp32 kernel uses the fp32 matrix instruction throughout.  (Two values, 2^-17, were 6 to 13 % faster
-// on full chips, 6 % on the first of the calls below, and rounded ten times as many outputs to the other neighbour of the
-// 64-bit result: 1.7e-3 of them for 1.1e-4 to 1.7e-4.)
+// value (8 bits of the 24 each, taken from the top: two instructions a part and one for two values of an operand; with
+// conversions that round it was three, and the first call below took 18.3 instead of 17.3 us) and multiplies V with all three,
+// which leaves the rounding of the output and the 32-bit sums as the only ones; the fp32 kernel uses the fp32 matrix instruction
+// throughout.  (Two values, 2^-17, were 6 to 13 % faster on full chips and rounded ten times as many outputs to the other
+// neighbour of the 64-bit result: 1.7e-3 of them for 1.1e-4 to 1.7e-4.)
 //
 // Measured against one wave per row (attn_row_kernel above, 32-bit arithmetic on the vector unit, lanes over keys): six
-// sessions of 300 to 2000 tokens, 64-wide heads, 380 -> 19 us; one fp32 session of 256 tokens, 24.6 -> 9.9 us, which is the
-// call itself; three fp32 sessions of 8192, 775 -> 193; 100 new tokens of eight sessions of 2000 with 64-wide heads,
-// 1949 -> 56.  The error against 64 bits is the same in bf16 and lower in fp32 (2.9e-7 for 4.7e-7 at 128 x 8000 keys).  A
-// small call is a chain load -> product -> softmax -> product: in the first of these a wave issues in 44 % of its cycles,
-// vector instructions in 29 %, and the matrix cores are busy for 8 % of the launch.  On a full chip the vector unit counts,
-// which has as many instructions for the split and the addresses as for the exponentials.
+// sessions of 300 to 2000 tokens, 64-wide heads, 380 -> 17.3 us; one fp32 session of 256 tokens, 24.6 -> 9.3 us, which is the
+// call itself; three fp32 sessions of 8192, 775 -> 172; 100 new tokens of eight sessions of 2000 with 64-wide heads,
+// 1949 -> 51.  The error against 64 bits is the same in bf16 and lower in fp32 (2.9e-7 for 4.7e-7 at 128 x 8000 keys).  A
+// small call is a chain load -> product -> softmax -> product, and a full chip counts instructions of the vector unit: about
+// 1000 of its clocks per 32-key block, 500 of the matrix cores'.  Tried and not kept: two key blocks per turn (as fast at best,
+// fp32 slower), the next block's first product in front of this one's exponentials (17 -> 23 us), twelve or six waves a tile
+// (17 -> 21), block ids asked for without a branch (the compiler waits for them at once: 17 -> 23).
 //
 // K goes from memory straight into operand registers: a row's D values are the operand's contraction index, and any order
 // of it will do as long as Q has the same.  V is needed transposed: in bf16 through LDS (a tile of the wave's own, rows
@@ -177,17 +181,17 @@ __device__ __forceinline__ int wave_last(int n, F holds) {
   return lo;
 }
 
-// The W waves' results of a tile of R rows, DC columns at a time through LDS: out = sum_w f_w O_w / sum_w f_w l_w with
-// f_w = e^(m_w - max_w m_w) (base 2 or e, as the caller's references are).  put(round, f, mine) writes the lane's part of the
-// wave's columns, scaled.  A row with a result that is not finite (an infinity or a NaN among the inputs, which the matrix
-// product spreads over rows that must not see its key) is worked out again by itself.  Its q is read again for that, so it is
-// not written before: out may be q.
-template <typename T, int D, int R, int DC, int W, typename Put, typename Exp>
-__device__ __forceinline__ void combine_rows(const RowsParams& p, char* lds, const float (*wave_m)[R],
-                                             const float (*wave_l)[R], unsigned& bad_rows, Put put, Exp exp_of, int s,
-                                             int cu_s, int kvh, int G, int64_t row0, int n_rows) {
+// The W waves' results of a tile of R rows through LDS: out = sum_w f_w O_w / sum_w f_w l_w with f_w = e^(m_w - max_w m_w)
+// (base 2 or e, as the caller's references are); wave_m has been written.  put(f, mine) writes the lane's part of the wave's
+// columns, scaled.  A row with a result that is not finite (an infinity or a NaN among the inputs, which the matrix product
+// spreads over rows that must not see its key) is worked out again by itself.  Its q is read again for that, so it is not
+// written before: out may be q.
+template <typename T, int D, int R, int W, typename Put, typename Exp>
+__device__ __forceinline__ void combine_rows(const RowsParams& p, char* lds, const float (*wave_m)[R], float (*wave_l)[R],
+                                             float l_row, unsigned& bad_rows, Put put, Exp exp_of, int s, int cu_s, int kvh,
+                                             int G, unsigned row0, int n_rows) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  constexpr int kStride = DC + 4;  // floats between rows (the padding spreads them over the banks)
+  constexpr int kStride = D + 4;  // floats between rows (the padding spreads them over the banks)
   float* const all = reinterpret_cast<float*>(lds);
   const int n = lane & (R - 1);
   float M = -INFINITY;
@@ -195,55 +199,61 @@ __device__ __forceinline__ void combine_rows(const RowsParams& p, char* lds, con
   for (int w = 0; w < W; ++w) M = fmaxf(M, wave_m[w][n]);
   const float mine_m = wave_m[wave][n];
   const float f = mine_m == -INFINITY ? 0.f : exp_of(mine_m - M);
-  // thread t adds up V columns from c0 on of row t * V / DC
-  constexpr int V = R * DC / (64 * W), kRounds = D / DC;
-  const int r = tid * V / DC, c0 = tid * V % DC;
-  float Mr = -INFINITY, L = 0.f;
+  if (lane < R) wave_l[wave][n] = mine_m == -INFINITY ? 0.f : l_row * f;
+  put(f, all + wave * R * kStride);
+  __syncthreads();
+  // a thread adds up four columns of a row at a time
+  constexpr int kQuads = R * D / 4, kTurns = (kQuads + 64 * W - 1) / (64 * W);
+  typedef T vec __attribute__((ext_vector_type(4)));
+  vec x[kTurns];
 #pragma unroll
-  for (int w = 0; w < W; ++w) Mr = fmaxf(Mr, wave_m[w][r]);
+  for (int t = 0; t < kTurns; ++t) {
+    const int i = tid + t * 64 * W, r = i / (D / 4), c0 = 4 * (i % (D / 4));
+    if (kQuads % (64 * W) != 0 && i >= kQuads) break;
+    float L = 0.f;
+    f32x4 sum{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int w = 0; w < W; ++w)
-    L += wave_m[w][r] == -INFINITY ? 0.f : wave_l[w][r] * exp_of(wave_m[w][r] - Mr);
-  const float inv = 1.0f / L;
-  typedef T vec __attribute__((ext_vector_type(V)));
-  vec x[kRounds];
-  bool bad = false;
-#pragma unroll
-  for (int round = 0; round < kRounds; ++round) {
-    if (round > 0) __syncthreads();  // the columns before have been added up
-    put(round, f, all + wave * R * kStride);
-    __syncthreads();
-    float sum[V];
-#pragma unroll
-    for (int v = 0; v < V; ++v) sum[v] = 0.f;
-#pragma unroll
-    for (int w = 0; w < W; ++w)
-#pragma unroll
-      for (int v = 0; v < V; ++v) sum[v] += all[(w * R + r) * kStride + c0 + v];
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-      bad = bad || !(fabsf(sum[v] * inv) < INFINITY);
-      x[round][v] = (T)(sum[v] * inv);
+    for (int w = 0; w < W; ++w) {
+      L += wave_l[w][r];
+      sum += *reinterpret_cast<const f32x4*>(all + (w * R + r) * kStride + c0);
     }
+    const float inv = 1.0f / L;
+    bool bad = false;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      bad = bad || !(fabsf(sum[v] * inv) < INFINITY);
+      x[t][v] = (T)(sum[v] * inv);
+    }
+    // (a sum that is NaN comes from a score that is: every value of the row is NaN, worked out either way)
+    if (bad && L == L && r < n_rows) atomicOr(&bad_rows, 1u << r);
   }
-  // (a sum that is NaN comes from a score that is: every value of the row is NaN, worked out either way)
-  if (bad && L == L && r < n_rows) atomicOr(&bad_rows, 1u << r);
   __syncthreads();
   const unsigned again = __builtin_amdgcn_readfirstlane(bad_rows);
-  if (r < n_rows && !((again >> r) & 1)) {
-    const int64_t row = row0 + r;
-    const int tok = (int)(row / G);
-    T* const op = (T*)p.out + ((int64_t)(cu_s + tok) * p.n_q_heads + kvh * G + (int)(row - (int64_t)tok * G)) * D;
 #pragma unroll
-    for (int round = 0; round < kRounds; ++round) *reinterpret_cast<vec*>(op + round * DC + c0) = x[round];
+  for (int t = 0; t < kTurns; ++t) {
+    const int i = tid + t * 64 * W, r = i / (D / 4), c0 = 4 * (i % (D / 4));
+    if (i < kQuads && r < n_rows && !((again >> r) & 1)) {
+      const unsigned row = row0 + r, tok = row / (unsigned)G;
+      T* const op = (T*)p.out + ((int64_t)(cu_s + (int)tok) * p.n_q_heads + kvh * G + (int)(row - tok * G)) * D;
+      *reinterpret_cast<vec*>(op + c0) = x[t];
+    }
   }
   int turn = 0;
   for (unsigned left = again; left; left &= left - 1) {
     if (turn++ % W != wave) continue;
-    const int64_t row = row0 + __builtin_ctz(left);
-    const int tok = (int)(row / G);
-    row_by_lanes<T, D, 64>(p, s, cu_s + tok, kvh * G + (int)(row - (int64_t)tok * G), all + wave * 2 * D);
+    const unsigned row = row0 + __builtin_ctz(left), tok = row / (unsigned)G;
+    row_by_lanes<T, D, 64>(p, s, cu_s + (int)tok, kvh * G + (int)(row - tok * G), all + wave * 2 * D);
   }
+}
+
+// The part of a float that a bf16 value holds without rounding, and two such parts as neighbours of an operand
+__device__ __forceinline__ float leading_bits(float x) {
+  return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, x) & 0xFFFF0000u);
+}
+__device__ __forceinline__ void put_upper_halves(bf16x8& v, int at, float x, float y) {
+  u32x4 words = __builtin_bit_cast(u32x4, v);
+  words[at >> 1] = __builtin_amdgcn_perm(__builtin_bit_cast(unsigned, y), __builtin_bit_cast(unsigned, x), 0x07060302u);
+  v = __builtin_bit_cast(bf16x8, words);
 }
 
 template <typename T, int D, int W>
@@ -252,8 +262,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
   constexpr int R = RowsTile<T>::R;
   constexpr int kVRow = D * 2 + 64;                                  // bytes between V rows in LDS (bf16)
   constexpr int kVBytes = kBf16 ? W * 32 * kVRow : 0;
-  constexpr int DC = kBf16 ? 32 : D;                                 // columns combined at a time
-  constexpr int kCombBytes = W * R * (DC + 4) * 4;
+  constexpr int kCombBytes = W * R * (D + 4) * 4;
   __shared__ __attribute__((aligned(16))) char lds[kVBytes > kCombBytes ? kVBytes : kCombBytes];
   __shared__ float wave_m[W][R], wave_l[W][R];
   __shared__ unsigned bad_rows;
@@ -263,26 +272,39 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
   const int kvh = blockIdx.x % Hkv;
   const int slot = blockIdx.x / Hkv;
   // Session s has the tile slots from floor(cu[s] * G / R) + s on: at least as many as it has tiles, without a list
-  auto first_slot = [&](int s) { return (int)((int64_t)p.cu_new_lens[s] * G / R) + s; };
-  const int s = wave_last(p.n_sessions, [&](int i) { return first_slot(i) <= slot; });
-  const int cu_s = p.cu_new_lens[s];
-  const int N = max(min(p.cu_new_lens[s + 1], p.total_new_tokens) - cu_s, 0);  // (rows past total_new_tokens do not exist)
-  const int P = p.prefix_lens[s];
-  const int64_t row0 = (int64_t)(slot - first_slot(s)) * R;
-  const int64_t rows = (int64_t)N * G;
-  if (row0 >= rows) return;
-  const int n_rows = (int)min((int64_t)R, rows - row0);
-
+  auto first_slot = [&](int s, int cu) { return (int)((int64_t)cu * G / R) + s; };
   const int tid = threadIdx.x, lane = tid & 63;
+  int s, cu_s, cu_next, P;
+  if (p.n_sessions > 1 && p.n_sessions <= 64) {  // a session per lane: one trip to memory for all there is to know of it
+    const int i = min(lane, p.n_sessions - 1);
+    const int cu_i = p.cu_new_lens[i], next_i = p.cu_new_lens[i + 1], P_i = p.prefix_lens[i];
+    s = __popcll(__ballot(lane < p.n_sessions && (lane == 0 || first_slot(lane, cu_i) <= slot))) - 1;
+    cu_s = __builtin_amdgcn_readlane(cu_i, s);
+    cu_next = __builtin_amdgcn_readlane(next_i, s);
+    P = __builtin_amdgcn_readlane(P_i, s);
+  } else {
+    s = wave_last(p.n_sessions, [&](int i) { return first_slot(i, p.cu_new_lens[i]) <= slot; });
+    cu_s = p.cu_new_lens[s];
+    cu_next = p.cu_new_lens[s + 1];
+    P = p.prefix_lens[s];
+  }
+  const int N = max(min(cu_next, p.total_new_tokens) - cu_s, 0);  // (rows past total_new_tokens do not exist)
+  // (rows of a kv-head fit 31 bits: the host has checked all heads' rows)
+  const int64_t row0_64 = (int64_t)(slot - first_slot(s, cu_s)) * R;
+  if (row0_64 >= (int64_t)N * G) return;
+  const unsigned row0 = (unsigned)row0_64, rows = (unsigned)N * (unsigned)G;
+  const int n_rows = (int)min((unsigned)R, rows - row0);
+
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & (R - 1);   // query row of this lane; also its row of the K operand
   const int kg = lane / R;        // its share of the contraction index: half (bf16) or quarter (fp32) of the wave
-  const int64_t my_row = row0 + min(n, n_rows - 1);
-  const int tok = (int)(my_row / G);
+  const unsigned my_row = row0 + min(n, n_rows - 1);
+  const int tok = (int)(my_row / (unsigned)G);
   const int limit = P + tok;      // last key this row may see
   const int total_keys = P + N;
-  const int n_blocks_k = (P + (int)((row0 + n_rows - 1) / G) + R) / R;  // key blocks up to the last row's limit
-  const T* const qp = (const T*)p.q + ((int64_t)(cu_s + tok) * p.n_q_heads + kvh * G + (int)(my_row - (int64_t)tok * G)) * D;
+  const int n_blocks_k = (P + (int)((row0 + n_rows - 1) / (unsigned)G) + R) / R;  // key blocks up to the last row's limit
+  const T* const qp =
+      (const T*)p.q + ((int64_t)(cu_s + tok) * p.n_q_heads + kvh * G + (int)(my_row - (unsigned)tok * G)) * D;
   if (tid == 0) bad_rows = 0;
 
   // ---- rows of K and V: block ids are read one per lane (lane i: key i of the block) and passed between lanes
@@ -305,14 +327,25 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
   // A block of keys that lies in the prefix, its 16-key groups in blocks of the cache each (block sizes that are powers of
   // two >= 16): a group's rows start at a scalar address and a lane adds a constant.  (The general form, row_of per lane, is
   // half of the vector instructions of an iteration.)
-  const bool grouped = p.bs_shift >= 4;
+  const bool grouped = p.group_bytes != 0;
   auto group_id = [&](int id, int g) { return __builtin_amdgcn_readlane(id, 16 * g); };
   auto in_cache = [&](int id) { return (unsigned)id < (unsigned)p.n_blocks; };
-  auto group_at = [&](const void* pool, int key, int id) {  // row of `key`, a multiple of 16, of this kv-head
-    return (const char*)((const T*)pool + (int64_t)id * p.block_stride +
-                         ((int64_t)(key & (p.block_size - 1)) * Hkv + kvh) * D);
+  const unsigned row_bytes = (unsigned)(Hkv * D * (int)sizeof(T));  // between the rows of consecutive keys
+  // Place of `key`, a multiple of 16, in the pool of this kv-head.  (A block fits 32 bits here: two multiplications.  A wave
+  // that has its SIMD to itself issues an instruction every five to six clocks, address work included.)
+  auto group_off = [&](int key, int id) {
+    return (uint64_t)(unsigned)id * p.group_bytes + (unsigned)(key & (p.block_size - 1)) * row_bytes;
   };
-  const int row_bytes = Hkv * D * (int)sizeof(T);  // between the rows of consecutive keys
+  // 16 bytes of global memory (a pointer that the compiler cannot place is loaded from by an instruction that counts among the
+  // LDS reads too); at a scalar base and a lane's 32-bit offset, kept apart for the compiler, which otherwise adds them per lane
+  // (fp32 with 64 columns is 1 to 3 % faster when it does, 128 columns 9 % slower: 3 x 8192 keys 210 -> 187 us)
+  auto load_vec = [](const void* at) { return *(const u32x4 __attribute__((address_space(1)))*)(uintptr_t)at; };
+  auto load16 = [&](const char* base, unsigned lane_off) {
+    if constexpr (kBf16 || D == 128) asm("" : "+s"(base), "+v"(lane_off));
+    return load_vec(base + lane_off);
+  };
+  const char* const k_head = (const char*)((const T*)p.k_layer + kvh * D);
+  const char* const v_head = (const char*)((const T*)p.v_layer + kvh * D);
 
   if constexpr (kBf16) {
     constexpr int NS = D / 16;            // contraction steps of the first product
@@ -326,31 +359,31 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
     const int vlane_row = lane / LPR, vlane_col = (lane % LPR) * 16;
     bf16x8 kr[NS];
     u32x4 vr[NV];
-    const int k_off = (krow & 15) * row_bytes + 16 * kg;
-    const int v_off_mem = vlane_row * row_bytes + vlane_col;
+    const unsigned k_off = (krow & 15) * row_bytes + 16 * kg;
+    unsigned v_off_mem[NV / 2];
+#pragma unroll
+    for (int i = 0; i < NV / 2; ++i) v_off_mem[i] = (unsigned)(i * RPI + vlane_row) * row_bytes + vlane_col;
     auto load_block = [&](int blk, int id) {
       const int id0 = group_id(id, 0), id1 = group_id(id, 1);
       if (grouped && (blk + 1) * 32 <= P && in_cache(id0) && in_cache(id1)) {
-        const char* const k0 = group_at(p.k_layer, blk * 32, id0);
-        const char* const k1 = group_at(p.k_layer, blk * 32 + 16, id1);
-        const char* const k_row = (krow < 16 ? k0 : k1) + k_off;
+        const uint64_t off0 = group_off(blk * 32, id0), off1 = group_off(blk * 32 + 16, id1);
+        const char* const k_row = k_head + (krow < 16 ? off0 : off1) + k_off;
 #pragma unroll
-        for (int st = 0; st < NS; ++st) kr[st] = *reinterpret_cast<const bf16x8*>(k_row + 32 * st);
-        const char* const v0 = group_at(p.v_layer, blk * 32, id0);
-        const char* const v1 = group_at(p.v_layer, blk * 32 + 16, id1);
+        for (int st = 0; st < NS; ++st) kr[st] = __builtin_bit_cast(bf16x8, load_vec(k_row + 32 * st));
+        const char* const v0 = v_head + off0;
+        const char* const v1 = v_head + off1;
 #pragma unroll
-        for (int i = 0; i < NV; ++i)
-          vr[i] = *reinterpret_cast<const u32x4*>((i < NV / 2 ? v0 : v1) + (i % (NV / 2)) * RPI * row_bytes + v_off_mem);
+        for (int i = 0; i < NV; ++i) vr[i] = load16(i < NV / 2 ? v0 : v1, v_off_mem[i % (NV / 2)]);
         return;
       }
       const T* const k_row = row_of(p.k_layer, p.k_new, blk * 32 + krow, __shfl(id, krow)) + 8 * kg;
 #pragma unroll
-      for (int st = 0; st < NS; ++st) kr[st] = *reinterpret_cast<const bf16x8*>(k_row + 16 * st);
+      for (int st = 0; st < NS; ++st) kr[st] = __builtin_bit_cast(bf16x8, load_vec(k_row + 16 * st));
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
         const int r = i * RPI + vlane_row;
         const T* const v_row = row_of(p.v_layer, p.v_new, blk * 32 + r, __shfl(id, r));
-        vr[i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(v_row) + vlane_col);
+        vr[i] = load_vec(reinterpret_cast<const char*>(v_row) + vlane_col);
       }
     };
     const int i16 = lane & 15;
@@ -395,20 +428,27 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
           for (int e = 0; e < 16; ++e) o[dt][e] *= a;
       }
       const float ref = m == -INFINITY ? 0.f : m;
-      bf16x8 hi[2], mid[2], lo[2];  // the probabilities, 8 bits each
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // (here, so that V operands can be read beside the exponentials)
+      __builtin_amdgcn_wave_barrier();
+      // the probabilities, 8 bits each: w = hi + mid + lo, each part the leading bits of what the ones before leave (no
+      // rounding: one instruction takes the upper halves of two floats)
+      bf16x8 hi[2], mid[2], lo[2];
       float sum = 0.f;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float w = __builtin_amdgcn_exp2f(fmaf(x[e], cs, -ref));
-        sum += w;
-        hi[e >> 3][e & 7] = (__bf16)w;
-        const float rest = w - (float)hi[e >> 3][e & 7];
-        mid[e >> 3][e & 7] = (__bf16)rest;
-        lo[e >> 3][e & 7] = (__bf16)(rest - (float)mid[e >> 3][e & 7]);
+      for (int e = 0; e < 16; e += 2) {
+        float w[2], rest[2], last[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          w[k] = __builtin_amdgcn_exp2f(fmaf(x[e + k], cs, -ref));
+          sum += w[k];
+          rest[k] = w[k] - leading_bits(w[k]);
+          last[k] = rest[k] - leading_bits(rest[k]);
+        }
+        put_upper_halves(hi[e >> 3], e & 7, w[0], w[1]);
+        put_upper_halves(mid[e >> 3], e & 7, rest[0], rest[1]);
+        put_upper_halves(lo[e >> 3], e & 7, last[0], last[1]);
       }
       l += sum;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -425,21 +465,15 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
       __builtin_amdgcn_wave_barrier();  // the tile has been read before the next one is written
     }
     const float l_row = sum_across_halves(l);
-    if (kg == 0) {
-      wave_m[wave][n] = m;
-      wave_l[wave][n] = l_row;
-    }
+    if (kg == 0) wave_m[wave][n] = m;
     __syncthreads();  // (also: no wave reads its V tile any more, the buffer is free)
-    combine_rows<T, D, R, DC, W>(p, lds, wave_m, wave_l, bad_rows, [&](int round, float f, float* mine) {
-      // (o[round] by a chain of selects: a register array cannot be indexed)
+    combine_rows<T, D, R, W>(p, lds, wave_m, wave_l, l_row, bad_rows, [&](float f, float* mine) {
 #pragma unroll
       for (int dt = 0; dt < NT; ++dt)
-        if (dt == round) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            *reinterpret_cast<f32x4*>(mine + n * (DC + 4) + 4 * kg + 8 * i) =
-                f32x4{o[dt][4 * i] * f, o[dt][4 * i + 1] * f, o[dt][4 * i + 2] * f, o[dt][4 * i + 3] * f};
-        }
+        for (int i = 0; i < 4; ++i)
+          *reinterpret_cast<f32x4*>(mine + n * (D + 4) + 32 * dt + 4 * kg + 8 * i) =
+              f32x4{o[dt][4 * i] * f, o[dt][4 * i + 1] * f, o[dt][4 * i + 2] * f, o[dt][4 * i + 3] * f};
     }, [](float x) { return __builtin_amdgcn_exp2f(x); }, s, cu_s, kvh, G, row0, n_rows);
   } else {
     constexpr int NS = D / 16;  // 16-byte loads of a row per lane
@@ -448,28 +482,29 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
 #pragma unroll
     for (int j = 0; j < NS; ++j) q[j] = *reinterpret_cast<const f32x4*>(qp + 16 * j + 4 * kg);
     f32x4 kr[NS], vr[4][NH];
+    const unsigned k_off = n * row_bytes + 16 * kg, v_off_mem = 4 * kg * row_bytes + 16 * n;
     auto load_block = [&](int blk, int id) {
       const int id0 = group_id(id, 0);
       if (grouped && (blk + 1) * 16 <= P && in_cache(id0)) {
-        const char* const k_row = group_at(p.k_layer, blk * 16, id0) + n * row_bytes + 16 * kg;
+        const uint64_t off = group_off(blk * 16, id0);
 #pragma unroll
-        for (int j = 0; j < NS; ++j) kr[j] = *reinterpret_cast<const f32x4*>(k_row + 64 * j);
-        const char* const v_row = group_at(p.v_layer, blk * 16, id0) + 4 * kg * row_bytes + 16 * n;
+        for (int j = 0; j < NS; ++j) kr[j] = __builtin_bit_cast(f32x4, load16(k_head + off + 64 * j, k_off));
+        const char* const v_rows = v_head + off;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
           for (int h = 0; h < NH; ++h)
-            vr[e][h] = *reinterpret_cast<const f32x4*>(v_row + e * row_bytes + 256 * h);
+            vr[e][h] = __builtin_bit_cast(f32x4, load16(v_rows + e * row_bytes + 256 * h, v_off_mem));
         return;
       }
       const T* const k_row = row_of(p.k_layer, p.k_new, blk * 16 + n, id) + 4 * kg;
 #pragma unroll
-      for (int j = 0; j < NS; ++j) kr[j] = *reinterpret_cast<const f32x4*>(k_row + 16 * j);
+      for (int j = 0; j < NS; ++j) kr[j] = __builtin_bit_cast(f32x4, load_vec(k_row + 16 * j));
 #pragma unroll
       for (int e = 0; e < 4; ++e) {  // key 4 * kg + e: values 64 * h + 4 * n .. + 3 of its row
         const T* const v_row = row_of(p.v_layer, p.v_new, blk * 16 + 4 * kg + e, __shfl(id, 4 * kg + e)) + 4 * n;
 #pragma unroll
-        for (int h = 0; h < NH; ++h) vr[e][h] = *reinterpret_cast<const f32x4*>(v_row + 64 * h);
+        for (int h = 0; h < NH; ++h) vr[e][h] = __builtin_bit_cast(f32x4, load_vec(v_row + 64 * h));
       }
     };
     // o[h][c][e]: column 64 * h + 16 * kg + 4 * e + c of row n.  A sum over thousands of keys in one chain loses bits (6.0e-7
@@ -554,17 +589,14 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
     join_run();
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
-    if (kg == 0) {
-      wave_m[wave][n] = m;
-      wave_l[wave][n] = l;
-    }
+    if (kg == 0) wave_m[wave][n] = m;
     __syncthreads();
-    combine_rows<T, D, R, DC, W>(p, lds, wave_m, wave_l, bad_rows, [&](int, float f, float* mine) {
+    combine_rows<T, D, R, W>(p, lds, wave_m, wave_l, l, bad_rows, [&](float f, float* mine) {
 #pragma unroll
       for (int h = 0; h < NH; ++h)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          *reinterpret_cast<f32x4*>(mine + n * (DC + 4) + 64 * h + 16 * kg + 4 * e) =
+          *reinterpret_cast<f32x4*>(mine + n * (D + 4) + 64 * h + 16 * kg + 4 * e) =
               f32x4{o[h][0][e] * f, o[h][1][e] * f, o[h][2][e] * f, o[h][3][e] * f};
     }, [](float x) { return expf(x); }, s, cu_s, kvh, G, row0, n_rows);
   }
@@ -597,6 +629,8 @@ static int32_t launch_rows(const AttnArgs& a, hipStream_t stream) {
   p.n_sessions = a.n_sessions;
   p.total_new_tokens = a.total_new_tokens;
   p.scale = a.scale;
+  const int64_t block_bytes = a.block_stride * (int64_t)sizeof(T);
+  p.group_bytes = p.bs_shift >= 4 && block_bytes <= 0x7FFFFFFFLL ? (uint32_t)block_bytes : 0;
   const int64_t rows = (int64_t)a.total_new_tokens * a.n_q_heads;
   if (rows > 0x7FFFFFFFLL) return SYMPH_EUNSUPPORTED;
   const uintptr_t address_bits = (uintptr_t)a.k_layer | (uintptr_t)a.v_layer | (uintptr_t)a.q | (uintptr_t)a.k_new |
@@ -607,9 +641,10 @@ static int32_t launch_rows(const AttnArgs& a, hipStream_t stream) {
   // decide.)
   // Eight waves a tile give the shortest chain of key blocks to a call that does not fill the chip.  With more tiles than
   // compute units, four waves each (two or three workgroups then share a compute unit) leave a last round less empty.  Eight
-  // / four waves, sessions of 1000 tokens, bf16 with 64-wide heads: 12.7 / 14.0 us at 112 tiles, 36 / 26 at 264, 50 / 34 at
-  // 504, 399 / 283 at 3200; fp32 with 128-wide heads: 39 / 51, 104 / 106, 158 / 139, 963 / 819; 32 tiles of 8000 keys 51 / 74
-  // and 204 / 268.  (Just below the line, at 248 tiles, four are ahead already: 26 / 20 and 74 / 67.)
+  // / four waves, sessions of 1000 to 2000 tokens, bf16 with 64-wide heads: 16.5 / 20.3 us at 192 tiles, 28.4 / 24.5 at 304,
+  // 39.5 / 33.8 at 552; with 128-wide heads 30.1 / 30.1, 52 / 46, 71 / 58; fp32 with 64-wide heads 33.5 / 49, 58.3 / 58.9 at
+  // 344, 83 / 74 at 608; with 128-wide heads 52.5 / 62, 92.6 / 94, 135 / 138; 150 to 300 tokens: 8.8 / 8.7, 12.1 / 9.1, 17.1 /
+  // 11.4 and 15.3 / 16.7, 27.6 / 23.1, 39.6 / 34.4.
   if ((address_bits & 15) == 0 && groups <= 0x7FFFFFFFLL) {
     if (groups <= kComputeUnits)
       hipLaunchKernelGGL((attn_rows_kernel<T, D, 8>), dim3((unsigned)groups), dim3(512), 0, stream, p);

@@ -377,6 +377,23 @@ def test_shapes_without_a_work_list(oracle_mod, dtype, d, hkv, group, bs, prefix
     check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 71), label="rows")
 
 
+@pytest.mark.parametrize("dtype,d,group,n_sessions,empty", [
+    ("bf16", 64, 3, 64, (0, 63)),                        # a session per lane, the first and the last without a turn
+    ("bf16", 64, 4, 65, (0, 1, 2, 64)),                  # one more: found by halves
+    ("fp32", 128, 1, 2, (0,)),
+    ("fp32", 64, 5, 64, tuple(range(0, 64, 2))),
+    ("bf16", 128, 3, 33, (5, 6, 7)),
+])
+def test_tiles_find_their_session(oracle_mod, dtype, d, group, n_sessions, empty):
+    rng = np.random.default_rng(n_sessions + group)
+    new = rng.integers(1, 40, n_sessions)
+    new[list(empty)] = 0
+    cfg = _cfg(dtype=dtype, head_dim=d, n_kv_heads=2, n_q_heads=2 * group, n_sessions=n_sessions, scale=1.0 / np.sqrt(d),
+               n_blocks=n_sessions * 6, prefix_dist=("uniform", 0, 90))
+    sess = W.make_sessions(cfg, 101, new_lens=new)
+    check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 101), label="sessions of tiles")
+
+
 @pytest.mark.parametrize("d,hkv,group,bs", [(64, 4, 4, 16), (128, 2, 3, 16), (128, 4, 2, 8)])
 def test_probabilities_of_bf16_rows_are_held_in_32_bits(oracle_mod, d, hkv, group, bs):
     """The shapes without a work list round to bf16 once, at the output: hardly any value is rounded to the other neighbour
