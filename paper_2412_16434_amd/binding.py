@@ -428,10 +428,33 @@ def _attn_args(cache: KVCache, layer, q, k_new, v_new, out, cu_new_lens, prefix_
             int(max_prefix_len), float(scale)]
 
 
+_attn_call = None
+
+
+def _load_attn_call():
+    """The compiled marshalling of the ordinary attention call (``csrc/attn_call.c``), bound to the library's entry point."""
+    global _attn_call
+    lib, torch = load_library(), _torch()
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:  # (a torch without them: the general path)
+        _attn_call = lambda *args: None
+    else:
+        from . import _attn_call as module
+        module.bind(C.cast(lib.symph_prefix_prefill_attn, C.c_void_p).value, torch.bfloat16, torch.float32, torch.int32, raw,
+                    device)
+        _attn_call = module.attn
+    return _attn_call
+
+
 def prefix_prefill_attn(cache: KVCache, layer: int, q, k_new, v_new, out, cu_new_lens, prefix_lens, block_table,
                         max_new_len: int, max_prefix_len: int, scale: float, workspace=None, stream=None,
                         tuning: Optional[AttnTuning] = None) -> None:
     """out[T][H_q][d] <- attention of the new turn over [cached prefix ; causal new tokens] for one layer."""
+    if stream is None and tuning is None:
+        status = (_attn_call or _load_attn_call())(cache.k_pool, cache.v_pool, layer, q, k_new, v_new, out, cu_new_lens,
+                                                   prefix_lens, block_table, max_new_len, max_prefix_len, scale, workspace)
+        if status is not None:
+            return _check(status, "symph_prefix_prefill_attn")
     st = cache.struct()
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     args = _attn_args(cache, layer, q, k_new, v_new, out, cu_new_lens, prefix_lens, block_table, max_new_len,

@@ -4,11 +4,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsymph.so")
+CALL_LIB = os.path.join(HERE, "_attn_call.so")  # Python extension module: the attention call's marshalling (host code only)
 SOURCES = ("api.hip", "kv_migrate.hip", "prefill_attn.hip", "rows_attn.hip", "attn_static.hip", "kv_pool.cpp")  # the last one is host code only
 # packed-fp32 instructions are switched off for every device compile
 HIPCC_FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
@@ -41,6 +43,10 @@ def build(verbose: bool = False) -> str:
             print(out)
     if failed:
         raise RuntimeError("hipcc failed")
+    tmp = CALL_LIB + f".tmp{os.getpid()}"
+    subprocess.check_call(["gcc", "-O2", "-std=c11", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], "-I",
+                           os.path.join(ROOT, "include"), os.path.join(CSRC, "attn_call.c"), "-o", tmp])
+    os.replace(tmp, CALL_LIB)
     tmp = LIB + f".tmp{os.getpid()}"
     subprocess.check_call([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp, *objs])
     os.replace(tmp, LIB)

@@ -1,0 +1,93 @@
+"""The compiled marshalling of the attention call against the general path: it takes the same calls with the same arguments,
+and leaves everything it does not take, errors above all, to the general path."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2412_16434_amd as S
+from paper_2412_16434_amd import binding
+
+
+def _call(dev, dtype=torch.bfloat16, d=128):
+    """Arguments of a call: two sessions of 20 and 0 cached tokens, 3 and 2 new ones, 4 / 2 heads."""
+    g = torch.Generator().manual_seed(5)
+    rand = lambda *shape: torch.randn(shape, generator=g).to(dtype).to(dev)
+    cache = S.KVCache(rand(2, 4, 16, 2, d), rand(2, 4, 16, 2, d))
+    q = rand(5, 4, d)
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device=dev)
+    return dict(cache=cache, layer=1, q=q, k_new=rand(5, 2, d), v_new=rand(5, 2, d), out=torch.zeros_like(q),
+                cu_new_lens=i32([0, 3, 5]), prefix_lens=i32([20, 0]), block_table=i32([[3, 1], [-1, -1]]), max_new_len=3,
+                max_prefix_len=20, scale=0.125)
+
+
+def _compiled(a, workspace=None):
+    return binding._load_attn_call()(a["cache"].k_pool, a["cache"].v_pool, *list(a.values())[1:], workspace)
+
+
+def test_calls_on_the_host_are_left_to_the_general_path():
+    a = _call("cpu")
+    assert _compiled(a) is None
+    with pytest.raises(ValueError, match="must be a device tensor"):
+        S.prefix_prefill_attn(**a)
+    assert binding._load_attn_call()() is None and binding._load_attn_call()(*range(14)) is None
+
+
+def _workspace(a):
+    n = S.prefix_prefill_attn_workspace_bytes(a["cache"], 2, 4, 5, a["max_new_len"], a["max_prefix_len"])
+    return torch.empty(n, dtype=torch.uint8, device="cuda:0") if n else None
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 128), (torch.bfloat16, 64), (torch.float32, 64)])
+def test_same_call_both_ways(dtype, d):
+    a = _call("cuda:0", dtype, d)
+    ws = _workspace(a)
+    assert _compiled(a, ws) == 0
+    torch.cuda.synchronize()
+    by_c = a["out"].clone()
+    a["out"] = torch.zeros_like(by_c)
+    S.prefix_prefill_attn(**a, workspace=ws, stream=torch.cuda.current_stream())   # (a stream: the general path)
+    torch.cuda.synchronize()
+    assert torch.equal(by_c, a["out"]) and bool(by_c.float().abs().sum() > 0)
+    # another stream is the current one: the call goes there
+    side = torch.cuda.Stream()
+    a["out"].zero_()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        S.prefix_prefill_attn(**a, workspace=ws)
+    side.synchronize()
+    assert torch.equal(by_c, a["out"])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("change,error", [
+    (dict(layer=2), S.SymphError),                       # statuses of the entry point
+    (dict(scale=0.0), S.SymphError),
+    (dict(max_new_len=6), S.SymphError),
+    (dict(workspace=None), S.SymphError),
+    (dict(scale=np.float32(0.125)), None),               # not of the plain types: converted by the general path
+    (dict(layer=np.int64(1)), None),
+    (dict(prefix_lens=lambda t: t.long()), ValueError),  # what the C side cannot see
+    (dict(q=lambda t: t.float()), ValueError),
+    (dict(k_new=lambda t: t.cpu()), ValueError),
+    (dict(out=lambda t: t[:4]), ValueError),
+    (dict(v_new=lambda t: torch.empty(5, 4, 128, dtype=t.dtype, device=t.device)[:, ::2]), ValueError),
+    (dict(block_table=lambda t: t[0]), ValueError),
+])
+def test_what_is_not_taken_ends_as_it_did(change, error):
+    a = _call("cuda:0")
+    a["workspace"] = _workspace(a)
+    for k, v in change.items():
+        a[k] = v(a[k]) if callable(v) else v
+    results = []
+    for stream in (None, torch.cuda.current_stream()):   # (a stream: the general path)
+        try:
+            S.prefix_prefill_attn(**a, stream=stream)
+            torch.cuda.synchronize()
+            results.append(a["out"].clone())
+        except Exception as e:
+            results.append((type(e), str(e)))
+    if error is None:
+        assert torch.equal(*results)
+    else:
+        assert results[0] == results[1] and results[0][0] is error
