@@ -394,6 +394,20 @@ def test_tiles_find_their_session(oracle_mod, dtype, d, group, n_sessions, empty
     check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 101), label="sessions of tiles")
 
 
+@pytest.mark.parametrize("d,group,bs,prefix,new", [
+    (64, 2, 16, 0, 5),                                   # a single fp32 session: no prefix (and no table),
+    (64, 1, 16, 100, 1),                                 # fewer key blocks than waves, a table shorter than two blocks a wave
+    (128, 3, 24, 250, 40),                               # a block size that is no power of two: a last, partial block
+    (64, 4, 8, 16 * 8, 3),                               # a block per wave from the prefix, the next one new keys
+    (64, 2, 32, 2000, 300),                              # more tiles than compute units: four waves
+])
+def test_a_single_fp32_session(oracle_mod, d, group, bs, prefix, new):
+    cfg = _cfg(dtype="fp32", head_dim=d, n_kv_heads=8, n_q_heads=8 * group, n_sessions=1, block_size=bs, n_blocks=300,
+               scale=1.0 / np.sqrt(d), prefix_dist=("const", prefix))
+    sess = W.make_sessions(cfg, 103, new_lens=np.array([new]))
+    check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 103), label="one session")
+
+
 @pytest.mark.parametrize("d,hkv,group,bs", [(64, 4, 4, 16), (128, 2, 3, 16), (128, 4, 2, 8)])
 def test_probabilities_of_bf16_rows_are_held_in_32_bits(oracle_mod, d, hkv, group, bs):
     """The shapes without a work list round to bf16 once, at the output: hardly any value is rounded to the other neighbour
