@@ -9,8 +9,8 @@ import pytest
 
 import paper_2412_16434_amd as S
 import workloads as W
-from gpu_util import (HDR_DECODE_TILES, HDR_PLAN, PLAN_DECODE, PLAN_DIRECT, PLAN_LIST, TOL, attn_errors, gpu_attention,
-                      widen)
+from gpu_util import (HDR_DECODE_TILES, HDR_ITEMS, HDR_PLAN, HDR_SPLIT_UNITS, PLAN_DECODE, PLAN_DIRECT, PLAN_LIST, TOL,
+                      attn_errors, gpu_attention, widen)
 
 pytestmark = pytest.mark.gpu
 
@@ -324,6 +324,26 @@ def test_direct_merges_and_pieces(oracle_mod, hkv, group, prefix, new):
     header = []
     check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 97), label="direct merges", header=header)
     assert header[HDR_PLAN] == PLAN_DIRECT
+
+
+@pytest.mark.parametrize("cut", [False, True])
+@pytest.mark.parametrize("n_sessions", [1, 2, 4, 5, 16, 17, 255, 257, 700])
+def test_work_list_of_any_number_of_sessions(oracle_mod, n_sessions, cut):
+    """The list finds a unit's session by quarters of the range (a third of the sessions have no unit), and takes a shorter way
+    where no unit is cut: pieces of at least one tile, or of more than any unit has."""
+    rng = np.random.default_rng(211 + n_sessions)
+    new = rng.integers(1, 70, n_sessions) * (rng.integers(0, 3, n_sessions) > 0)
+    new[0] = max(new[0], 33)
+    cfg = _cfg(n_sessions=n_sessions, n_blocks=n_sessions * 24 + 8, prefix_dist=("uniform", 0, 300))
+    sess = W.make_sessions(cfg, 211, new_lens=new)
+    header = []
+    check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 211), label=f"list of {n_sessions}, cut={cut}", header=header,
+          tuning=S.AttnTuning(coarse=-1, decode=-1, c_min=1 if cut else 1000))
+    assert header[HDR_PLAN] == PLAN_LIST
+    per_wave = 128 // (cfg.n_q_heads // cfg.n_kv_heads)
+    assert header[HDR_ITEMS] >= sum(-(-int(n) // per_wave) for n in new)
+    if not cut:
+        assert header[HDR_SPLIT_UNITS] == 0 and header[HDR_ITEMS] == sum(-(-int(n) // per_wave) for n in new)
 
 
 @pytest.mark.parametrize("hkv,group,prefix,new,plan", [
