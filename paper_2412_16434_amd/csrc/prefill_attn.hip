@@ -587,13 +587,15 @@ constexpr int kTileBytes = 16 * kGroupBytes;  // 16640
 // What a cut into W workgroups of at most C tiles costs, in microseconds, fitted to 280 timings of 27 batches (1 to 48
 // sessions of 500 to 32 768 tokens, 8 to 1000 new ones, 2 to 8 kv-heads; the cut it chooses is on average 0.5 % slower
 // than the best one tried): a tile takes 1.1 while every workgroup has its CU to itself and up to 1.65 when two share it,
-// a further round of workgroups 14 beside its tiles and a piece that has to be combined 0.012 (its 66 KB written and
-// read back; 0.018 with the merge kernel the timings were taken with, and with today's one 23 batches are 0.5 % slower that
-// way: 8 x 143 over 1724 43.6 us for 42.0, one turn of 160 over 3001 26.1 for 26.6).  Against the scheduling kernel and the
-// combining last piece: 45 new tokens over 3001, 30.0 -> 17.1 us (47 before either was reworked); 17 over 16 000, 53 -> 24;
-// 8 x 64 .. 128 over 1500 .. 3000, 69 -> 55; 512 over 32 768 in groups of eight heads, 496 -> 490.
+// a further round of workgroups 14 beside its tiles and a piece that has to be combined 0.018 (its 66 KB written and
+// read back with the merge kernel the timings were taken with).  Today's merge kernel is faster, but with a price of 0.012 the
+// calls are not (45 new tokens over 3001 20.0 us for 19.7, 160 over 3001 29.1 for 28.9, 6 x 20 over 2000 22.6 for 21.2), and
+// every cut that moves makes probabilities be rounded against other references, which moves outputs by 2.8e-3.  Against the
+// scheduling kernel and the combining last piece: 45 new tokens over 3001, 30.0 -> 17 to 20 us (47 before either was
+// reworked); 17 over 16 000, 53 -> 24; 8 x 64 .. 128 over 1500 .. 3000, 69 -> 55; 512 over 32 768 in groups of eight heads,
+// 496 -> 490.
 constexpr int kDirectUnits = 64;
-constexpr float kTileAlone = 1.1f, kTilePaired = 1.65f, kRoundFixed = 14.f, kPieceMerge = 0.012f;
+constexpr float kTileAlone = 1.1f, kTilePaired = 1.65f, kRoundFixed = 14.f, kPieceMerge = 0.018f;
 
 __device__ __forceinline__ bool direct_item(const MfmaParams& p, int bmt, int piece, WorkItem& it) {
   const int lane = threadIdx.x & 63;
@@ -1258,23 +1260,26 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const MfmaParams p) {
           oc[k][i] = *reinterpret_cast<const f32x4*>(part + ((part_of * kVecs + i) * 256 + tid) * 4);
       }
     }
-    float m_new = M;
 #pragma unroll
-    for (int k = 0; k < kAtOnce; ++k) m_new = fmaxf(m_new, ml[k][0]);
-    const float a = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - m_new);
-    M = m_new;
-    L *= a;
+    for (int k0 = 0; k0 < kAtOnce; k0 += 8) {  // (sums go by eight pieces however many are in flight: one result)
+      float m_new = M;
 #pragma unroll
-    for (int i = 0; i < kVecs; ++i) o[i] *= a;
+      for (int k = k0; k < k0 + 8; ++k) m_new = fmaxf(m_new, ml[k][0]);
+      const float a = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - m_new);
+      M = m_new;
+      L *= a;
 #pragma unroll
-    for (int k = 0; k < kAtOnce; ++k) {
-      if (ml[k][0] == -INFINITY) continue;  // absent, or it saw no key of the row
-      const float w = __builtin_amdgcn_exp2f(ml[k][0] - M);
-      L = fmaf(w, ml[k][1], L);
+      for (int i = 0; i < kVecs; ++i) o[i] *= a;
 #pragma unroll
-      for (int i = 0; i < kVecs; ++i)
+      for (int k = k0; k < k0 + 8; ++k) {
+        if (ml[k][0] == -INFINITY) continue;  // absent, or it saw no key of the row
+        const float w = __builtin_amdgcn_exp2f(ml[k][0] - M);
+        L = fmaf(w, ml[k][1], L);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[i][e] = fmaf(w, oc[k][i][e], o[i][e]);
+        for (int i = 0; i < kVecs; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[i][e] = fmaf(w, oc[k][i][e], o[i][e]);
+      }
     }
   }
   const float inv = 1.0f / sum_across_halves(L);

@@ -52,7 +52,7 @@ def gpu_unpack(cache: S.KVCache, ds: DeviceSessions, buf: torch.Tensor, dst: boo
 
 
 # Of the counts at the start of the attention workspace (kHdr* of prefill_attn.hip): which plan ran, 32-key tiles of a decode step
-HDR_ITEMS, HDR_SPLIT_UNITS, HDR_PLAN, HDR_DECODE_TILES = 0, 2, 4, 5
+HDR_ITEMS, HDR_CHUNK, HDR_SPLIT_UNITS, HDR_PLAN, HDR_DECODE_TILES = 0, 1, 2, 4, 5
 PLAN_LIST, PLAN_DIRECT, PLAN_DECODE = 0, 1, 2
 
 

@@ -9,8 +9,8 @@ import pytest
 
 import paper_2412_16434_amd as S
 import workloads as W
-from gpu_util import (HDR_DECODE_TILES, HDR_ITEMS, HDR_PLAN, HDR_SPLIT_UNITS, PLAN_DECODE, PLAN_DIRECT, PLAN_LIST, TOL,
-                      attn_errors, gpu_attention, widen)
+from gpu_util import (HDR_CHUNK, HDR_DECODE_TILES, HDR_ITEMS, HDR_PLAN, HDR_SPLIT_UNITS, PLAN_DECODE, PLAN_DIRECT, PLAN_LIST,
+                      TOL, attn_errors, gpu_attention, widen)
 
 pytestmark = pytest.mark.gpu
 
@@ -324,6 +324,24 @@ def test_direct_merges_and_pieces(oracle_mod, hkv, group, prefix, new):
     header = []
     check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 97), label="direct merges", header=header)
     assert header[HDR_PLAN] == PLAN_DIRECT
+
+
+@pytest.mark.parametrize("prefix,new,tiles,pieces", [
+    ([3001], [45], 4, 24),                               # two units of 48 tiles
+    ([3001], [160], 9, 30),                              # five of 48 to 50
+    ([16000], [17], 8, 32),                              # one of 251
+    ([1500, 0, 3000], [33, 64, 5], 4, 26),               # units of 24, 24, 1, 1 and 47 tiles
+])
+def test_cuts_of_direct_calls(oracle_mod, prefix, new, tiles, pieces):
+    """Where a direct call's units are cut decides against which references probabilities are rounded to bf16: another price of
+    a piece is another result (2.8e-3 away for the first of these), so the cuts are pinned."""
+    cfg = _cfg(n_sessions=len(new), n_kv_heads=8, n_q_heads=32, n_blocks=1280, prefix_dist=("const", max(prefix)))
+    sess = W.make_sessions(cfg, 109, new_lens=np.array(new))
+    sess.prefix_lens[:] = prefix
+    sess.buf_token_offsets[1:] = np.cumsum(prefix)
+    header = []
+    check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 109), label="cuts", header=header)
+    assert header[HDR_PLAN] == PLAN_DIRECT and (header[HDR_CHUNK], header[HDR_ITEMS]) == (tiles, pieces)
 
 
 @pytest.mark.parametrize("cut", [False, True])
