@@ -274,15 +274,6 @@ static int32_t launch_rows(const MigrateParams& p_in, hipStream_t stream) {
   return hipGetLastError() == hipSuccess ? SYMPH_OK : SYMPH_ELAUNCH;
 }
 
-// LDS that nothing uses: six workgroups (24 waves) share a compute unit and its 160 KB instead of eight.  With two vectors in
-// flight per lane, 32 waves keep more rows of memory open than DRAM has room for, and a scatter, which writes into random
-// blocks, loses by it wherever its pools are not placed well: 16 chats 3390 -> 3295 us, 16 sessions of 4096 tokens 3110 ->
-// 3020, 256 of 600 7500 -> 7350, 80 layers of two of 8192 1955 -> 1905, 28 of 30 of 1500 1855 -> 1808, one of 30 000 1405 ->
-// 1362, four of 300 50.4 -> 49.2, one layer 96.1 -> 94.0; well placed (pools of 64 GiB), 2630 to 2740 either way.  Five
-// workgroups gain another percent there and lose up to one here.  Rows shorter than a wave have a lookup per lane and need the
-// waves (525 -> 535), as does the gather with one plane per lane (3040 -> 3230 with five).
-constexpr unsigned kSixGroupsLds = 24 * 1024;
-
 // planes: 1 for the gather of rows that fill whole waves, else 2
 template <typename VecT, bool PACK>
 static int32_t launch_planes(int planes, const MigrateParams& p_in, hipStream_t stream) {
@@ -293,7 +284,11 @@ static int32_t launch_planes(int planes, const MigrateParams& p_in, hipStream_t 
   // sessions of 4096 tokens take 2960 to 3020 us wherever that is, and 3140 or 2590 with two planes per lane in the plain
   // order; 256 of 600, 6940 to 7480 and 7590 or 6190; the 16 chats (18 GB) 3160 to 3190 and 3300 to 3390.  Everything that
   // widens the set of rows under way at once loses: 8 / 64 planes per wave in a software pipeline, gather 3040 -> 3306 /
-  // 3491 us, scatter 3390 -> 3484 / 3607.
+  // 3491 us, scatter 3390 -> 3484 / 3607.  The reverse, six workgroups per compute unit instead of eight (by 24 KB of LDS that
+  // nothing uses), gains 1 to 2.5 % (six processes: 16 chats 3283 to 3347 -> 3232 to 3260 us, 256 of 600 6740 to 7794 -> 6737
+  // to 7742) and is not used: an attention workgroup on another stream then finds no room until the scatter's last workgroups
+  // are through (a call of the 16 chats beside it ends after 3530 us instead of 540, eight after 5700 instead of 4920, 32
+  // layers unpacked and attended one by one 12.2 ms instead of 12.0).
   if constexpr (PACK) {
     if (planes == 1 && p_in.n_sessions > 1) return launch_rows<VecT, PACK, 2, 1>(p_in, stream);
   }
@@ -313,7 +308,7 @@ static int32_t launch_planes(int planes, const MigrateParams& p_in, hipStream_t 
     }
   }
   if (p.row_shift >= 6)  // a row is a whole number of waves: scalar session search and table read
-    hipLaunchKernelGGL((kv_migrate_kernel<VecT, PACK, 2, kMigrateNT, true>), grid, dim3(256), kSixGroupsLds, stream, p);
+    hipLaunchKernelGGL((kv_migrate_kernel<VecT, PACK, 2, kMigrateNT, true>), grid, dim3(256), 0, stream, p);
   else
     hipLaunchKernelGGL((kv_migrate_kernel<VecT, PACK, 2, kMigrateNT, false>), grid, dim3(256), 0, stream, p);
   return hipGetLastError() == hipSuccess ? SYMPH_OK : SYMPH_ELAUNCH;

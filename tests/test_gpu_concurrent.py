@@ -58,3 +58,45 @@ def test_attention_and_unpack_on_two_streams(oracle_mod):
         assert max_abs <= TOL["bf16"][0] and rel <= TOL["bf16"][1]
         assert to_host(ucache.k_pool).tobytes() == ref_k.tobytes(), "unpack beside attention: K pool differs"
         assert to_host(ucache.v_pool).tobytes() == ref_v.tobytes(), "unpack beside attention: V pool differs"
+
+
+@pytest.mark.parametrize("first", ["attention", "unpack"])
+def test_attention_is_not_held_back_by_an_unpack(first):
+    """Three calls of attention of eight resumed turns (0.15 ms alone) beside the unpack of 16 arriving sessions (3 ms): workgroups of both share the
+    compute units, so the attention is done long before the unpack, whichever was launched first.  (An unpack that holds LDS
+    leaves no room for an attention workgroup until its own last ones are through: the two then end together.)"""
+    dims = dict(dtype=torch.bfloat16, device=DEV)
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device=DEV)
+    tokens, sessions, layers, bs, hkv, d = 4096, 16, 32, 16, 8, 128
+    blocks = tokens * sessions // bs
+    order = torch.randperm(blocks, generator=torch.Generator().manual_seed(3)).to(torch.int32)
+    incoming = S.KVCache(torch.empty(layers, blocks, bs, hkv, d, **dims), torch.empty(layers, blocks, bs, hkv, d, **dims))
+    buf = torch.zeros(layers * 2 * tokens * sessions * hkv * d, **dims)
+    offsets = torch.arange(sessions + 1, dtype=torch.int64, device=DEV) * tokens
+    cache = S.KVCache(torch.zeros(1, 1024, bs, hkv, d, **dims), torch.zeros(1, 1024, bs, hkv, d, **dims))
+    q, kv = torch.zeros(800, 32, d, **dims), torch.zeros(800, hkv, d, **dims)
+    out = torch.empty_like(q)
+    size = S.prefix_prefill_attn_workspace_bytes(cache, 8, 32, 800, 100, 2000)
+    attn_args = (cache, 0, q, kv, kv, out, i32(range(0, 801, 100)), i32([2000] * 8),
+                 torch.arange(1000, dtype=torch.int32, device=DEV).view(8, 125), 100, 2000, 0.1)
+    workspace = torch.empty(size, dtype=torch.uint8, device=DEV)
+    unpack_args = (incoming, order.view(sessions, -1).to(DEV), i32([tokens] * sessions), offsets, tokens * sessions, buf)
+    streams = {"attention": torch.cuda.Stream(), "unpack": torch.cuda.Stream()}
+    calls = {"attention": lambda s: [S.prefix_prefill_attn(*attn_args, workspace=workspace, stream=s) for _ in range(3)],
+             "unpack": lambda s: S.kv_unpack(*unpack_args, stream=s)}
+    shares = []
+    for rep in range(6):
+        start, done = torch.cuda.Event(enable_timing=True), {}
+        torch.cuda.synchronize()
+        start.record()
+        for name in sorted(calls, key=lambda n: n != first):
+            streams[name].wait_event(start)
+            calls[name](streams[name])
+            done[name] = torch.cuda.Event(enable_timing=True)
+            done[name].record(streams[name])
+        torch.cuda.synchronize()
+        ms = {name: start.elapsed_time(e) for name, e in done.items()}
+        print(f"[concurrent] {first} first: attention done after {ms['attention']:.3f} ms, unpack after {ms['unpack']:.3f}",
+              flush=True)
+        shares.append(ms["attention"] / ms["unpack"])
+    assert sorted(shares[1:])[2] < 0.5   # (0.06 and 0.14 as it should be; held back 0.2 to 0.45 and 1.04)
