@@ -1143,7 +1143,9 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
         for (int i = 0; i < 4; ++i)
           *reinterpret_cast<f32x4*>(part + ((dt * 4 + i) * 256 + tid) * 4) =
               f32x4{o_acc[dt][4 * i], o_acc[dt][4 * i + 1], o_acc[dt][4 * i + 2], o_acc[dt][4 * i + 3]};
-      *reinterpret_cast<f32x2*>(part + 64 * 256 + tid * 2) = f32x2{m_run, l_run};
+      // (a piece whose every score is NaN has no reference either: with one, the merge does not take it for a piece that
+      // saw no key, and its sum makes the row NaN)
+      *reinterpret_cast<f32x2*>(part + 64 * 256 + tid * 2) = f32x2{l_run == l_run ? m_run : 0.f, l_run};
     }
   } else {
     // Register dump, 16 bytes per lane per store: fully coalesced.  The chunks of a unit may run on different XCDs,
@@ -1694,7 +1696,7 @@ __global__ __launch_bounds__(64 * HW, HW == 8 ? 1 : 2) void attn_decode_kernel(c
 #pragma unroll
           for (int j = 0; j < 4; ++j) so[32 * dt + 8 * i + j] = o_acc[dt][4 * i + j];
       if (g2 == 0) {
-        stage[rows * 128 + r] = m_run;
+        stage[rows * 128 + r] = l_row == l_row ? m_run : 0.f;  // (NaN scores only: not a piece that saw no key)
         stage[rows * 129 + r] = l_row;
       }
     }

@@ -344,6 +344,31 @@ def test_cuts_of_direct_calls(oracle_mod, prefix, new, tiles, pieces):
     assert header[HDR_PLAN] == PLAN_DIRECT and (header[HDR_CHUNK], header[HDR_ITEMS]) == (tiles, pieces)
 
 
+@pytest.mark.parametrize("group,prefix,new,first_key,tuning", [
+    (4, 2048, 1, 2048, dict()),                          # decode: the one new key is a tile, and a piece, of its own
+    (4, 64, 1, 64, dict()),
+    (16, 1024, 2, 992, dict()),
+    (4, 3001, 45, 2816, dict()),                         # direct: the last of twelve pieces of four tiles
+    (2, 6000, 20, 5824, dict()),                         # of 24
+    (4, 3001, 45, 2816, dict(coarse=-1, c_min=1)),       # the same by the work list
+])
+def test_keys_that_are_not_numbers_in_a_piece_of_their_own(group, prefix, new, first_key, tuning):
+    """Keys of one kv-head are NaN from `first_key` on, which every row sees: a piece with no other keys has no reference and a
+    sum that is NaN.  It is not one that saw no key: the head's rows are NaN, and nothing else is touched."""
+    cfg = _cfg(n_sessions=1, n_kv_heads=8, n_q_heads=8 * group, n_blocks=512, prefix_dist=("const", prefix))
+    sess = W.make_sessions(cfg, 113, new_lens=np.array([new]))
+    k_pool, v_pool, q, k_new, v_new = W.make_attn_inputs(cfg, sess, 113)
+    clean = gpu_attention(cfg, sess, (k_pool, v_pool, q, k_new, v_new), tuning=S.AttnTuning(**tuning))
+    for key in range(first_key, prefix):
+        k_pool[sess.block_table[0, key // 16], key % 16, 3] = W.SENTINEL16
+    k_new[:, 3] = W.SENTINEL16
+    got = widen(gpu_attention(cfg, sess, (k_pool, v_pool, q, k_new, v_new), tuning=S.AttnTuning(**tuning)))
+    sees = np.zeros(got.shape, dtype=bool)
+    sees[:, 3 * group:4 * group] = True
+    assert np.isnan(got[sees]).all()
+    assert np.array_equal(got[~sees], widen(clean)[~sees])
+
+
 @pytest.mark.parametrize("cut", [False, True])
 @pytest.mark.parametrize("n_sessions", [1, 2, 4, 5, 16, 17, 255, 257, 700])
 def test_work_list_of_any_number_of_sessions(oracle_mod, n_sessions, cut):
