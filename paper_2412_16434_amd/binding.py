@@ -432,14 +432,22 @@ _attn_call = None
 
 
 def _load_attn_call():
-    """The compiled marshalling of the ordinary attention call (``csrc/attn_call.c``), bound to the library's entry point."""
+    """The compiled marshalling of the ordinary attention call (``csrc/attn_call.c``), bound to the library's entry point; where
+    it is not built (or not for this interpreter), or torch lacks what it needs, what leaves every call to the general path."""
     global _attn_call
-    lib, torch = load_library(), _torch()
+    try:
+        lib = load_library()
+    except ImportError:  # (the general path says so, behind its checks)
+        return lambda *args: None
+    torch = _torch()
     raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
-    if raw is None or device is None:  # (a torch without them: the general path)
+    try:
+        from . import _attn_call as module
+    except ImportError:
+        module = None
+    if module is None or raw is None or device is None:
         _attn_call = lambda *args: None
     else:
-        from . import _attn_call as module
         module.bind(C.cast(lib.symph_prefix_prefill_attn, C.c_void_p).value, torch.bfloat16, torch.float32, torch.int32, raw,
                     device)
         _attn_call = module.attn

@@ -10,11 +10,28 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsymph.so")
-CALL_LIB = os.path.join(HERE, "_attn_call.so")  # Python extension module: the attention call's marshalling (host code only)
+# Python extension module: the attention call's marshalling (host code only).  The name says which interpreter it is for.
+CALL_LIB = os.path.join(HERE, "_attn_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ("api.hip", "kv_migrate.hip", "prefill_attn.hip", "rows_attn.hip", "attn_static.hip", "kv_pool.cpp")  # the last one is host code only
 # packed-fp32 instructions are switched off for every device compile
 HIPCC_FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
                "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
+
+
+def build_attn_call() -> bool:
+    """Compile the attention call's marshalling.  The binding does without it where the interpreter's headers are absent."""
+    include = sysconfig.get_paths()["include"]
+    for old in (CALL_LIB, os.path.join(HERE, "_attn_call.so")):  # (the second: a name that any interpreter would load)
+        if os.path.exists(old):
+            os.remove(old)
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        print(f"[build] no Python.h in {include}: the attention call is marshalled in Python", file=sys.stderr)
+        return False
+    tmp = CALL_LIB + f".tmp{os.getpid()}"
+    subprocess.check_call(["gcc", "-O2", "-std=c11", "-Wall", "-shared", "-fPIC", "-I", include, "-I",
+                           os.path.join(ROOT, "include"), os.path.join(CSRC, "attn_call.c"), "-o", tmp])
+    os.replace(tmp, CALL_LIB)
+    return True
 
 
 def build(verbose: bool = False) -> str:
@@ -43,10 +60,7 @@ def build(verbose: bool = False) -> str:
             print(out)
     if failed:
         raise RuntimeError("hipcc failed")
-    tmp = CALL_LIB + f".tmp{os.getpid()}"
-    subprocess.check_call(["gcc", "-O2", "-std=c11", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], "-I",
-                           os.path.join(ROOT, "include"), os.path.join(CSRC, "attn_call.c"), "-o", tmp])
-    os.replace(tmp, CALL_LIB)
+    build_attn_call()
     tmp = LIB + f".tmp{os.getpid()}"
     subprocess.check_call([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp, *objs])
     os.replace(tmp, LIB)

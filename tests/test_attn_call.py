@@ -1,11 +1,15 @@
 """The compiled marshalling of the attention call against the general path: it takes the same calls with the same arguments,
 and leaves everything it does not take, errors above all, to the general path."""
+import os
+import sys
+import sysconfig
+
 import numpy as np
 import pytest
 import torch
 
 import paper_2412_16434_amd as S
-from paper_2412_16434_amd import binding
+from paper_2412_16434_amd import binding, build
 
 
 def _call(dev, dtype=torch.bfloat16, d=128):
@@ -30,6 +34,38 @@ def test_calls_on_the_host_are_left_to_the_general_path():
     with pytest.raises(ValueError, match="must be a device tensor"):
         S.prefix_prefill_attn(**a)
     assert binding._load_attn_call()() is None and binding._load_attn_call()(*range(14)) is None
+
+
+@pytest.fixture
+def without_the_module(monkeypatch):
+    """The compiled marshalling as if it had not been built."""
+    monkeypatch.setattr(binding, "_attn_call", None)
+    monkeypatch.delattr(S, "_attn_call", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2412_16434_amd._attn_call", None)
+
+
+def test_without_the_module_the_general_path_decides(without_the_module):
+    with pytest.raises(ValueError, match="must be a device tensor"):
+        S.prefix_prefill_attn(**_call("cpu"))
+    assert binding._attn_call is not None, "the import is tried again by every call"
+
+
+def test_without_the_library_the_checks_come_first(monkeypatch):
+    monkeypatch.setattr(binding, "_attn_call", None)
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_LIB_PATH", "/nonexistent/libsymph.so")
+    with pytest.raises(ValueError, match="must be a device tensor"):
+        S.prefix_prefill_attn(**_call("cpu"))
+
+
+def test_the_file_is_for_one_interpreter(monkeypatch, tmp_path, capsys):
+    assert build.CALL_LIB.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    # where the interpreter's headers are absent there is none, and building goes on
+    monkeypatch.setattr(build, "CALL_LIB", str(tmp_path / "call.so"))
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert build.build_attn_call() is False and not os.listdir(tmp_path)
+    assert "Python.h" in capsys.readouterr().err
 
 
 def _workspace(a):
@@ -57,6 +93,20 @@ def test_same_call_both_ways(dtype, d):
         S.prefix_prefill_attn(**a, workspace=ws)
     side.synchronize()
     assert torch.equal(by_c, a["out"])
+
+
+@pytest.mark.gpu
+def test_same_call_without_the_module(without_the_module, monkeypatch):
+    a = _call("cuda:0")
+    ws = _workspace(a)
+    S.prefix_prefill_attn(**a, workspace=ws)
+    torch.cuda.synchronize()
+    by_python = a["out"].clone()
+    monkeypatch.undo()
+    a["out"].zero_()
+    assert _compiled(a, ws) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(by_python, a["out"])
 
 
 @pytest.mark.gpu
