@@ -458,7 +458,7 @@ def prefix_prefill_attn(cache: KVCache, layer: int, q, k_new, v_new, out, cu_new
                         max_new_len: int, max_prefix_len: int, scale: float, workspace=None, stream=None,
                         tuning: Optional[AttnTuning] = None) -> None:
     """out[T][H_q][d] <- attention of the new turn over [cached prefix ; causal new tokens] for one layer."""
-    if stream is None and tuning is None:
+    if stream is None and tuning is None and type(cache) is KVCache:  # (a subclass may have a struct() of its own)
         status = (_attn_call or _load_attn_call())(cache.k_pool, cache.v_pool, layer, q, k_new, v_new, out, cu_new_lens,
                                                    prefix_lens, block_table, max_new_len, max_prefix_len, scale, workspace)
         if status is not None:

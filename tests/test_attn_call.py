@@ -36,6 +36,25 @@ def test_calls_on_the_host_are_left_to_the_general_path():
     assert binding._load_attn_call()() is None and binding._load_attn_call()(*range(14)) is None
 
 
+def test_a_cache_that_describes_itself_takes_the_general_path(monkeypatch):
+    """The compiled marshalling reads the pools; what a subclass says in ``struct()`` it does not see."""
+    class LastBlocks(S.KVCache):
+        def struct(self):
+            st = super().struct()
+            st.n_blocks = 2
+            return st
+
+    taken = []
+    monkeypatch.setattr(binding, "_attn_call", lambda *args: taken.append(args) or 0)
+    a = _call("cpu")
+    S.prefix_prefill_attn(**a)
+    assert len(taken) == 1
+    a["cache"] = LastBlocks(a["cache"].k_pool, a["cache"].v_pool)
+    with pytest.raises(ValueError, match="must be a device tensor"):
+        S.prefix_prefill_attn(**a)
+    assert len(taken) == 1
+
+
 @pytest.fixture
 def without_the_module(monkeypatch):
     """The compiled marshalling as if it had not been built."""
