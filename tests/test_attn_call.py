@@ -104,14 +104,27 @@ def test_same_call_both_ways(dtype, d):
     S.prefix_prefill_attn(**a, workspace=ws, stream=torch.cuda.current_stream())   # (a stream: the general path)
     torch.cuda.synchronize()
     assert torch.equal(by_c, a["out"]) and bool(by_c.float().abs().sum() > 0)
-    # another stream is the current one: the call goes there
-    side = torch.cuda.Stream()
+
+
+@pytest.mark.gpu
+def test_the_call_goes_to_the_current_stream():
+    """On a side stream: a delay, the queries copied over other values, the call.  Launched anywhere else it would not wait for the
+    copy and read the other values."""
+    a = _call("cuda:0")
+    ws = _workspace(a)
+    S.prefix_prefill_attn(**a, workspace=ws)
+    torch.cuda.synchronize()
+    want, q = a["out"].clone(), a["q"]
+    a["q"] = torch.ones_like(q)
     a["out"].zero_()
+    side = torch.cuda.Stream()
     torch.cuda.synchronize()
     with torch.cuda.stream(side):
-        S.prefix_prefill_attn(**a, workspace=ws)
+        torch.cuda._sleep(20_000_000)   # (10 to 200 ms)
+        a["q"].copy_(q)
+        assert _compiled(a, ws) == 0
     side.synchronize()
-    assert torch.equal(by_c, a["out"])
+    assert torch.equal(want, a["out"])
 
 
 @pytest.mark.gpu
