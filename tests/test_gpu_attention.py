@@ -175,24 +175,26 @@ def test_decode_units_and_merges(oracle_mod, hkv, group, prefix, new, stated):
     assert np.sqrt(np.sum((f(got) - f(main)) ** 2) / np.sum(f(main) ** 2)) <= 1e-2
 
 
-@pytest.mark.parametrize("hkv,group,prefix,new", [
-    (8, 4, [2047], [1]),                                 # a workgroup per row: 64 pieces, one round of a row's half-waves
-    (8, 1, [2080], [1]),                                 # 66: a second round
-    (2, 16, [9000, 40], [2, 1]),                         # 283 pieces of 32 rows
-    (8, 2, [1500] + [20] * 24, [3] * 25),                # four rows per workgroup, six rows, 47 pieces of one session
-    (8, 1, [1200, 900] + [10] * 44, [3] * 46),           # three rows: half-waves without one
-    (8, 4, [600] + [5] * 69, [8] * 70),                  # rows left for a second turn
-    (3, 8, [1500] + [5] * 15, [4] + [3] * 15),           # single-wave workgroups
+@pytest.mark.parametrize("hkv,group,prefix,new,tiles", [
+    (8, 4, [2047], [1], 64),                             # a workgroup per row: 64 pieces, one round of a row's half-waves
+    (8, 1, [2080], [1], 66),                             # a second round
+    (2, 16, [9000, 40], [2, 1], 282 + 2),                # 282 pieces of 32 rows
+    (8, 2, [1500] + [20] * 24, [3] * 25, 47 + 24),       # four rows per workgroup, six rows, 47 pieces of one session
+    (8, 1, [1200, 900] + [10] * 44, [3] * 46, 38 + 29 + 44),   # three rows: half-waves without one
+    (8, 4, [600] + [5] * 69, [8] * 70, 19 + 69),         # rows left for a second turn
+    (3, 8, [1500] + [5] * 15, [4] + [3] * 15, 47 + 15),  # single-wave workgroups
 ])
-def test_merges_of_many_pieces(oracle_mod, hkv, group, prefix, new):
+def test_merges_of_many_pieces(oracle_mod, hkv, group, prefix, new, tiles):
+    """As many 32-key tiles as stated, and more key ranges than that: every tile is a piece of its own."""
     cfg = _cfg(n_sessions=len(new), n_kv_heads=hkv, n_q_heads=hkv * group, n_blocks=-(-max(prefix) // 16) * len(new) + 8,
                prefix_dist=("const", max(prefix)))
     sess = W.make_sessions(cfg, 89, new_lens=np.array(new))
     sess.prefix_lens[:] = prefix
     sess.buf_token_offsets[1:] = np.cumsum(prefix)
-    header = []
-    check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 89), label="merges", header=header)
-    assert header[HDR_PLAN] == PLAN_DECODE
+    header, decode_wgs = [], 512
+    check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 89), label="merges", header=header,
+          tuning=S.AttnTuning(decode_wgs=decode_wgs))
+    assert header[HDR_PLAN] == PLAN_DECODE and header[HDR_DECODE_TILES] == tiles <= 4 * decode_wgs // hkv
 
 
 @pytest.mark.parametrize("hkv,group,prefix,new", [
