@@ -256,7 +256,7 @@ __device__ __forceinline__ void put_upper_halves(bf16x8& v, int at, float x, flo
   v = __builtin_bit_cast(bf16x8, words);
 }
 
-template <typename T, int D, int W>
+template <typename T, int D, int W, bool EARLY>
 __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p) {
   constexpr bool kBf16 = sizeof(T) == 2;
   constexpr int R = RowsTile<T>::R;
@@ -278,18 +278,19 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
   const int n = lane & (R - 1);   // query row of this lane; also its row of the K operand
   const int kg = lane / R;        // its share of the contraction index: half (bf16) or quarter (fp32) of the wave
   auto block_of = [&](int key) { return p.bs_shift >= 0 ? key >> p.bs_shift : key / p.block_size; };
-  // A single session's row of the table needs no lengths to be found: the block ids of the wave's first two key blocks are
-  // asked for beside them, one trip to memory less in front of the first K rows.  (Whether the keys exist is seen later; an
-  // index past the row's end reads its last entry.)  One fp32 session of 256 tokens 9.17 -> 8.60 us on the GPU, of 1000 with
-  // 128-wide heads 31.5 -> 31.0; bf16, whose first block waits for two ids per lane group, 7.60 -> 7.71: not there.
-  int early_id[2] = {-1, -1};
-  const bool early = !kBf16 && p.n_sessions == 1 && p.table != nullptr && p.table_stride > 0;
-  if (early) {
+  // EARLY: a single fp32 session.  Its row of the table needs no lengths to be found: the block ids of the wave's first two key
+  // blocks are asked for beside them, one trip to memory less in front of the first K rows.  (Whether the keys exist is seen
+  // later; an index past the row's end reads its last entry.)  One session of 256 tokens 9.26 -> 8.70 us, of 1000 with 128-wide
+  // heads 31.6 -> 31.3; bf16, whose first block waits for two ids per lane group, 7.60 -> 7.71: not there.  An instantiation of
+  // its own: as a branch in every call it made three sessions of 256 tokens 9.35 -> 9.60.
+  int early_id[2];
+  if constexpr (EARLY) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) early_id[i] = p.table[(unsigned)min(block_of((wave + i * W) * R + n), p.table_stride - 1)];
   }
   int s, cu_s, cu_next, P;
-  if (p.n_sessions > 1 && p.n_sessions <= 64) {  // a session per lane: one trip to memory for all there is to know of it
+  if (!EARLY && p.n_sessions > 1 && p.n_sessions <= 64) {
+    // a session per lane: one trip to memory for all there is to know of it
     const int i = min(lane, p.n_sessions - 1);
     const int cu_i = p.cu_new_lens[i], next_i = p.cu_new_lens[i + 1], P_i = p.prefix_lens[i];
     s = __popcll(__ballot(lane < p.n_sessions && (lane == 0 || first_slot(lane, cu_i) <= slot))) - 1;
@@ -297,7 +298,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
     cu_next = __builtin_amdgcn_readlane(next_i, s);
     P = __builtin_amdgcn_readlane(P_i, s);
   } else {
-    s = wave_last(p.n_sessions, [&](int i) { return first_slot(i, p.cu_new_lens[i]) <= slot; });
+    s = EARLY ? 0 : wave_last(p.n_sessions, [&](int i) { return first_slot(i, p.cu_new_lens[i]) <= slot; });
     cu_s = p.cu_new_lens[s];
     cu_next = p.cu_new_lens[s + 1];
     P = p.prefix_lens[s];
@@ -327,7 +328,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
   };
   auto first_id = [&](int i) {  // of the wave's block i (0 or 1)
     const int blk = wave + i * W, key = blk * R + n;
-    if (!early) return fetch_id(blk);
+    if constexpr (!EARLY) return fetch_id(blk);
     return blk < n_blocks_k && key < P && block_of(key) < p.table_stride ? early_id[i] : -1;
   };
   auto row_of = [&](const void* pool, const void* fresh, int key, int id) {
@@ -544,9 +545,15 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
         }
     };
     int run = 0;
+    // With 64 columns both ids before the first K rows: one that is still under way when the loop begins makes the compiler
+    // wait in every turn for all that is under way (six sessions of 300 to 2000 tokens 33.0 -> 30.9 us, three of 8192 116.8 ->
+    // 109.4, three of 256 9.31 -> 8.98).  With 128 columns that is slower (three of 8192 184.9 -> 187.0, one of 256 to 4000 the
+    // same), and where the ids are early nothing is under way.
+    constexpr bool kBothIds = D == 64 && !EARLY;
     int id_next = first_id(0);
+    const int id_second = kBothIds ? first_id(1) : -1;
     if (wave < n_blocks_k) load_block(wave, id_next);
-    id_next = first_id(1);
+    id_next = kBothIds ? id_second : first_id(1);
     for (int blk = wave; blk < n_blocks_k; blk += W) {
       f32x4 sc[4];
 #pragma unroll
@@ -661,10 +668,13 @@ static int32_t launch_rows(const AttnArgs& a, hipStream_t stream) {
   // 344, 83 / 74 at 608; with 128-wide heads 52.5 / 62, 92.6 / 94, 135 / 138; 150 to 300 tokens: 8.8 / 8.7, 12.1 / 9.1, 17.1 /
   // 11.4 and 15.3 / 16.7, 27.6 / 23.1, 39.6 / 34.4.
   if ((address_bits & 15) == 0 && groups <= 0x7FFFFFFFLL) {
-    if (groups <= kComputeUnits)
-      hipLaunchKernelGGL((attn_rows_kernel<T, D, 8>), dim3((unsigned)groups), dim3(512), 0, stream, p);
+    constexpr bool kFp32 = sizeof(T) == 4;
+    if (groups > kComputeUnits)
+      hipLaunchKernelGGL((attn_rows_kernel<T, D, 4, false>), dim3((unsigned)groups), dim3(256), 0, stream, p);
+    else if (kFp32 && a.n_sessions == 1 && a.max_prefix_len > 0)  // (a prefix: there is a table, one that may be read)
+      hipLaunchKernelGGL((attn_rows_kernel<T, D, 8, kFp32>), dim3((unsigned)groups), dim3(512), 0, stream, p);
     else
-      hipLaunchKernelGGL((attn_rows_kernel<T, D, 4>), dim3((unsigned)groups), dim3(256), 0, stream, p);
+      hipLaunchKernelGGL((attn_rows_kernel<T, D, 8, false>), dim3((unsigned)groups), dim3(512), 0, stream, p);
   } else
     hipLaunchKernelGGL((attn_row_kernel<T, D>), dim3((unsigned)rows), dim3(64), 0, stream, p);
   return hipGetLastError() == hipSuccess ? SYMPH_OK : SYMPH_ELAUNCH;

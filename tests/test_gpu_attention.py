@@ -6,6 +6,7 @@ thousands of Gaussian keys gives outputs of magnitude ~1e-2, every case is ALSO 
 """
 import numpy as np
 import pytest
+import torch
 
 import paper_2412_16434_amd as S
 import workloads as W
@@ -471,6 +472,35 @@ def test_a_single_fp32_session(oracle_mod, d, group, bs, prefix, new):
                scale=1.0 / np.sqrt(d), prefix_dist=("const", prefix))
     sess = W.make_sessions(cfg, 103, new_lens=np.array([new]))
     check(oracle_mod, cfg, sess, W.make_attn_inputs(cfg, sess, 103), label="one session")
+
+
+@pytest.mark.parametrize("d,bs,prefix,new,stated_prefix", [
+    (64, 16, 100, 5, 100),                               # one session and several: kernels of their own, one result
+    (64, 16, 700, 60, 700),
+    (128, 16, 400, 33, 512),
+    (128, 24, 250, 7, 250),
+    (64, 16, 300, 5, 0),                                 # a bound of zero that is not true: the table is read all the same
+    (64, 16, 0, 9, 0),
+])
+def test_a_fp32_session_alone_and_beside_others(d, bs, prefix, new, stated_prefix):
+    dims = dict(device="cuda:0", dtype=torch.float32)
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(107)
+    rand = lambda *shape: torch.empty(shape, **dims).normal_(0.0, 1.0, generator=g)
+    cols = max(1, -(-prefix // bs))
+    cache = S.KVCache(rand(1, 2 * cols, bs, 4, d), rand(1, 2 * cols, bs, 4, d))
+    table = torch.full((2, max(cols, -(-stated_prefix // bs))), -1, dtype=torch.int32, device="cuda:0")
+    table[:, :cols] = torch.randperm(2 * cols, generator=torch.Generator().manual_seed(107)).to(torch.int32).view(2, cols)
+    q, k, v = rand(2 * new, 8, d), rand(2 * new, 4, d), rand(2 * new, 4, d)
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device="cuda:0")
+    outs = []
+    for n in (1, 2):
+        out = torch.full((n * new, 8, d), float("nan"), **dims)
+        S.prefix_prefill_attn(cache, 0, q[:n * new], k[:n * new], v[:n * new], out, i32(range(0, n * new + 1, new)),
+                              i32([prefix] * n), table[:n] if prefix else None, new, stated_prefix, d ** -0.5)
+        outs.append(out[:new])
+    torch.cuda.synchronize()
+    assert bool(outs[0].isfinite().all()) and torch.equal(*outs)
 
 
 @pytest.mark.parametrize("d,hkv,group,bs", [(64, 4, 4, 16), (128, 2, 3, 16), (128, 4, 2, 8)])
