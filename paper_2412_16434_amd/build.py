@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -19,7 +20,7 @@ HIPCC_FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-Xclang",
 
 
 def build_attn_call() -> bool:
-    """Compile the attention call's marshalling.  The binding does without it where the interpreter's headers are absent."""
+    """Compile the attention call's marshalling.  The binding does without it where the interpreter's headers or gcc are absent."""
     include = sysconfig.get_paths()["include"]
     for old in (CALL_LIB, os.path.join(HERE, "_attn_call.so")):  # (the second: a name that any interpreter would load)
         if os.path.exists(old):
@@ -27,8 +28,12 @@ def build_attn_call() -> bool:
     if not os.path.exists(os.path.join(include, "Python.h")):
         print(f"[build] no Python.h in {include}: the attention call is marshalled in Python", file=sys.stderr)
         return False
+    gcc = shutil.which("gcc")
+    if gcc is None:
+        print("[build] no gcc: the attention call is marshalled in Python", file=sys.stderr)
+        return False
     tmp = CALL_LIB + f".tmp{os.getpid()}"
-    subprocess.check_call(["gcc", "-O2", "-std=c11", "-Wall", "-shared", "-fPIC", "-I", include, "-I",
+    subprocess.check_call([gcc, "-O2", "-std=c11", "-Wall", "-shared", "-fPIC", "-I", include, "-I",
                            os.path.join(ROOT, "include"), os.path.join(CSRC, "attn_call.c"), "-o", tmp])
     os.replace(tmp, CALL_LIB)
     return True

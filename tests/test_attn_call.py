@@ -79,9 +79,13 @@ def test_without_the_library_the_checks_come_first(monkeypatch):
 
 def test_the_file_is_for_one_interpreter(monkeypatch, tmp_path, capsys):
     assert build.CALL_LIB.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
-    # where the interpreter's headers are absent there is none, and building goes on
+    # where gcc or the interpreter's headers are absent there is none, and building goes on
     monkeypatch.setattr(build, "CALL_LIB", str(tmp_path / "call.so"))
     monkeypatch.setattr(build, "HERE", str(tmp_path))
+    with monkeypatch.context() as m:
+        m.setenv("PATH", str(tmp_path))
+        assert build.build_attn_call() is False and not os.listdir(tmp_path)
+        assert "gcc" in capsys.readouterr().err
     monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
     assert build.build_attn_call() is False and not os.listdir(tmp_path)
     assert "Python.h" in capsys.readouterr().err
