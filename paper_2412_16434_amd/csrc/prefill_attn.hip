@@ -139,8 +139,8 @@ __device__ __forceinline__ void block_inclusive_scan2(int& a, int& b, int (*wave
 // It is a chain that one compute unit walks, 20 000 clocks for 512 units.  What a batch does not need is left out: the
 // divisions, block-wide sums and counters of cuts where no unit is cut, the barrier behind the cut's length, which every wave
 // works out for itself, half of the steps of the search for a unit's session: 16 500.  Calls: 16 x 78 new tokens over 99,
-// 20.7 -> 19.8 us; 70 x 20..60 over 100..300, 37.0 -> 35.4; 256 x 4..30 over 16..64, 39.5 -> 38.7; 256 sessions of a mean of 600,
-// 262.3 -> 261.6.  512 threads are as fast, 1024 slower; two 16-byte loads for a unit's eight block ids change nothing.
+// 20.7 -> 19.6 us; 70 x 20..60 over 100..300, 37.0 -> 35.4; 256 x 4..30 over 16..64, 39.5 -> 38.7; long calls the same.  512
+// threads are as fast, 1024 slower; two 16-byte loads for a unit's eight block ids change nothing.
 __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(const SchedParams p) {
   __shared__ int unit_off[kSchedMaxSessions + 1];
   __shared__ int len_new[kSchedMaxSessions], len_prefix[kSchedMaxSessions], cu_of[kSchedMaxSessions];
@@ -588,12 +588,12 @@ constexpr int kTileBytes = 16 * kGroupBytes;  // 16640
 // sessions of 500 to 32 768 tokens, 8 to 1000 new ones, 2 to 8 kv-heads; the cut it chooses is on average 0.5 % slower
 // than the best one tried): a tile takes 1.1 while every workgroup has its CU to itself and up to 1.65 when two share it,
 // a further round of workgroups 14 beside its tiles and a piece that has to be combined 0.018 (its 66 KB written and
-// read back with the merge kernel the timings were taken with).  Today's merge kernel is faster, but with a price of 0.012 the
-// calls are not (45 new tokens over 3001 20.0 us for 19.7, 160 over 3001 29.1 for 28.9, 6 x 20 over 2000 22.6 for 21.2), and
-// every cut that moves makes probabilities be rounded against other references, which moves outputs by 2.8e-3.  Against the
-// scheduling kernel and the combining last piece: 45 new tokens over 3001, 30.0 -> 17 to 20 us (47 before either was
-// reworked); 17 over 16 000, 53 -> 24; 8 x 64 .. 128 over 1500 .. 3000, 69 -> 55; 512 over 32 768 in groups of eight heads,
-// 496 -> 490.
+// read back with the merge kernel the timings were taken with).  Today's merge kernel is faster, but a price of 0.012 serves
+// one of twelve calls (45 new tokens over 3001 17.0 us for 17.5), costs three (6 x 20 over 2000 22.9 for 21.8, 3 x 20 .. 40
+// over 8000 37.7 for 35.5, 160 over 3001 26.6 for 26.0), and every cut that moves makes probabilities be rounded against other
+// references, which moves outputs by 2.8e-3.  Against the work list: 45 new tokens over 3001, 29.7 -> 17.5 us (47 before the
+// scheduling kernel was reworked); 17 over 16 000, 53 -> 24; 8 x 64 .. 128 over 1500 .. 3000, 75 -> 55; 512 over 32 768 in
+// groups of eight heads, 504 -> 502.
 constexpr int kDirectUnits = 64;
 constexpr float kTileAlone = 1.1f, kTilePaired = 1.65f, kRoundFixed = 14.f, kPieceMerge = 0.018f;
 
@@ -1229,8 +1229,8 @@ __global__ __launch_bounds__(256, 2) void attn_mfma_kernel(const MfmaParams p) {
 // Combines the pieces of split units in direct mode: PARTS workgroups per (unit, kv-head), an equal part of the sixteen 16-byte
 // vectors of a thread's slot for each.  Few units are cut into many pieces, and what counts is how few trips to memory a thread
 // makes: sixteen workgroups of one vector, sixteen pieces at a time (45 new tokens over 3001, 12 pieces: 18.8 us with four
-// workgroups and eight pieces at a time, 17.6; 17 over 16 000, 32 pieces: 27.1 and 23.6).  Many units have few pieces each, and
-// every workgroup reads their references and sums again: four workgroups (8 x 100 over 3000: 43.3 us, 44.7 with eight).
+// workgroups and eight pieces at a time, 17.5; 17 over 16 000, 32 pieces: 27.1 and 23.8).  Many units have few pieces each, and
+// every workgroup reads their references and sums again: four workgroups (8 x 100 over 3000: 63.7 us, 67.9 with sixteen).
 template <int G, int PARTS>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const MfmaParams p) {
   constexpr int TW = 128 / G / 4;  // tokens per wave, as in attn_mfma_kernel
@@ -1841,7 +1841,11 @@ static AttnTuning resolve_tuning(const symph_attn_tuning* t) {
 // 69.7, 256 79.3 / 75.0); above it at most this many workgroups, as far as one per record and kv-head allows.
 constexpr int64_t kMergeSingleRows = 1024, kMergeGroups = 4096;
 
-// Direct calls: (unit, kv-head) pairs up to which a merge has sixteen workgroups each
+// Direct calls: (unit, kv-head) pairs up to which a merge has sixteen workgroups each; above it four.  The pairs are the bound
+// that the grid is made for, total_new_tokens / bmt + n_sessions units: two turns of 22 tokens in groups of four count
+// as three units.  Four /
+// sixteen, in us: 16 pairs 18.7 / 17.5, 24 20.0 / 19.4, 32 22.5 / 22.9 (one turn) and 19.2 / 18.1 (two), 48 26.0 / 26.7, 64
+// 22.2 / 22.3 and 47.0 / 48.0, 96 25.4 / 26.3, 128 34.5 / 35.0, 192 47.9 / 50.8, 264 63.8 / 67.9.
 constexpr unsigned kMergeFewPairs = 32;
 
 struct MfmaPlan {
@@ -1924,12 +1928,15 @@ static bool make_plan(MfmaPlan& pl, int32_t n_sessions, int32_t n_q_heads, int32
   // Direct calls: few units, and few enough for the chip.  Cutting what fills it half already gains little, and a cut that
   // takes a second round of workgroups loses; a long turn's units grow with their place in it, so that the work list's
   // longest-first order is worth more than the scheduling kernel, unless a much longer prefix makes them alike.  Below half
-  // of the slots the list is as fast or faster only for such turns (4 heads, 1500 new tokens over none, 33 us by the list,
-  // 35 directly; 2 x 772 over 129, 28 and 31; but 3 turns of up to 780 over 15 000, 105 and 76).  Above it short turns over
-  // short prefixes are better listed (16 x 78 over 99, 17 and 18; 34 x 5 over 500, 21 and 23), long prefixes cut directly
-  // (8 x 143 over 1724, 53 and 46; 512 over 32 768 in groups of eight, 496 and 490) up to five sixths of the slots (6 x 343
-  // over 5656, 132 and 140; 20 x 70 over 300, 25 and 29).  175 batches of 1 to 60 sessions, 0 to 20 000 cached tokens and 1
-  // to 2000 new ones: 0.78 of the time of list and scheduler as they were, the better of the two for each 0.77, none slower.
+  // of the slots the list is as fast only for such turns (groups of four on four kv-heads: 1500 new tokens over none, 32.9 us by
+  // the list, 31.9 directly; 2 x 772 over 129, 30.5 and 30.3; but 3 x 600 over 15 000 on two, 164 and 128).  Above it short
+  // turns over short prefixes are better listed (groups of four on eight: 16 x 78 over 99, 19.6 and 21.0; 20 x 70 over 300, 25.4
+  // and 28.2), long prefixes cut directly (8 x 143 over 1724, 77 and 56; 512 over 32 768 in groups of eight, 504 and 502) up to
+  // five sixths of the slots (6 x 343 over 5656 in groups of two, 144 and 147).  The lines were fitted to 175 batches of 1 to 60
+  // sessions, 0 to 20 000 cached tokens and 1 to 2000 new ones with the list and direct calls of that time.  Both have become
+  // faster since, direct calls more, and the lines were left where they were (a batch that changes sides is cut elsewhere, and
+  // its outputs are others): 30 x 30 over 700 or 800 is listed and takes 44.7 and 47.4 us where a direct call takes 31.6 and
+  // 34.8, 34 x 5 .. 20 over 500 in groups of eight 40 and 28.
   const int64_t wg_units = pl.units_bound * (int64_t)n_kv_heads;
   const bool short_turns = max_new_len * wg_units <= 160 * (int64_t)tu.slots;
   const bool direct_pays =

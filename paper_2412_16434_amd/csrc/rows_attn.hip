@@ -140,13 +140,14 @@ __global__ __launch_bounds__(64) void attn_row_kernel(const RowsParams p) {
 // neighbour of the 64-bit result: 1.7e-3 of them for 1.1e-4 to 1.7e-4.)
 //
 // Measured against one wave per row (attn_row_kernel above, 32-bit arithmetic on the vector unit, lanes over keys): six
-// sessions of 300 to 2000 tokens, 64-wide heads, 380 -> 17.3 us; one fp32 session of 256 tokens, 24.6 -> 9.3 us, which is the
-// call itself; three fp32 sessions of 8192, 775 -> 172; 100 new tokens of eight sessions of 2000 with 64-wide heads,
-// 1949 -> 51.  The error against 64 bits is the same in bf16 and lower in fp32 (2.9e-7 for 4.7e-7 at 128 x 8000 keys).  A
-// small call is a chain load -> product -> softmax -> product, and a full chip counts instructions of the vector unit: about
-// 1000 of its clocks per 32-key block, 500 of the matrix cores'.  Tried and not kept: two key blocks per turn (as fast at best,
-// fp32 slower), the next block's first product in front of this one's exponentials (17 -> 23 us), twelve or six waves a tile
-// (17 -> 21), block ids asked for without a branch (the compiler waits for them at once: 17 -> 23).
+// sessions of 300 to 2000 tokens, 64-wide heads, 380 -> 17.7 us; one fp32 session of 256 tokens, 24.7 -> 8.7; 16 new tokens of
+// three fp32 sessions of 8192, eight heads on two kv-heads, 385 -> 109 with 64-wide heads and 798 -> 185 with 128-wide ones;
+// 100 new tokens of eight sessions of 2000 with 64-wide heads, 1921 -> 51.  The error against 64 bits is the same in bf16 and
+// lower in fp32 (2.9e-7 for 4.7e-7 at 128 x 8000 keys).  A small call is a chain load -> product -> softmax -> product, and a
+// full chip counts instructions of the vector unit: about 1000 of its clocks per 32-key block, 500 of the matrix
+// cores'.  Tried and not kept: two key blocks per turn (as fast at best, fp32 slower), the next block's first product in front
+// of this one's exponentials (17 -> 23 us), twelve or six waves a tile (17 -> 21), block ids asked for without a branch (the
+// compiler waits for them at once: 17 -> 23).
 //
 // K goes from memory straight into operand registers: a row's D values are the operand's contraction index, and any order
 // of it will do as long as Q has the same.  V is needed transposed: in bf16 through LDS (a tile of the wave's own, rows
@@ -354,7 +355,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_rows_kernel(const RowsParams p
   };
   // 16 bytes of global memory (a pointer that the compiler cannot place is loaded from by an instruction that counts among the
   // LDS reads too); at a scalar base and a lane's 32-bit offset, kept apart for the compiler, which otherwise adds them per lane
-  // (fp32 with 64 columns is 1 to 3 % faster when it does, 128 columns 9 % slower: 3 x 8192 keys 210 -> 187 us)
+  // (fp32 with 64 columns is 1 to 3 % faster when it does, 128 columns 9 % slower)
   auto load_vec = [](const void* at) { return *(const u32x4 __attribute__((address_space(1)))*)(uintptr_t)at; };
   auto load16 = [&](const char* base, unsigned lane_off) {
     if constexpr (kBf16 || D == 128) asm("" : "+s"(base), "+v"(lane_off));

@@ -62,9 +62,10 @@ def test_attention_and_unpack_on_two_streams(oracle_mod):
 
 @pytest.mark.parametrize("first", ["attention", "unpack"])
 def test_attention_is_not_held_back_by_an_unpack(first):
-    """Three calls of attention of eight resumed turns (0.15 ms alone) beside the unpack of 16 arriving sessions (3 ms): workgroups of both share the
-    compute units, so the attention is done long before the unpack, whichever was launched first.  (An unpack that holds LDS
-    leaves no room for an attention workgroup until its own last ones are through: the two then end together.)"""
+    """Three calls of attention of eight resumed turns (0.15 ms alone) beside the unpack of 16 arriving sessions (3 ms):
+    workgroups of both share the compute units, so the attention is done long before the unpack, whichever was launched
+    first.  (An unpack that holds LDS leaves no room for an attention workgroup until its own last ones are through: launched
+    first, it then ends together with the attention.)"""
     dims = dict(dtype=torch.bfloat16, device=DEV)
     i32 = lambda x: torch.tensor(x, dtype=torch.int32, device=DEV)
     tokens, sessions, layers, bs, hkv, d = 4096, 16, 32, 16, 8, 128
